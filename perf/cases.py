@@ -220,7 +220,8 @@ def prepare(case, seed):
         ctx.graph_capture(s["pos"], s["mass"], s["offsets"], case["theta"], s["acc"], s["pot"])
     if kind == "neighbors":
         s["ids"] = torch.arange(n, device="cuda")
-        s["lists"] = torch.zeros(2 * case["ngb"] * n, dtype=torch.int32, device="cuda")
+        # room for the outskirts of a small sphere too, whose kernels reach into the core
+        s["lists"] = torch.zeros((3 * case["ngb"] + 128) * n, dtype=torch.int32, device="cuda")
     if kind == "active":  # the tree of the last rebuild
         ctx.build_tree(s["pos"], s["mass"])
     return s
