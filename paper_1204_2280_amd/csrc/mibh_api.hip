@@ -130,6 +130,9 @@ size_t layout(int64_t n_max, const mibh_params &p, char *base, Buffers *b) {
     t.lvinfo = (uchar4 *)take(4 * n);
     t.blkcnt = (uint32_t *)take(4 * NCOUNTERS * nblk);
     t.ctot = (uint32_t *)take(4 * NCOUNTERS);
+    size_t nranges = 0;  // of the multipole pass: chunks, then one in MP_FAN until one is left
+    for (size_t r = (n + MP_CHUNK - 1) / MP_CHUNK; r > 1; r = (r + MP_FAN - 1) / MP_FAN) nranges += r;
+    t.mlist = (uint32_t *)take(4 * KEY_LEVELS * std::max<size_t>(nranges, 1));
     t.topo = (uint4 *)take(16 * cap_cells);
     t.mp = (double *)take(80 * cap_cells);
     t.delta = (double *)take(8 * cap_cells);
@@ -365,7 +368,7 @@ mibh_status mibh_compute_multipoles(mibh_ctx *ctx) {
     if (st) return st;
     if (ctx->state < 1) return fail(MIBH_ESTATE, "compute_multipoles before build_tree");
     if ((st = mark(ctx, MIBH_STAGE_BUILD))) return st;  // no-op after a build in this step
-    HIP_TRY(launch_multipoles(ctx->b, (unsigned)ctx->nsys, ctx->stream), "multipoles");
+    HIP_TRY(launch_multipoles(ctx->b, (unsigned)ctx->n, (unsigned)ctx->nsys, ctx->stream), "multipoles");
     if ((st = mark(ctx, MIBH_STAGE_MULTIPOLES))) return st;
     ctx->state = 2;
     return MIBH_OK;

@@ -31,6 +31,10 @@ constexpr int SORT_TILE = SORT_THREADS * SORT_ITEMS;
 #endif
 constexpr int BUILD_THREADS = MIBH_BUILD_THREADS;
 constexpr int MAX_WINDOW = 64;          // largest ncrit and group_cap (a build wave's window reach)
+#ifndef MP_CHUNK
+#define MP_CHUNK 2048u  // particles per workgroup of the multipole pass
+#endif
+constexpr unsigned MP_FAN = 64;         // ranges per workgroup of its merge launches
 constexpr int BBOX_BLOCKS = 1024;
 constexpr int ENERGY_BLOCKS = 1024;
 constexpr int ENERGY_THREADS = 256;
@@ -160,6 +164,7 @@ struct Buffers {
     uchar4 *lvinfo;         // per particle: first level started, leaf level, group level, group start
     uint32_t *blkcnt;       // [NCOUNTERS][nblk]
     uint32_t *ctot;         // [NCOUNTERS]
+    uint32_t *mlist;        // multipoles: cells that leave their range of particles, per range size and level
     uint4 *topo;            // cells: first, count, child_first, system<<16 | level<<8 | nchild
     double *mp;             // cells: [10] M, com xyz, S xx yy zz xy xz yz
     double *delta;          // cells: |com - centre|
@@ -210,7 +215,7 @@ hipError_t launch_sort(const Buffers &b, unsigned n, unsigned nsys, hipStream_t 
 inline int sorted_buffer(unsigned nsys) { return nsys > 1 ? (SORT_PASSES + 1) & 1 : SORT_PASSES & 1; }
 hipError_t launch_reorder(const Buffers &b, unsigned n, unsigned nsys, hipStream_t s);
 hipError_t launch_build(const Buffers &b, unsigned n, unsigned nsys, int ncrit, int gcap, hipStream_t s);
-hipError_t launch_multipoles(const Buffers &b, unsigned nsys, hipStream_t s);
+hipError_t launch_multipoles(const Buffers &b, unsigned n, unsigned nsys, hipStream_t s);
 // theta: the float32 opening angle widened to float64
 hipError_t launch_mac_prep(const Buffers &b, unsigned nsys, double theta, hipStream_t s);
 // order: the queue (NULL: groups in Morton order); qlen: device count of queue

@@ -866,9 +866,7 @@ hipError_t launch_build(const Buffers &b, unsigned n, unsigned nsys, int ncrit, 
 }
 
 // --------------------------------------------------------------------------
-// Multipole moments, float64: one launch for the leaves of every level (they
-// depend on particles only), then one per level for its internal cells, from
-// the deepest up.
+// Multipole moments, float64, bottom-up:
 //   leaf:     M = sum m, com = (sum fma(m, x, .)) / M, S_ab = sum fma(m d_a, d_b, .)
 //   internal: M = sum M_c, com = (sum fma(M_c, com_c, .)) / M,
 //             S_ab = sum (S_c,ab + (M_c e_a) e_b), e = com_c - com
@@ -883,255 +881,381 @@ hipError_t launch_build(const Buffers &b, unsigned n, unsigned nsys, int ncrit, 
 // fma calls, so every run gives the same bits.
 // --------------------------------------------------------------------------
 
-constexpr unsigned LEAF_REGS = 16;  // leaves up to this size are summed from registers
+// Eight lanes take an internal cell together.  Lane q of the octet sums second
+// moment min(q, 5) of (xx, yy, zz, xy, xz, yz), centre-of-mass axis q mod 3 and
+// box component min(q, 5); every lane sums the mass.  Each sum keeps its own
+// order, so the bits are those of one thread per cell; that form held the 8
+// children in 234 registers (two waves per SIMD) and ran the sums one after the
+// other.  Stores are the same for every lane but for their address and value:
+// no branch on the lane alone sits beside the shuffles (see the walk's queue
+// loop).
+constexpr unsigned OCT = 8;
 
-// Side and geometric centre of cell t (level from its record, corner from the
-// key prefix of its first particle).
-__device__ __forceinline__ double cell_geometry(const uint4 &t, const SysCube *__restrict__ cube,
-                                                const uint64_t *__restrict__ keys, double centre[3]) {
+struct CellBuffers {
+    const SysCube *cube;
+    const uint4 *topo;
+    const uint64_t *keys;
+    const float4 *spos;
+    double *mp, *delta;
+    float *cbox;
+    double *lside;
+    float4 *cmac, *ceval;
+};
+
+struct Octet {
+    unsigned q;        // lane of the octet
+    unsigned ax;       // centre-of-mass axis
+    unsigned ma, mb;   // second moment's axes
+    unsigned qb;       // second moment and box component
+};
+
+__device__ __forceinline__ Octet octet() {
+    Octet o;
+    o.q = threadIdx.x & (OCT - 1u);
+    o.ax = o.q % 3u;
+    o.qb = min(o.q, 5u);
+    o.ma = o.qb < 3u ? o.qb : (o.qb == 5u ? 1u : 0u);
+    o.mb = o.qb < 3u ? o.qb : (o.qb == 3u ? 1u : 2u);
+    return o;
+}
+
+__device__ __forceinline__ double oct_shfl(double v, unsigned lane) { return __shfl(v, (int)lane, OCT); }
+__device__ __forceinline__ float oct_shfl(float v, unsigned lane) { return __shfl(v, (int)lane, OCT); }
+
+// Side of the cell of level lev that starts at particle `first` (system sys)
+// and its geometric centre along axis ax (corner from the key prefix).
+__device__ __forceinline__ double cell_geometry(const CellBuffers &a, unsigned first, unsigned lev, unsigned sys,
+                                                unsigned ax, double *centre) {
 #pragma clang fp contract(off)
-    const int lev = (int)((t.w >> 8) & 255u);
-    const SysCube cb3 = cube[t.w >> 16];
-    const double lo[3] = {(double)cb3.lo[0], (double)cb3.lo[1], (double)cb3.lo[2]};
-    const double l = ldexp(1.0, cb3.k - lev);
-    const uint64_t pre = keys[t.x] >> (3 * (KEY_LEVELS - lev));
-    const double q[3] = {(double)compact3(pre >> 2), (double)compact3(pre >> 1), (double)compact3(pre)};
-    for (int a = 0; a < 3; a++) {
-        const double corner = lo[a] + q[a] * l;
-        centre[a] = corner + 0.5 * l;
-    }
+    const SysCube *cb = a.cube + sys;
+    const double l = ldexp(1.0, cb->k - (int)lev);
+    const uint64_t pre = a.keys[first] >> (3 * (KEY_LEVELS - (int)lev));
+    const double corner = (double)cb->lo[ax] + (double)compact3(pre >> (2u - ax)) * l;
+    *centre = corner + 0.5 * l;
     return l;
 }
 
-// Writes cell c's moments and the quantities derived from them.
-__device__ __forceinline__ void store_cell(unsigned c, double l, const double centre[3], double M,
-                                           const double com[3], const double S[6], const float bn[3],
-                                           const float bx[3], double *__restrict__ mp, double *__restrict__ delta,
-                                           float *__restrict__ cbox, double *__restrict__ lside,
-                                           float4 *__restrict__ cmac, float4 *__restrict__ ceval) {
+// Quantities derived from the moments of cell c, one thread: |com - centre|,
+// the opening size and the walk's float32 data.
+__device__ __forceinline__ void store_derived(const CellBuffers &a, unsigned c, double l, const double centre[3],
+                                              double M, const double com[3], const double S[6], const float bn[3],
+                                              const float bx[3]) {
 #pragma clang fp contract(off)
-    double *o = mp + 10 * (size_t)c;
+    const double tr = (S[0] + S[1]) + S[2];
+    const double Q0 = 3.0 * S[0] - tr, Q1 = 3.0 * S[1] - tr, Q2 = 3.0 * S[2] - tr;
+    const double dx = com[0] - centre[0], dy = com[1] - centre[1], dz = com[2] - centre[2];
+    a.delta[c] = sqrt((dx * dx + dy * dy) + dz * dz);
+    double reach = 0.0;
+    for (int k = 0; k < 3; k++) {
+        reach = fmax(reach, centre[k] - (double)bn[k]);
+        reach = fmax(reach, (double)bx[k] - centre[k]);
+    }
+    a.lside[c] = fmax(l, 2.0 * reach);
+    a.cmac[c] = make_float4((float)com[0], (float)com[1], (float)com[2], 0.0f);
+    a.ceval[2 * (size_t)c] = make_float4((float)M, (float)Q0, (float)Q1, (float)Q2);
+    a.ceval[2 * (size_t)c + 1] = make_float4((float)(3.0 * S[3]), (float)(3.0 * S[4]), (float)(3.0 * S[5]), 0.0f);
+}
+
+// Leaf c of `cnt` particles from sorted position `first`, one thread: the first
+// `nl` of them are in LDS at sp, the others are read from the sorted array.
+__device__ __forceinline__ void leaf_cell(const CellBuffers &a, unsigned c, unsigned first, unsigned cnt,
+                                          unsigned lev, unsigned sys, const float4 *sp, unsigned nl) {
+#pragma clang fp contract(off)
+    double centre[3], l = 0.0;
+    for (unsigned ax = 0; ax < 3; ax++) l = cell_geometry(a, first, lev, sys, ax, centre + ax);
+    const float4 *gp = a.spos + first;
+    double M = 0.0, cm[3] = {0.0, 0.0, 0.0}, com[3], S[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    float bn[3] = {sp[0].x, sp[0].y, sp[0].z}, bx[3] = {bn[0], bn[1], bn[2]};
+    auto first_pass = [&](const float4 p) {
+        bn[0] = fminf(bn[0], p.x);
+        bx[0] = fmaxf(bx[0], p.x);
+        bn[1] = fminf(bn[1], p.y);
+        bx[1] = fmaxf(bx[1], p.y);
+        bn[2] = fminf(bn[2], p.z);
+        bx[2] = fmaxf(bx[2], p.z);
+        const double m = (double)p.w;
+        M = M + m;
+        cm[0] = fma(m, (double)p.x, cm[0]);
+        cm[1] = fma(m, (double)p.y, cm[1]);
+        cm[2] = fma(m, (double)p.z, cm[2]);
+    };
+    auto second_pass = [&](const float4 p) {
+#pragma clang fp contract(off)
+        const double m = (double)p.w;
+        const double dx = (double)p.x - com[0], dy = (double)p.y - com[1], dz = (double)p.z - com[2];
+        S[0] = fma(m * dx, dx, S[0]);
+        S[1] = fma(m * dy, dy, S[1]);
+        S[2] = fma(m * dz, dz, S[2]);
+        S[3] = fma(m * dx, dy, S[3]);
+        S[4] = fma(m * dx, dz, S[4]);
+        S[5] = fma(m * dy, dz, S[5]);
+    };
+#pragma unroll 4
+    for (unsigned j = 0; j < nl; j++) first_pass(sp[j]);
+    for (unsigned j = nl; j < cnt; j++) first_pass(gp[j]);
+    for (int k = 0; k < 3; k++) com[k] = M > 0.0 ? cm[k] / M : centre[k];
+#pragma unroll 4
+    for (unsigned j = 0; j < nl; j++) second_pass(sp[j]);
+    for (unsigned j = nl; j < cnt; j++) second_pass(gp[j]);
+    double *o = a.mp + 10 * (size_t)c;
     o[0] = M;
     o[1] = com[0];
     o[2] = com[1];
     o[3] = com[2];
-    for (int s = 0; s < 6; s++) o[4 + s] = S[s];
-    const double tr = (S[0] + S[1]) + S[2];
-    const double Q0 = 3.0 * S[0] - tr, Q1 = 3.0 * S[1] - tr, Q2 = 3.0 * S[2] - tr;
-    const double dx = com[0] - centre[0], dy = com[1] - centre[1], dz = com[2] - centre[2];
-    delta[c] = sqrt((dx * dx + dy * dy) + dz * dz);
-    double reach = 0.0;
-    for (int a = 0; a < 3; a++) {
-        reach = fmax(reach, centre[a] - (double)bn[a]);
-        reach = fmax(reach, (double)bx[a] - centre[a]);
-        cbox[6 * (size_t)c + a] = bn[a];
-        cbox[6 * (size_t)c + 3 + a] = bx[a];
+    for (int k = 0; k < 6; k++) o[4 + k] = S[k];
+    for (int k = 0; k < 3; k++) {
+        a.cbox[6 * (size_t)c + k] = bn[k];
+        a.cbox[6 * (size_t)c + 3 + k] = bx[k];
     }
-    lside[c] = fmax(l, 2.0 * reach);
-    cmac[c] = make_float4((float)com[0], (float)com[1], (float)com[2], 0.0f);
-    ceval[2 * (size_t)c] = make_float4((float)M, (float)Q0, (float)Q1, (float)Q2);
-    ceval[2 * (size_t)c + 1] = make_float4((float)(3.0 * S[3]), (float)(3.0 * S[4]), (float)(3.0 * S[5]), 0.0f);
+    store_derived(a, c, l, centre, M, com, S, bn, bx);
 }
 
-// Every leaf of every level.
-__global__ __launch_bounds__(256) void k_multipole_leaves(
-    const Header *__restrict__ hdr, const SysCube *__restrict__ cube, const uint4 *__restrict__ topo,
-    const float4 *__restrict__ spos, const uint64_t *__restrict__ keys, double *__restrict__ mp,
-    double *__restrict__ delta, float *__restrict__ cbox, double *__restrict__ lside, float4 *__restrict__ cmac,
-    float4 *__restrict__ ceval, unsigned cap_cells) {
+// An internal cell: (c, first child, system << 16 | level << 8 | children, first particle).
+__device__ __forceinline__ uint4 cell_entry(unsigned c, const uint4 &t) { return make_uint4(c, t.z, t.w, t.x); }
+
+// Internal cell of entry e, its children done: the children's values are
+// loaded together, then combined in child order.
+__device__ __forceinline__ void internal_cell(const CellBuffers &a, const Octet &o, const uint4 &e) {
 #pragma clang fp contract(off)
+    const unsigned nch = e.z & 255u;
+    double Mc[8], xa[8], xb[8], Sc[8];
+    float bc[8];
+#pragma unroll
+    for (unsigned j = 0; j < 8; j++) {
+        const unsigned k = e.y + min(j, nch - 1u);  // the last child again: its values are not used
+        const double *m = a.mp + 10 * (size_t)k;
+        Mc[j] = m[0];
+        xa[j] = m[1 + o.ma];
+        xb[j] = m[1 + o.mb];
+        Sc[j] = m[4 + o.qb];
+        bc[j] = a.cbox[6 * (size_t)k + o.qb];
+    }
+    double centre;
+    cell_geometry(a, e.w, (e.z >> 8) & 255u, e.z >> 16, o.ax, &centre);
+    // Lanes 0..2 hold their centre-of-mass axis in xa (ma = ax there); the other
+    // lanes' own axes differ, so their sums are not used.
+    double M = 0.0, cm = 0.0, S = 0.0;
+    float box = bc[0];
+#pragma unroll
+    for (unsigned j = 0; j < 8; j++) {
+        const bool in = j < nch;
+        const double M1 = M + Mc[j], c1 = fma(Mc[j], xa[j], cm);
+        M = in ? M1 : M;
+        cm = in ? c1 : cm;
+        box = o.q < 3u ? fminf(box, bc[j]) : fmaxf(box, bc[j]);
+    }
+    const double own = M > 0.0 ? cm / M : centre;
+    const double com = oct_shfl(own, o.ax);
+    const double ca = oct_shfl(own, o.ma), cb = oct_shfl(own, o.mb);
+#pragma unroll
+    for (unsigned j = 0; j < 8; j++) {
+        const double ea = xa[j] - ca, eb = xb[j] - cb;
+        const double S1 = S + (Sc[j] + (Mc[j] * ea) * eb);
+        S = j < nch ? S1 : S;
+    }
+    double *m = a.mp + 10 * (size_t)e.x;
+    m[o.q < 6u ? 4u + o.q : 0u] = o.q < 6u ? S : M;
+    m[1 + o.ax] = com;
+    a.cbox[6 * (size_t)e.x + o.qb] = box;
+}
+
+// The derived quantities of the internal cell of entry e, its moments done: one thread.
+__device__ __forceinline__ void derive_cell(const CellBuffers &a, const uint4 &e) {
+    double centre[3], l = 0.0, com[3], S[6];
+    float bn[3], bx[3];
+    const double *m = a.mp + 10 * (size_t)e.x;
+    const float *cb = a.cbox + 6 * (size_t)e.x;
+    const double M = m[0];
+    for (int k = 0; k < 3; k++) com[k] = m[1 + k];
+    for (int k = 0; k < 6; k++) S[k] = m[4 + k];
+    for (int k = 0; k < 3; k++) {
+        bn[k] = cb[k];
+        bx[k] = cb[3 + k];
+    }
+    for (unsigned ax = 0; ax < 3; ax++) l = cell_geometry(a, e.w, (e.z >> 8) & 255u, e.z >> 16, ax, centre + ax);
+    store_derived(a, e.x, l, centre, M, com, S, bn, bx);
+}
+
+// All cells in a few launches.  The particles are cut into chunks of MP_CHUNK,
+// whole build blocks; the cells of one level that start in a chunk are
+// consecutive (the build's block counts give their range), and all but the last
+// of them end in it.
+//   k_multipole_chunk: one workgroup per chunk, the chunk's particles in LDS:
+//     every leaf that starts in the chunk, then the internal cells that end in
+//     it, level by level from the deepest with workgroup barriers between
+//     (their children lie in the chunk too).  An internal cell that does not
+//     end in its chunk, at most one per level, goes on the list of the chunk.
+//   k_multipole_merge: one workgroup per MP_FAN chunks takes the listed cells
+//     that end within its range in the same way and lists the others; it is
+//     launched until one range covers everything.
+// What bounds it: the chain of levels, about 2 us each (children from the L2,
+// float64 sums and a division, the barrier's wait for the stores), so the
+// quantities that no parent needs are derived after the last level.  A leaf
+// pass and one launch per level (21 launches) took 57 / 68 / 77 / 103 / 203 us
+// at n = 1000 / 20000 / 100003 / 2^20 / 2^22; this takes 21 / 43 / 50 / 82 /
+// 173 us (chunks of 1024: 21 / 41 / 60 / 88 / 196; one workgroup for all listed
+// cells instead of MP_FAN-way merges: 567 us at 2^22).
+constexpr unsigned MP_THREADS = 256;
+constexpr unsigned MP_OCTS = MP_THREADS / OCT;
+constexpr unsigned MP_CELLS = 512;  // internal cells of a chunk listed in LDS (more: the level ranges are walked)
+constexpr unsigned MP_NONE = 0xffffffffu;
+static_assert(MP_CHUNK % BUILD_THREADS == 0, "chunks are whole build blocks");
+
+__global__ __launch_bounds__(MP_THREADS, 3) void k_multipole_chunk(const Header *__restrict__ hdr, CellBuffers a,
+                                                                   const uint32_t *__restrict__ blkcnt, unsigned nblk,
+                                                                   unsigned n, unsigned nchunks,
+                                                                   uint32_t *__restrict__ out) {
+    __shared__ float4 s_p[MP_CHUNK];
+    __shared__ uint4 s_raw[MP_CELLS], s_int[MP_CELLS];  // internal cells as met, then by level
+    __shared__ unsigned short s_rank[MP_CELLS];         // their ranks in their levels
+    __shared__ unsigned s_lo[KEY_LEVELS + 1], s_hi[KEY_LEVELS + 1];  // cells of a level that start here
+    __shared__ unsigned s_pre[KEY_LEVELS + 2];          // their prefix sums
+    __shared__ unsigned s_cnt[KEY_LEVELS + 1], s_at[KEY_LEVELS + 1];  // internal cells of a level: number, place
+    __shared__ unsigned s_nint;
+    constexpr unsigned PB = MP_CHUNK / BUILD_THREADS;
     if (hdr->flags & FLAG_CELLCAP) return;
-    const unsigned nc = min(hdr->ncells, cap_cells);
-    for (unsigned c = blockIdx.x * 256u + threadIdx.x; c < nc; c += gridDim.x * 256u) {
-        const uint4 t = topo[c];
-        if ((t.w & 255u) != 0) continue;
-        double centre[3];
-        const double l = cell_geometry(t, cube, keys, centre);
-        double M = 0.0, cm[3] = {0.0, 0.0, 0.0}, com[3];
-        double S[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        float bn[3], bx[3];
-        if (t.y <= LEAF_REGS) {
-            // a leaf of up to LEAF_REGS particles: all loads in flight at once,
-            // both passes from registers (same operations in the same order)
-            float4 pr[LEAF_REGS];
-#pragma unroll
-            for (int j = 0; j < LEAF_REGS; j++)
-                pr[j] = (unsigned)j < t.y ? spos[t.x + j] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            bn[0] = bx[0] = pr[0].x;
-            bn[1] = bx[1] = pr[0].y;
-            bn[2] = bx[2] = pr[0].z;
-#pragma unroll
-            for (int j = 1; j < LEAF_REGS; j++) {
-                if ((unsigned)j < t.y) {
-                    bn[0] = fminf(bn[0], pr[j].x);
-                    bx[0] = fmaxf(bx[0], pr[j].x);
-                    bn[1] = fminf(bn[1], pr[j].y);
-                    bx[1] = fmaxf(bx[1], pr[j].y);
-                    bn[2] = fminf(bn[2], pr[j].z);
-                    bx[2] = fmaxf(bx[2], pr[j].z);
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < LEAF_REGS; j++) {
-                if ((unsigned)j < t.y) {
-                    const double m = (double)pr[j].w;
-                    M = M + m;
-                    cm[0] = fma(m, (double)pr[j].x, cm[0]);
-                    cm[1] = fma(m, (double)pr[j].y, cm[1]);
-                    cm[2] = fma(m, (double)pr[j].z, cm[2]);
-                }
-            }
-            for (int a = 0; a < 3; a++) com[a] = M > 0.0 ? cm[a] / M : centre[a];
-            // the second pass converts the particles to float64 again instead of
-            // keeping 16 x 4 float64 values live across the divisions (128 registers)
-#pragma unroll
-            for (int j = 0; j < LEAF_REGS; j++)
-                asm volatile("" : "+v"(pr[j].x), "+v"(pr[j].y), "+v"(pr[j].z), "+v"(pr[j].w));
-#pragma unroll
-            for (int j = 0; j < LEAF_REGS; j++) {
-                if ((unsigned)j < t.y) {
-                    const double m = (double)pr[j].w;
-                    const double dx = (double)pr[j].x - com[0], dy = (double)pr[j].y - com[1],
-                                 dz = (double)pr[j].z - com[2];
-                    S[0] = fma(m * dx, dx, S[0]);
-                    S[1] = fma(m * dy, dy, S[1]);
-                    S[2] = fma(m * dz, dz, S[2]);
-                    S[3] = fma(m * dx, dy, S[3]);
-                    S[4] = fma(m * dx, dz, S[4]);
-                    S[5] = fma(m * dy, dz, S[5]);
-                }
-            }
+    const unsigned t = threadIdx.x;
+    const unsigned b = blockIdx.x * MP_CHUNK, e = min(b + MP_CHUNK, n);
+    if (t < 64u) {  // the first wave: ranges of the levels and their prefix sums
+        const bool lev = t <= (unsigned)KEY_LEVELS;
+        const unsigned l = lev ? t : 0u;
+        const unsigned b0 = blockIdx.x * PB, b1 = b0 + PB;
+        const unsigned lb = hdr->lvl_begin[l], le = hdr->lvl_begin[l + 1];
+        const unsigned lo = lb + blkcnt[(size_t)l * nblk + b0];
+        const unsigned hi = b1 < nblk ? lb + blkcnt[(size_t)l * nblk + b1] : le;
+        const unsigned cnt = lev ? hi - lo : 0u;
+        const unsigned inc = wave_incl_scan(cnt);
+        if (lev) {
+            s_lo[l] = lo;
+            s_hi[l] = hi;
+            s_pre[l] = inc - cnt;
+            s_cnt[l] = 0;
+            if (out && l < (unsigned)KEY_LEVELS) out[l * nchunks + blockIdx.x] = MP_NONE;
+        }
+        if (t == 63u) s_pre[KEY_LEVELS + 1] = inc;
+        if (t == 63u) s_nint = 0;
+    }
+    for (unsigned i = b + t; i < e; i += MP_THREADS) s_p[i - b] = a.spos[i];
+    __syncthreads();
+    // the chunk's cells: leaves are done at once, internal cells that end here listed
+    const unsigned total = s_pre[KEY_LEVELS + 1];
+    for (unsigned i = t; i < total; i += MP_THREADS) {
+        unsigned l = 0, h = KEY_LEVELS + 1;  // s_pre[l] <= i < s_pre[h]
+        while (h - l > 1) {
+            const unsigned mid = (l + h) >> 1;
+            if (s_pre[mid] <= i) l = mid; else h = mid;
+        }
+        const unsigned c = s_lo[l] + (i - s_pre[l]);
+        const uint4 tc = a.topo[c];
+        if ((tc.w & 255u) == 0) {
+            leaf_cell(a, c, tc.x, tc.y, l, tc.w >> 16, s_p + (tc.x - b), min(tc.y, e - tc.x));
+        } else if (tc.x + tc.y > b + MP_CHUNK) {
+            out[l * nchunks + blockIdx.x] = c;  // leaves the chunk: there is more than one, so a list
         } else {
-            {
-                const float4 p0 = spos[t.x];
-                bn[0] = bx[0] = p0.x;
-                bn[1] = bx[1] = p0.y;
-                bn[2] = bx[2] = p0.z;
-            }
-            for (unsigned j = t.x; j < t.x + t.y; j++) {
-                const float4 p = spos[j];
-                bn[0] = fminf(bn[0], p.x);
-                bx[0] = fmaxf(bx[0], p.x);
-                bn[1] = fminf(bn[1], p.y);
-                bx[1] = fmaxf(bx[1], p.y);
-                bn[2] = fminf(bn[2], p.z);
-                bx[2] = fmaxf(bx[2], p.z);
-                const double m = (double)p.w;
-                M = M + m;
-                cm[0] = fma(m, (double)p.x, cm[0]);
-                cm[1] = fma(m, (double)p.y, cm[1]);
-                cm[2] = fma(m, (double)p.z, cm[2]);
-            }
-            for (int a = 0; a < 3; a++) com[a] = M > 0.0 ? cm[a] / M : centre[a];
-            for (unsigned j = t.x; j < t.x + t.y; j++) {
-                const float4 p = spos[j];
-                const double m = (double)p.w;
-                const double dx = (double)p.x - com[0], dy = (double)p.y - com[1], dz = (double)p.z - com[2];
-                S[0] = fma(m * dx, dx, S[0]);
-                S[1] = fma(m * dy, dy, S[1]);
-                S[2] = fma(m * dz, dz, S[2]);
-                S[3] = fma(m * dx, dy, S[3]);
-                S[4] = fma(m * dx, dz, S[4]);
-                S[5] = fma(m * dy, dz, S[5]);
+            const unsigned r = atomicAdd(&s_cnt[l], 1u), k = atomicAdd(&s_nint, 1u);
+            if (k < MP_CELLS) {
+                s_raw[k] = cell_entry(c, tc);
+                s_rank[k] = (unsigned short)r;
             }
         }
-        store_cell(c, l, centre, M, com, S, bn, bx, mp, delta, cbox, lside, cmac, ceval);
+    }
+    __syncthreads();
+    const unsigned nint = s_nint;
+    const bool listed = nint <= MP_CELLS;
+    if (t < 64u) {
+        const unsigned cnt = t <= (unsigned)KEY_LEVELS ? s_cnt[t] : 0u;
+        const unsigned inc = wave_incl_scan(cnt);
+        if (t <= (unsigned)KEY_LEVELS) s_at[t] = inc - cnt;
+    }
+    __syncthreads();
+    if (listed)
+        for (unsigned k = t; k < nint; k += MP_THREADS) s_int[s_at[(s_raw[k].z >> 8) & 255u] + s_rank[k]] = s_raw[k];
+    __syncthreads();
+    const Octet o = octet();
+    const unsigned oct = t / OCT;
+    for (int l = KEY_LEVELS - 1; l >= 0; l--) {
+        const unsigned cnt = s_cnt[l];
+        if (cnt == 0) continue;  // the same for the whole workgroup
+        if (listed) {
+            const unsigned at = s_at[l];
+            for (unsigned i = oct; i < cnt; i += MP_OCTS) internal_cell(a, o, s_int[at + i]);
+        } else {
+            for (unsigned c = s_lo[l] + oct; c < s_hi[l]; c += MP_OCTS) {
+                const uint4 tc = a.topo[c];
+                if ((tc.w & 255u) != 0 && tc.x + tc.y <= b + MP_CHUNK) internal_cell(a, o, cell_entry(c, tc));
+            }
+        }
+        __syncthreads();
+    }
+    // the derived quantities at the end, off the chain of the levels
+    if (listed) {
+        for (unsigned k = t; k < nint; k += MP_THREADS) derive_cell(a, s_int[k]);
+    } else {
+        for (int l = KEY_LEVELS - 1; l >= 0; l--)
+            for (unsigned c = s_lo[l] + t; c < s_hi[l]; c += MP_THREADS) {
+                const uint4 tc = a.topo[c];
+                if ((tc.w & 255u) != 0 && tc.x + tc.y <= b + MP_CHUNK) derive_cell(a, cell_entry(c, tc));
+            }
     }
 }
 
-// The internal cells of level lev (their children, at level lev + 1, are
-// done).  The up to 8 children's moments and boxes are loaded together, one
-// round trip per cell instead of one per child, then combined in child order.
-// One wave per workgroup: about one cell in five of a level is internal, and
-// the cell code holds many registers (two waves per SIMD), so small
-// workgroups spread a level's internal cells over more compute units.
-constexpr unsigned MP_INTERNAL_THREADS = 64;
-#ifndef MP_INTERNAL_GRID
-#define MP_INTERNAL_GRID 1024u  // workgroups per level launch (grid-stride over the level's cells; 8192 and 256 were slower)
-#endif
-
-__global__ __launch_bounds__(MP_INTERNAL_THREADS) void k_multipole_internal(
-    int lev, const Header *__restrict__ hdr, const SysCube *__restrict__ cube, const uint4 *__restrict__ topo,
-    const uint64_t *__restrict__ keys, double *__restrict__ mp, double *__restrict__ delta,
-    float *__restrict__ cbox, double *__restrict__ lside, float4 *__restrict__ cmac, float4 *__restrict__ ceval,
-    unsigned cap_cells) {
-#pragma clang fp contract(off)
+// in[level][nin]: listed cells of the ranges below, MP_FAN of them per
+// workgroup; `span`: particles of this workgroup's range; out as above
+__global__ __launch_bounds__(MP_THREADS) void k_multipole_merge(const Header *__restrict__ hdr, CellBuffers a,
+                                                                const uint32_t *__restrict__ in, unsigned nin,
+                                                                unsigned long long span, unsigned nout,
+                                                                uint32_t *__restrict__ out) {
+    __shared__ uint4 s_int[KEY_LEVELS][MP_FAN];
+    __shared__ unsigned s_cnt[KEY_LEVELS];
     if (hdr->flags & FLAG_CELLCAP) return;
-    const unsigned nc = min(hdr->ncells, cap_cells);
-    const unsigned cb = min(hdr->lvl_begin[lev], nc), ce = min(hdr->lvl_begin[lev + 1], nc);
-    for (unsigned c = cb + blockIdx.x * MP_INTERNAL_THREADS + threadIdx.x; c < ce;
-         c += gridDim.x * MP_INTERNAL_THREADS) {
-        const uint4 t = topo[c];
-        const unsigned nch = t.w & 255u;
-        if (nch == 0) continue;
-        double2 cm2[8][5];  // child moments: M, com xyz, S xx yy zz xy xz yz
-        float2 cb2[8][3];   // child boxes: min xyz, max xyz
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-            if ((unsigned)j < nch) {
-                const double2 *pm = reinterpret_cast<const double2 *>(mp + 10 * (size_t)(t.z + j));
-                const float2 *pb = reinterpret_cast<const float2 *>(cbox + 6 * (size_t)(t.z + j));
-#pragma unroll
-                for (int a = 0; a < 5; a++) cm2[j][a] = pm[a];
-#pragma unroll
-                for (int a = 0; a < 3; a++) cb2[j][a] = pb[a];
-            }
-        }
-        double centre[3];
-        const double l = cell_geometry(t, cube, keys, centre);
-        float bn[3] = {cb2[0][0].x, cb2[0][0].y, cb2[0][1].x}, bx[3] = {cb2[0][1].y, cb2[0][2].x, cb2[0][2].y};
-#pragma unroll
-        for (int j = 1; j < 8; j++) {
-            if ((unsigned)j < nch) {
-                bn[0] = fminf(bn[0], cb2[j][0].x);
-                bn[1] = fminf(bn[1], cb2[j][0].y);
-                bn[2] = fminf(bn[2], cb2[j][1].x);
-                bx[0] = fmaxf(bx[0], cb2[j][1].y);
-                bx[1] = fmaxf(bx[1], cb2[j][2].x);
-                bx[2] = fmaxf(bx[2], cb2[j][2].y);
-            }
-        }
-        double M = 0.0, cm[3] = {0.0, 0.0, 0.0}, com[3];
-        double S[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-            if ((unsigned)j < nch) {
-                const double Mc = cm2[j][0].x;
-                M = M + Mc;
-                cm[0] = fma(Mc, cm2[j][0].y, cm[0]);
-                cm[1] = fma(Mc, cm2[j][1].x, cm[1]);
-                cm[2] = fma(Mc, cm2[j][1].y, cm[2]);
-            }
-        }
-        for (int a = 0; a < 3; a++) com[a] = M > 0.0 ? cm[a] / M : centre[a];
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-            if ((unsigned)j < nch) {
-                const double Mc = cm2[j][0].x;
-                const double ex = cm2[j][0].y - com[0], ey = cm2[j][1].x - com[1], ez = cm2[j][1].y - com[2];
-                S[0] = S[0] + (cm2[j][2].x + (Mc * ex) * ex);
-                S[1] = S[1] + (cm2[j][2].y + (Mc * ey) * ey);
-                S[2] = S[2] + (cm2[j][3].x + (Mc * ez) * ez);
-                S[3] = S[3] + (cm2[j][3].y + (Mc * ex) * ey);
-                S[4] = S[4] + (cm2[j][4].x + (Mc * ex) * ez);
-                S[5] = S[5] + (cm2[j][4].y + (Mc * ey) * ez);
-            }
-        }
-        store_cell(c, l, centre, M, com, S, bn, bx, mp, delta, cbox, lside, cmac, ceval);
+    const unsigned t = threadIdx.x;
+    const unsigned r0 = blockIdx.x * MP_FAN;
+    const unsigned long long end = (blockIdx.x + 1ull) * span;
+    if (t < (unsigned)KEY_LEVELS) {
+        s_cnt[t] = 0;
+        if (out) out[t * nout + blockIdx.x] = MP_NONE;
     }
+    __syncthreads();
+    for (unsigned i = t; i < (unsigned)KEY_LEVELS * MP_FAN; i += MP_THREADS) {
+        const unsigned l = i / MP_FAN, k = r0 + i % MP_FAN;
+        const unsigned c = k < nin ? in[l * nin + k] : MP_NONE;
+        if (c != MP_NONE) {
+            const uint4 tc = a.topo[c];
+            if (tc.x + (unsigned long long)tc.y > end) out[l * nout + blockIdx.x] = c;
+            else s_int[l][atomicAdd(&s_cnt[l], 1u)] = cell_entry(c, tc);
+        }
+    }
+    __syncthreads();
+    const Octet o = octet();
+    const unsigned oct = t / OCT;
+    for (int l = KEY_LEVELS - 1; l >= 0; l--) {
+        const unsigned cnt = s_cnt[l];
+        if (cnt == 0) continue;  // the same for the whole workgroup
+        for (unsigned i = oct; i < cnt; i += MP_OCTS) internal_cell(a, o, s_int[l][i]);
+        __syncthreads();
+    }
+    for (unsigned i = t; i < (unsigned)KEY_LEVELS * MP_FAN; i += MP_THREADS)
+        if (i % MP_FAN < s_cnt[i / MP_FAN]) derive_cell(a, s_int[i / MP_FAN][i % MP_FAN]);
 }
 
-hipError_t launch_multipoles(const Buffers &b, unsigned nsys, hipStream_t s) {
-    const uint64_t *keys = b.keys[sorted_buffer(nsys)];
-    // up to one thread per cell at N = 2^22 (multipoles 210 us with 2048 blocks, 204 us with 4096)
-    const unsigned grid = min((b.cap_cells + 255u) / 256u, 4096u);
-    hipLaunchKernelGGL(k_multipole_leaves, dim3(grid), dim3(256), 0, s, b.hdr, b.cube, b.topo, b.spos, keys, b.mp,
-                       b.delta, b.cbox, b.lside, b.cmac, b.ceval, b.cap_cells);
-    // level KEY_LEVELS holds leaves only
-    const unsigned igrid = min((b.cap_cells + MP_INTERNAL_THREADS - 1u) / MP_INTERNAL_THREADS, MP_INTERNAL_GRID);
-    for (int lev = KEY_LEVELS - 1; lev >= 0; lev--)
-        hipLaunchKernelGGL(k_multipole_internal, dim3(igrid), dim3(MP_INTERNAL_THREADS), 0, s, lev, b.hdr, b.cube,
-                           b.topo, keys, b.mp, b.delta, b.cbox, b.lside, b.cmac, b.ceval, b.cap_cells);
+hipError_t launch_multipoles(const Buffers &b, unsigned n, unsigned nsys, hipStream_t s) {
+    const CellBuffers a = {b.cube, b.topo, b.keys[sorted_buffer(nsys)], b.spos, b.mp, b.delta, b.cbox, b.lside,
+                           b.cmac, b.ceval};
+    const unsigned nblk = (n + BUILD_THREADS - 1) / BUILD_THREADS;
+    unsigned nr = (n + MP_CHUNK - 1) / MP_CHUNK;
+    uint32_t *list = b.mlist;
+    unsigned long long span = MP_CHUNK;
+    hipLaunchKernelGGL(k_multipole_chunk, dim3(nr), dim3(MP_THREADS), 0, s, b.hdr, a, b.blkcnt, nblk, n, nr,
+                       nr > 1 ? list : nullptr);
+    while (nr > 1) {
+        const unsigned nout = (nr + MP_FAN - 1) / MP_FAN;
+        uint32_t *next = list + (size_t)KEY_LEVELS * nr;
+        span *= MP_FAN;
+        hipLaunchKernelGGL(k_multipole_merge, dim3(nout), dim3(MP_THREADS), 0, s, b.hdr, a, list, nr, span, nout,
+                           nout > 1 ? next : nullptr);
+        list = next;
+        nr = nout;
+    }
     return hipGetLastError();
 }
 
