@@ -33,18 +33,19 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "walk_hbm_traffic.json")
 
 PEAK_HBM_GBS = 8000.0  # MI355X published HBM3E bandwidth
 
-# Algorithmic HBM bytes of the tree stages: per particle, per radix pass and per cell.
-#   sorting: bounding box reads x, y, z, m (16); keys read them again and write the
-#     key (8) and the packed record (16); each of the 8 radix passes (60-bit keys in
-#     8-bit digits) reads the key for the histogram (8), reads key + index (12) and
-#     writes them (12);
-#   moving: index (4), gathered record (16), written record (16);
+# Algorithmic HBM bytes of the tree stages: per particle and per cell (the bucket
+# sort, which inputs of up to 5.59 million particles take).
+#   sorting: bounding box reads x, y, z, m (16); the counting reads the positions
+#     (12) and writes the bucket (2); the scatter reads both and the mass (18) and
+#     writes record and index (20);
+#   moving: the sort inside the buckets reads record and index (20) and writes the
+#     key (8), the index (4), the record (16) and the shared digits (1);
 #   tree construction: keys and the common-prefix byte read (9), level record
 #     written and read (8), groups written (8), plus one 16-byte topology record per cell;
 #   multipoles: sorted records read (16) plus per cell the topology (16), float64
 #     moments, delta and l' written (96) and read back by the parent (96), the
 #     particle box (24) and the walk data (48) written.
-HBM_B_PER_PARTICLE = {"sorting": 16 + 40 + 8 * 32, "moving": 36, "tree_construction": 25, "multipoles": 16}
+HBM_B_PER_PARTICLE = {"sorting": 16 + 14 + 18 + 20, "moving": 49, "tree_construction": 25, "multipoles": 16}
 HBM_B_PER_CELL = {"tree_construction": 16, "multipoles": 16 + 96 + 96 + 24 + 48}
 
 

@@ -82,8 +82,34 @@ struct SysOffsets {
     unsigned off[MAX_SYSTEMS + 1];
 };
 
-__global__ void k_set_offsets(SysOffsets o, uint32_t *__restrict__ sys_off) {
-    for (unsigned i = threadIdx.x; i <= o.nsys; i += blockDim.x) sys_off[i] = o.off[i];
+// The start of a build: system offsets, the first sort bucket of each system,
+// the header and the walk's padding entries.  The flags of the previous build
+// move into the sticky word, so that a driver running many steps still sees a
+// condition that one of its earlier builds met.
+__global__ void k_begin_build(SysOffsets o, uint32_t *__restrict__ sys_off, uint32_t *__restrict__ bkt_off,
+                              Header *__restrict__ hdr, float4 *__restrict__ cmac, float4 *__restrict__ ceval,
+                              float4 *__restrict__ spos, unsigned cap_cells, unsigned n_max) {
+    for (unsigned i = threadIdx.x; i <= o.nsys; i += blockDim.x) {
+        sys_off[i] = o.off[i];
+        unsigned nb = 0;
+        for (unsigned s = 0; s < i; s++) nb += sort_buckets(o.off[s + 1] - o.off[s]);
+        bkt_off[i] = nb;
+    }
+    if (threadIdx.x == 0) {
+        // the walk's padding cell and particle: massless, far away
+        cmac[cap_cells] = make_float4(WALK_FAR, WALK_FAR, WALK_FAR, 0.0f);
+        ceval[2 * (size_t)cap_cells] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        ceval[2 * (size_t)cap_cells + 1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        spos[n_max] = make_float4(WALK_FAR, WALK_FAR, WALK_FAR, 0.0f);
+        hdr->nsys = o.nsys;
+        hdr->sticky |= hdr->flags;
+        hdr->flags = 0;
+        hdr->n = o.off[o.nsys];
+        hdr->ncells = 0;
+        hdr->ngroups = 0;
+        for (int l = 0; l < 24; l++) hdr->lvl_begin[l] = 0;
+    }
+    if (threadIdx.x < WALK_QUEUES) hdr->walk_head[QUEUE_STRIDE * threadIdx.x] = 0;
 }
 
 bool params_valid(const mibh_params &p) {
@@ -116,6 +142,7 @@ size_t layout(int64_t n_max, const mibh_params &p, char *base, Buffers *b) {
     t.hdr = (Header *)take(sizeof(Header));
     t.cube = (SysCube *)take(sizeof(SysCube) * nsys);
     t.sys_off = (uint32_t *)take(4 * (nsys + 1));
+    t.bkt_off = (uint32_t *)take(4 * (nsys + 1));
     t.sys8 = (uint8_t *)take(nsys > 1 ? n : 1);
     t.bbox_part = (float *)take(sizeof(float) * 8 * std::max(bbox_blocks, (size_t)BBOX_BLOCKS));
     t.keys[0] = (uint64_t *)take(8 * n);
@@ -337,13 +364,30 @@ mibh_status mibh_build_tree_batch(mibh_ctx *ctx, const float *d_pos, const float
     const unsigned un = (unsigned)n, us = (unsigned)nsys;
     hipStream_t s = ctx->stream;
     if ((st = mark(ctx, -1))) return st;
-    hipLaunchKernelGGL(k_set_offsets, dim3(1), dim3(256), 0, s, o, ctx->b.sys_off);
-    HIP_TRY(hipGetLastError(), "set_offsets");
-    HIP_TRY(launch_bbox(ctx->b, d_pos, d_mass, un, us, s), "bbox");
-    HIP_TRY(launch_keys(ctx->b, d_pos, d_mass, un, us, s), "keys");
-    HIP_TRY(launch_sort(ctx->b, un, us, s), "sort");
-    if ((st = mark(ctx, MIBH_STAGE_SORT))) return st;
-    HIP_TRY(launch_reorder(ctx->b, un, us, s), "reorder");
+    const Buffers &b = ctx->b;
+    hipLaunchKernelGGL(k_begin_build, dim3(1), dim3(256), 0, s, o, b.sys_off, b.bkt_off, b.hdr, b.cmac, b.ceval, b.spos,
+                       b.cap_cells, b.n_max);
+    HIP_TRY(hipGetLastError(), "begin_build");
+    // The bucket sort up to its 4096 buckets (5.59 million particles in one
+    // system), whose splitters fill a workgroup's 64 KB of LDS; the radix sort
+    // beyond.
+    unsigned nb = 0, nb_max = 0;
+    for (int k = 0; k < nsys; k++) {
+        const unsigned nk = sort_buckets(o.off[k + 1] - o.off[k]);
+        nb += nk;
+        nb_max = std::max(nb_max, nk);
+    }
+    if (bucket_sort_fits(ctx->b, un, nb)) {
+        HIP_TRY(launch_bucket_partition(ctx->b, d_pos, d_mass, un, us, nb, nb_max, s), "partition");
+        if ((st = mark(ctx, MIBH_STAGE_SORT))) return st;
+        HIP_TRY(launch_bucket_sort(ctx->b, d_pos, d_mass, un, us, nb, s), "bucket sort");
+    } else {
+        HIP_TRY(launch_bbox(ctx->b, d_pos, d_mass, us, s), "bbox");
+        HIP_TRY(launch_keys(ctx->b, d_pos, d_mass, un, us, s), "keys");
+        HIP_TRY(launch_sort(ctx->b, un, us, s), "sort");
+        if ((st = mark(ctx, MIBH_STAGE_SORT))) return st;
+        HIP_TRY(launch_reorder(ctx->b, un, us, s), "reorder");
+    }
     if ((st = mark(ctx, MIBH_STAGE_MOVE))) return st;
     HIP_TRY(launch_build(ctx->b, un, us, ctx->p.ncrit, ctx->p.group_cap, s), "build");
     if ((st = mark(ctx, MIBH_STAGE_BUILD))) return st;
@@ -791,8 +835,8 @@ mibh_status mibh_export(mibh_ctx *ctx, int what, void *d_dst, size_t bytes) {
         return fail(MIBH_ESTATE, "export of multipoles before compute_multipoles");
     const void *src = nullptr;
     switch (what) {
-        case MIBH_EXPORT_KEYS: src = ctx->b.keys[sorted_buffer((unsigned)ctx->nsys)]; break;
-        case MIBH_EXPORT_PERM: src = ctx->b.vals[sorted_buffer((unsigned)ctx->nsys)]; break;
+        case MIBH_EXPORT_KEYS: src = ctx->b.keys[0]; break;
+        case MIBH_EXPORT_PERM: src = ctx->b.vals[0]; break;
         case MIBH_EXPORT_CELLS: src = ctx->b.topo; break;
         case MIBH_EXPORT_GROUPS: src = ctx->b.groups; break;
         case MIBH_EXPORT_COUNTS: src = ctx->b.gcounts; break;

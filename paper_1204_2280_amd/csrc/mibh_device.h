@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 namespace mibh {
@@ -31,9 +32,7 @@ constexpr int SORT_TILE = SORT_THREADS * SORT_ITEMS;
 #endif
 constexpr int BUILD_THREADS = MIBH_BUILD_THREADS;
 constexpr int MAX_WINDOW = 64;          // largest ncrit and group_cap (a build wave's window reach)
-#ifndef MP_CHUNK
-#define MP_CHUNK 2048u  // particles per workgroup of the multipole pass
-#endif
+constexpr unsigned MP_CHUNK = 2048;     // particles per workgroup of the multipole pass
 constexpr unsigned MP_FAN = 64;         // ranges per workgroup of its merge launches
 constexpr int BBOX_BLOCKS = 1024;
 constexpr int ENERGY_BLOCKS = 1024;
@@ -152,6 +151,7 @@ struct Buffers {
     Header *hdr;
     SysCube *cube;          // [max_systems]
     uint32_t *sys_off;      // [max_systems + 1] first particle of each system (input = sorted order)
+    uint32_t *bkt_off;      // [max_systems + 1] first sort bucket of each system
     uint8_t *sys8;          // [n] system of each input particle (batches only)
     float *bbox_part;       // [max_systems][bbox blocks per system][8]
     uint64_t *keys[2];
@@ -205,14 +205,133 @@ __device__ __forceinline__ unsigned system_of(const uint32_t *__restrict__ sys_o
     return lo;
 }
 
+// Morton bit spreading: bit b of v (20 bits) moves to bit 3b.
+__device__ __forceinline__ uint64_t spread3(uint64_t x) {
+    x &= 0x1fffffull;
+    x = (x | (x << 32)) & 0x1f00000000ffffull;
+    x = (x | (x << 16)) & 0x1f0000ff0000ffull;
+    x = (x | (x << 8)) & 0x100f00f00f00f00full;
+    x = (x | (x << 4)) & 0x10c30c30c30c30c3ull;
+    x = (x | (x << 2)) & 0x1249249249249249ull;
+    return x;
+}
+
+// Morton key of a point in its system's cube: q_a = min(floor((x_a - lo_a)
+// 2^(20-k)), 2^20 - 1), bits of q_x, q_y, q_z at 3b+2, 3b+1, 3b.
+__device__ __forceinline__ uint64_t morton_key(const SysCube &c, float px, float py, float pz) {
+    const double s = ldexp(1.0, KEY_LEVELS - c.k);
+    const float x[3] = {px, py, pz};
+    uint64_t q[3];
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        double f = floor(((double)x[a] - (double)c.lo[a]) * s);
+        if (!(f >= 0.0)) f = 0.0;
+        if (f > 1048575.0) f = 1048575.0;
+        q[a] = (uint64_t)f;
+    }
+    return (spread3(q[0]) << 2) | (spread3(q[1]) << 1) | spread3(q[2]);
+}
+
+// Bounding box and input flags of a set of particles.
+struct BoxFlags {
+    float mn[3], mx[3];
+    unsigned flags;
+    __device__ BoxFlags() : mn{INFINITY, INFINITY, INFINITY}, mx{-INFINITY, -INFINITY, -INFINITY}, flags(0) {}
+    __device__ void add(float x, float y, float z, float m) {
+        if (!(isfinite(x) && isfinite(y) && isfinite(z) && isfinite(m))) flags |= FLAG_NONFINITE;
+        if (m < 0.0f) flags |= FLAG_NEGMASS;
+        const float p[3] = {x, y, z};
+        for (int a = 0; a < 3; a++) {
+            mn[a] = fminf(mn[a], p[a]);
+            mx[a] = fmaxf(mx[a], p[a]);
+        }
+    }
+    __device__ void add(const float *p) {  // a stored box: min xyz, max xyz, flags
+        for (int a = 0; a < 3; a++) {
+            mn[a] = fminf(mn[a], p[a]);
+            mx[a] = fmaxf(mx[a], p[3 + a]);
+        }
+        flags |= __float_as_uint(p[6]);
+    }
+    __device__ void store(float *p) const {
+        for (int a = 0; a < 3; a++) {
+            p[a] = mn[a];
+            p[3 + a] = mx[a];
+        }
+        p[6] = __uint_as_float(flags);
+    }
+};
+
+// The box of all threads of a workgroup of NT, in every thread; s: one row per wave.
+template <unsigned NT>
+__device__ __forceinline__ void block_box(BoxFlags &b, float (*s)[8]) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            b.mn[a] = fminf(b.mn[a], __shfl_xor(b.mn[a], o, 64));
+            b.mx[a] = fmaxf(b.mx[a], __shfl_xor(b.mx[a], o, 64));
+        }
+        b.flags |= __shfl_xor(b.flags, o, 64);
+    }
+    if ((threadIdx.x & 63u) == 0u) b.store(s[threadIdx.x >> 6]);
+    __syncthreads();
+    for (unsigned w = 0; w < NT / 64; w++) b.add(s[w]);
+}
+
+// Root cube of a box: corner = per-axis minimum, side 2^k with 2^k > largest
+// extent (frexp of the float64 extent), k = 0 for a zero extent.
+__device__ __forceinline__ SysCube root_cube(const BoxFlags &b) {
+    double ext = 0.0;
+    for (int a = 0; a < 3; a++) {
+        const double e = (double)b.mx[a] - (double)b.mn[a];
+        if (e > ext) ext = e;
+    }
+    int k = 0;
+    if (ext > 0.0) frexp(ext, &k);
+    // non-finite input: keep every later index computation tame
+    const bool tame = (b.flags & FLAG_NONFINITE) != 0;
+    SysCube c;
+    for (int a = 0; a < 3; a++) c.lo[a] = tame ? 0.0f : b.mn[a];
+    c.k = tame ? 0 : k;
+    return c;
+}
+
+// Number of leading octal digits two 60-bit keys share (0..20).
+__device__ __forceinline__ int shared_digits(uint64_t a, uint64_t b) {
+    const uint64_t x = a ^ b;
+    if (x == 0) return KEY_LEVELS;
+    return (__clzll((long long)x) - 4) / 3;
+}
+
 // Host launchers (kernels live in the .hip files).
-hipError_t launch_bbox(const Buffers &b, const float *pos, const float *mass, unsigned n, unsigned nsys,
-                       hipStream_t s);
+// boxes of *nparts stretches of each system into b.bbox_part
+hipError_t launch_bbox_partial(const Buffers &b, const float *pos, const float *mass, unsigned nsys, unsigned *nparts,
+                               hipStream_t s);
+// the same and the root cubes
+hipError_t launch_bbox(const Buffers &b, const float *pos, const float *mass, unsigned nsys, hipStream_t s);
 hipError_t launch_keys(const Buffers &b, const float *pos, const float *mass, unsigned n, unsigned nsys,
                        hipStream_t s);
 hipError_t launch_sort(const Buffers &b, unsigned n, unsigned nsys, hipStream_t s);
-// buffer (0 or 1) that holds the sorted keys and permutation after launch_sort
-inline int sorted_buffer(unsigned nsys) { return nsys > 1 ? (SORT_PASSES + 1) & 1 : SORT_PASSES & 1; }
+// Both sorts leave the sorted keys and the permutation in keys[0] and vals[0].
+// The radix sort's keys start in the buffer from which its passes end there.
+inline int radix_first_buffer(unsigned nsys) { return nsys > 1 ? (SORT_PASSES + 1) & 1 : SORT_PASSES & 1; }
+// Bucket sort (sort_kernels.hip): buckets of a system of n particles.
+constexpr unsigned SORT_BUCKET = 4096;       // elements one workgroup sorts in LDS
+// elements of a bucket on average (sorting and moving at 2^22 before the sample
+// had several lists: 1024 421 us, 1365 398, 1700 391; at 100003 101 / 104 / 102)
+constexpr unsigned SORT_BUCKET_MEAN = 1365;
+constexpr unsigned SORT_MAX_BUCKETS = 4096;  // splitters and counts of all buckets fit LDS
+// shared digits of a particle that the tree build takes from its keys
+constexpr int8_t CL_FROM_KEYS = 127;
+__host__ __device__ inline unsigned sort_buckets(unsigned n) {
+    return n <= SORT_BUCKET ? 1u : (n + SORT_BUCKET_MEAN - 1u) / SORT_BUCKET_MEAN;
+}
+bool bucket_sort_fits(const Buffers &b, unsigned n, unsigned nb);
+hipError_t launch_bucket_partition(const Buffers &b, const float *pos, const float *mass, unsigned n, unsigned nsys,
+                                   unsigned nb, unsigned nb_max, hipStream_t s);
+hipError_t launch_bucket_sort(const Buffers &b, const float *pos, const float *mass, unsigned n, unsigned nsys,
+                              unsigned nb, hipStream_t s);
 hipError_t launch_reorder(const Buffers &b, unsigned n, unsigned nsys, hipStream_t s);
 hipError_t launch_build(const Buffers &b, unsigned n, unsigned nsys, int ncrit, int gcap, hipStream_t s);
 hipError_t launch_multipoles(const Buffers &b, unsigned n, unsigned nsys, hipStream_t s);

@@ -453,7 +453,7 @@ hipError_t launch_neighbors(const Buffers &b, int mode, const float *radius, uin
     a.topo = b.topo;
     a.cbox = b.cbox;
     a.spos = b.spos;
-    a.perm = b.vals[sorted_buffer(nsys)];
+    a.perm = b.vals[0];
     a.groups = b.groups;
     a.radius = radius;
     a.scale = mode == NGB_DENSITY ? 2.0f : 1.0f;

@@ -67,17 +67,6 @@ __device__ __forceinline__ unsigned block_excl_scan(unsigned v, unsigned *s_wave
     return r;
 }
 
-// Morton bit spreading: bit b of v (20 bits) moves to bit 3b.
-__device__ __forceinline__ uint64_t spread3(uint64_t x) {
-    x &= 0x1fffffull;
-    x = (x | (x << 32)) & 0x1f00000000ffffull;
-    x = (x | (x << 16)) & 0x1f0000ff0000ffull;
-    x = (x | (x << 8)) & 0x100f00f00f00f00full;
-    x = (x | (x << 4)) & 0x10c30c30c30c30c3ull;
-    x = (x | (x << 2)) & 0x1249249249249249ull;
-    return x;
-}
-
 // Inverse of spread3: gathers bits 0, 3, 6, ... into a dense integer.
 __device__ __forceinline__ uint32_t compact3(uint64_t x) {
     x &= 0x1249249249249249ull;
@@ -87,13 +76,6 @@ __device__ __forceinline__ uint32_t compact3(uint64_t x) {
     x = (x ^ (x >> 16)) & 0x1f00000000ffffull;
     x = (x ^ (x >> 32)) & 0x1fffffull;
     return (uint32_t)x;
-}
-
-// Number of leading octal digits two 60-bit keys share (0..20).
-__device__ __forceinline__ int shared_digits(uint64_t a, uint64_t b) {
-    const uint64_t x = a ^ b;
-    if (x == 0) return KEY_LEVELS;
-    return (__clzll((long long)x) - 4) / 3;
 }
 
 // First index j > i whose key differs from key i in the first `lev` octal
@@ -126,139 +108,45 @@ __global__ __launch_bounds__(256) void k_bbox_partial(const float *__restrict__ 
                                                       const float *__restrict__ mass,
                                                       const uint32_t *__restrict__ sys_off,
                                                       float *__restrict__ part) {
+    __shared__ float s[4][8];
     const unsigned sys = blockIdx.y;
     const unsigned b0 = sys_off[sys], b1 = sys_off[sys + 1];
-    float mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
-    unsigned flags = 0;
+    BoxFlags b;
     for (unsigned i = b0 + blockIdx.x * 256u + threadIdx.x; i < b1; i += gridDim.x * 256u) {
-        const size_t b = (size_t)i * 3;
-        const float x[3] = {pos[b], pos[b + 1], pos[b + 2]};
-        const float m = mass[i];
-        if (!(isfinite(x[0]) && isfinite(x[1]) && isfinite(x[2]) && isfinite(m))) flags |= FLAG_NONFINITE;
-        if (m < 0.0f) flags |= FLAG_NEGMASS;
-#pragma unroll
-        for (int a = 0; a < 3; a++) {
-            mn[a] = fminf(mn[a], x[a]);
-            mx[a] = fmaxf(mx[a], x[a]);
-        }
+        const size_t p = (size_t)i * 3;
+        b.add(pos[p], pos[p + 1], pos[p + 2], mass[i]);
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-#pragma unroll
-        for (int a = 0; a < 3; a++) {
-            mn[a] = fminf(mn[a], __shfl_xor(mn[a], o, 64));
-            mx[a] = fmaxf(mx[a], __shfl_xor(mx[a], o, 64));
-        }
-        flags |= __shfl_xor(flags, o, 64);
-    }
-    __shared__ float s[4][8];
-    const unsigned w = threadIdx.x >> 6;
-    if (lane64() == 0) {
-        for (int a = 0; a < 3; a++) { s[w][a] = mn[a]; s[w][3 + a] = mx[a]; }
-        s[w][6] = __uint_as_float(flags);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int v = 1; v < 4; v++) {
-            for (int a = 0; a < 3; a++) {
-                s[0][a] = fminf(s[0][a], s[v][a]);
-                s[0][3 + a] = fmaxf(s[0][3 + a], s[v][3 + a]);
-            }
-            s[0][6] = __uint_as_float(__float_as_uint(s[0][6]) | __float_as_uint(s[v][6]));
-        }
-        float *o = part + ((size_t)sys * gridDim.x + blockIdx.x) * 8;
-        for (int a = 0; a < 7; a++) o[a] = s[0][a];
-    }
+    block_box<256>(b, s);
+    if (threadIdx.x == 0) b.store(part + ((size_t)sys * gridDim.x + blockIdx.x) * 8);
 }
 
-// Root cube of each system (one block per system): corner = per-axis minimum,
-// side 2^k with 2^k > largest extent (frexp of the float64 extent), k = 0 for a
-// zero extent.  Block 0 also resets the header.
+// Root cube of each system (one block per system).
 __global__ __launch_bounds__(256) void k_bbox_final(const float *__restrict__ part, unsigned nblocks,
-                                                    unsigned n, unsigned nsys, Header *__restrict__ hdr,
-                                                    SysCube *__restrict__ cube) {
-    const unsigned sys = blockIdx.x;
-    float mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
-    unsigned flags = 0;
-    for (unsigned b = threadIdx.x; b < nblocks; b += 256) {
-        const float *p = part + ((size_t)sys * nblocks + b) * 8;
-        for (int a = 0; a < 3; a++) {
-            mn[a] = fminf(mn[a], p[a]);
-            mx[a] = fmaxf(mx[a], p[3 + a]);
-        }
-        flags |= __float_as_uint(p[6]);
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        for (int a = 0; a < 3; a++) {
-            mn[a] = fminf(mn[a], __shfl_xor(mn[a], o, 64));
-            mx[a] = fmaxf(mx[a], __shfl_xor(mx[a], o, 64));
-        }
-        flags |= __shfl_xor(flags, o, 64);
-    }
+                                                    Header *__restrict__ hdr, SysCube *__restrict__ cube) {
     __shared__ float s[4][8];
-    const unsigned w = threadIdx.x >> 6;
-    if (lane64() == 0) {
-        for (int a = 0; a < 3; a++) { s[w][a] = mn[a]; s[w][3 + a] = mx[a]; }
-        s[w][6] = __uint_as_float(flags);
-    }
-    __syncthreads();
+    const unsigned sys = blockIdx.x;
+    BoxFlags b;
+    for (unsigned q = threadIdx.x; q < nblocks; q += 256) b.add(part + ((size_t)sys * nblocks + q) * 8);
+    block_box<256>(b, s);
     if (threadIdx.x == 0) {
-        for (int v = 1; v < 4; v++) {
-            for (int a = 0; a < 3; a++) {
-                s[0][a] = fminf(s[0][a], s[v][a]);
-                s[0][3 + a] = fmaxf(s[0][3 + a], s[v][3 + a]);
-            }
-            s[0][6] = __uint_as_float(__float_as_uint(s[0][6]) | __float_as_uint(s[v][6]));
-        }
-        flags = __float_as_uint(s[0][6]);
-        double ext = 0.0;
-        for (int a = 0; a < 3; a++) {
-            const double e = (double)s[0][3 + a] - (double)s[0][a];
-            if (e > ext) ext = e;
-        }
-        int k = 0;
-        if (ext > 0.0) frexp(ext, &k);
-        if (flags & FLAG_NONFINITE) {  // keep every later index computation tame
-            k = 0;
-            for (int a = 0; a < 3; a++) s[0][a] = 0.0f;
-        }
-        for (int a = 0; a < 3; a++) cube[sys].lo[a] = s[0][a];
-        cube[sys].k = k;
-        if (flags) atomicOr(&hdr->flags, flags);
+        cube[sys] = root_cube(b);
+        if (b.flags) atomicOr(&hdr->flags, b.flags);
     }
 }
 
-// Header reset, before the per-system reductions of one build.  The flags of
-// the previous build move into the sticky word, so that a driver running many
-// steps still sees a condition that one of its earlier builds met.
-__global__ void k_header_reset(unsigned n, unsigned nsys, Header *__restrict__ hdr, float4 *__restrict__ cmac,
-                               float4 *__restrict__ ceval, float4 *__restrict__ spos, unsigned cap_cells,
-                               unsigned n_max) {
-    if (threadIdx.x == 0) {
-        // the walk's padding cell and particle: massless, far away
-        cmac[cap_cells] = make_float4(WALK_FAR, WALK_FAR, WALK_FAR, 0.0f);
-        ceval[2 * (size_t)cap_cells] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        ceval[2 * (size_t)cap_cells + 1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        spos[n_max] = make_float4(WALK_FAR, WALK_FAR, WALK_FAR, 0.0f);
-        hdr->nsys = nsys;
-        hdr->sticky |= hdr->flags;
-        hdr->flags = 0;
-        hdr->n = n;
-        hdr->ncells = 0;
-        hdr->ngroups = 0;
-        for (int l = 0; l < 24; l++) hdr->lvl_begin[l] = 0;
-    }
-    if (threadIdx.x < WALK_QUEUES) hdr->walk_head[QUEUE_STRIDE * threadIdx.x] = 0;
-}
-
-hipError_t launch_bbox(const Buffers &b, const float *pos, const float *mass, unsigned n, unsigned nsys,
-                       hipStream_t s) {
+hipError_t launch_bbox_partial(const Buffers &b, const float *pos, const float *mass, unsigned nsys, unsigned *nparts,
+                               hipStream_t s) {
     const unsigned per = max((unsigned)BBOX_MIN_BLOCKS, (unsigned)BBOX_BLOCKS / nsys);
-    hipLaunchKernelGGL(k_header_reset, dim3(1), dim3(64), 0, s, n, nsys, b.hdr, b.cmac, b.ceval, b.spos, b.cap_cells,
-                       b.n_max);
     hipLaunchKernelGGL(k_bbox_partial, dim3(per, nsys), dim3(256), 0, s, pos, mass, b.sys_off, b.bbox_part);
-    hipLaunchKernelGGL(k_bbox_final, dim3(nsys), dim3(256), 0, s, b.bbox_part, per, n, nsys, b.hdr, b.cube);
+    *nparts = per;
+    return hipGetLastError();
+}
+
+hipError_t launch_bbox(const Buffers &b, const float *pos, const float *mass, unsigned nsys, hipStream_t s) {
+    unsigned per;
+    hipError_t e = launch_bbox_partial(b, pos, mass, nsys, &per, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_bbox_final, dim3(nsys), dim3(256), 0, s, b.bbox_part, per, b.hdr, b.cube);
     return hipGetLastError();
 }
 
@@ -276,19 +164,9 @@ __global__ __launch_bounds__(256) void k_keys(const float *__restrict__ pos, con
     const unsigned i = blockIdx.x * 256u + threadIdx.x;
     if (i >= n) return;
     const unsigned sys = nsys > 1 ? system_of(sys_off, nsys, i) : 0u;
-    const SysCube c = cube[sys];
-    const double s = ldexp(1.0, KEY_LEVELS - c.k);
-    const float x[3] = {pos[(size_t)i * 3], pos[(size_t)i * 3 + 1], pos[(size_t)i * 3 + 2]};
-    ppack[i] = make_float4(x[0], x[1], x[2], mass[i]);
-    uint64_t q[3];
-#pragma unroll
-    for (int a = 0; a < 3; a++) {
-        double f = floor(((double)x[a] - (double)c.lo[a]) * s);
-        if (!(f >= 0.0)) f = 0.0;
-        if (f > 1048575.0) f = 1048575.0;
-        q[a] = (uint64_t)f;
-    }
-    keys[i] = (spread3(q[0]) << 2) | (spread3(q[1]) << 1) | spread3(q[2]);
+    const float x = pos[(size_t)i * 3], y = pos[(size_t)i * 3 + 1], z = pos[(size_t)i * 3 + 2];
+    ppack[i] = make_float4(x, y, z, mass[i]);
+    keys[i] = morton_key(cube[sys], x, y, z);
     if (nsys > 1) sys8[i] = (uint8_t)sys;
 }
 
@@ -316,7 +194,7 @@ hipError_t launch_pack(const Buffers &b, const float *pos, const float *mass, un
 hipError_t launch_keys(const Buffers &b, const float *pos, const float *mass, unsigned n, unsigned nsys,
                        hipStream_t s) {
     hipLaunchKernelGGL(k_keys, dim3((n + 255) / 256), dim3(256), 0, s, pos, mass, n, nsys, b.sys_off, b.cube,
-                       b.keys[0], b.sys8, b.ppack);
+                       b.keys[radix_first_buffer(nsys)], b.sys8, b.ppack);
     return hipGetLastError();
 }
 
@@ -501,7 +379,7 @@ hipError_t launch_sort(const Buffers &b, unsigned n, unsigned nsys, hipStream_t 
     const unsigned ntiles = (n + SORT_TILE - 1) / SORT_TILE;
     const int passes = SORT_PASSES + (nsys > 1 ? 1 : 0);
     for (int pass = 0; pass < passes; pass++) {
-        const int src = pass & 1, dst = src ^ 1;
+        const int src = (pass + radix_first_buffer(nsys)) & 1, dst = src ^ 1;
         const int shift = pass < SORT_PASSES ? pass * RADIX_BITS : -1;
         if (shift < 0 || shift >= MIBH_HIST_AGG_SHIFT)
             hipLaunchKernelGGL(k_radix_hist<true>, dim3(ntiles), dim3(SORT_THREADS), 0, s, b.keys[src], b.vals[src],
@@ -535,8 +413,7 @@ __global__ __launch_bounds__(256) void k_reorder(const float4 *__restrict__ ppac
 }
 
 hipError_t launch_reorder(const Buffers &b, unsigned n, unsigned nsys, hipStream_t s) {
-    const int sb = sorted_buffer(nsys);
-    hipLaunchKernelGGL(k_reorder, dim3((n + 255) / 256), dim3(256), 0, s, b.ppack, b.keys[sb], b.vals[sb],
+    hipLaunchKernelGGL(k_reorder, dim3((n + 255) / 256), dim3(256), 0, s, b.ppack, b.keys[0], b.vals[0],
                        n, nsys, b.sys_off, b.spos, b.cl);
     return hipGetLastError();
 }
@@ -593,6 +470,7 @@ __global__ __launch_bounds__(BUILD_THREADS) void k_build_count(
     for (int r = 0; r < 3; r++) {
         const long long j = wb - 64 + 64 * r + ln_;
         t[r] = (j >= 0 && j < (long long)n) ? (int)cl[j] : -1;
+        if (t[r] == CL_FROM_KEYS) t[r] = shared_digits(keys[j - 1], keys[j]);  // a sort bucket's first particle
     }
     const int ci = t[1];
     // Minima by doubling: after step k, t[r] at lane l is the minimum of the 2^k
@@ -854,7 +732,7 @@ __global__ __launch_bounds__(256) void k_build_nchild(const Header *__restrict__
 
 hipError_t launch_build(const Buffers &b, unsigned n, unsigned nsys, int ncrit, int gcap, hipStream_t s) {
     const unsigned nblk = (n + BUILD_THREADS - 1) / BUILD_THREADS;
-    const uint64_t *keys = b.keys[sorted_buffer(nsys)];
+    const uint64_t *keys = b.keys[0];
     hipLaunchKernelGGL(k_build_count, dim3(nblk), dim3(BUILD_THREADS), 0, s, b.cl, keys, n, nsys, b.sys_off,
                        ncrit, gcap, b.lvinfo, b.blkcnt, nblk);
     hipLaunchKernelGGL(k_build_scan, dim3(NCOUNTERS), dim3(1024), 0, s, b.blkcnt, nblk, b.ctot);
@@ -1239,7 +1117,7 @@ __global__ __launch_bounds__(MP_THREADS) void k_multipole_merge(const Header *__
 }
 
 hipError_t launch_multipoles(const Buffers &b, unsigned n, unsigned nsys, hipStream_t s) {
-    const CellBuffers a = {b.cube, b.topo, b.keys[sorted_buffer(nsys)], b.spos, b.mp, b.delta, b.cbox, b.lside,
+    const CellBuffers a = {b.cube, b.topo, b.keys[0], b.spos, b.mp, b.delta, b.cbox, b.lside,
                            b.cmac, b.ceval};
     const unsigned nblk = (n + BUILD_THREADS - 1) / BUILD_THREADS;
     unsigned nr = (n + MP_CHUNK - 1) / MP_CHUNK;

@@ -825,7 +825,7 @@ hipError_t launch_walk(const Buffers &b, unsigned n, unsigned nsys, float eps2, 
     a.cmac = b.cmac;
     a.ceval = b.ceval;
     a.spos = b.spos;
-    a.perm = b.vals[sorted_buffer(nsys)];
+    a.perm = b.vals[0];
     a.groups = b.groups;
     a.gcounts = b.gcounts;
     a.wstack = b.wstack;
@@ -1028,7 +1028,7 @@ hipError_t launch_queue_order(const Buffers &b, int mode, const uint8_t *active,
     o.groups = b.groups;
     o.pred = b.pred;
     o.counts = b.gcounts;
-    o.perm = b.vals[sorted_buffer(nsys)];
+    o.perm = b.vals[0];
     o.active = active;
     o.mode = mode;
     hipLaunchKernelGGL(k_order_hist, dim3(ORDER_BLOCKS), dim3(ORDER_THREADS), 0, s, o, b.ohist);
