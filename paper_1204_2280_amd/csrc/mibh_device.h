@@ -91,20 +91,33 @@ struct Header {
 // processing order (Morton order by default), so the waves of one XCD walk
 // neighbouring groups, whose cells they then share in that XCD's L2.  A wave
 // takes slots from its XCD's queue, then from the following queues in turn as
-// each runs empty, and stops when all are empty.
+// each runs empty, and stops when all are empty.  Where the launch has a
+// workgroup for every slot, each takes the slot of its number within its XCD's
+// eighth and no queue is touched: the eight failing atomics in a row that end a
+// wave took 20-30 us of such a walk.  ONCE = false leaves that case out, for the
+// walk of large trees: the code cost its full register file 1.5% of a step.
+// (Reading all eight heads at once when one runs empty cost it 2-3%.)
 constexpr unsigned WALK_QUEUES = 8;
 constexpr unsigned QUEUE_STRIDE = 64;  // words between queue heads
 
 struct QueueCursor {
-    unsigned q, tried;  // queue in use, queues found empty
+    unsigned q, tried;  // queue in use, queues found empty (one slot per workgroup: 0 until it was taken)
 };
 
 __device__ __forceinline__ QueueCursor queue_start() { return QueueCursor{blockIdx.x % WALK_QUEUES, 0u}; }
 
-// Next slot for the calling wave, or n when every queue is empty.  Every lane
-// calls it (lane 0 adds 1, the others 0), so no lane-dependent branch is
-// needed around it.
+// Next slot for the calling wave, or n when there is none.  Every lane calls it
+// (lane 0 adds 1, the others 0), so no lane-dependent branch is needed around
+// it.
+template <bool ONCE = true>
 __device__ __forceinline__ unsigned queue_next(unsigned *heads, unsigned n, QueueCursor &qc) {
+    const unsigned per = (n + WALK_QUEUES - 1u) / WALK_QUEUES;
+    if (ONCE && per * WALK_QUEUES <= gridDim.x) {
+        const unsigned k = blockIdx.x / WALK_QUEUES;
+        const bool take = qc.tried == 0u && k < per;
+        qc.tried = 1u;
+        return take ? min(qc.q * per + k, n) : n;
+    }
     while (qc.tried < WALK_QUEUES) {
         const unsigned lo = (unsigned)((unsigned long long)n * qc.q / WALK_QUEUES);
         const unsigned hi = (unsigned)((unsigned long long)n * (qc.q + 1u) / WALK_QUEUES);
@@ -136,7 +149,8 @@ constexpr unsigned PREFIX_SCRATCH = PREFIX_F_CAP + 2 * PREFIX_S_CAP;
 // 2^32 - 1 words, the reach of a 32-bit offset.  Anchors that find no room
 // leave their groups to walk from the root.
 constexpr unsigned PREFIX_POOL_WORDS_1 = 16;
-constexpr unsigned PREFIX_STEP = 4;     // stack cells per lane in one step of an anchor's traversal
+constexpr unsigned PREFIX_WAVES = 4;    // waves that build an anchor's lists
+constexpr unsigned PREFIX_THREADS = 64 * PREFIX_WAVES;
 constexpr unsigned PREFIX_RING = 4096;  // LDS stack ring of the anchor-list pass
 constexpr unsigned WALK_PC_LDS = 1024;  // particle-cell list
 constexpr unsigned WALK_PP_LDS = 512;   // particle-particle list

@@ -2,12 +2,13 @@
 // Results section) on gfx950.
 //
 // One wave64 per group (the vector-machine idea of Barnes 1990: one
-// interaction list shared by a group of nearby particles), persistent waves
-// pulling groups from eight queues, one per XCD, each an atomic head on a
-// cache line of its own over one eighth of the processing order: the groups
-// in Morton order (the waves of an XCD then walk spatial neighbours, whose
-// cells they share in that XCD's L2) or a work-ordered permutation, heaviest
-// groups first.  A wave whose queue is empty takes groups from the others.
+// interaction list shared by a group of nearby particles; two or four waves where
+// groups are few, see walk_group_waves), persistent waves pulling groups from
+// eight queues, one per XCD, each an atomic head on a cache line of its own over
+// one eighth of the processing order: the groups in Morton order (the waves of an
+// XCD then walk spatial neighbours, whose cells they share in that XCD's L2) or a
+// work-ordered permutation, heaviest groups first.  A wave whose queue is empty
+// takes groups from the others.
 //
 // Traversal: lanes hold up to 64 candidate cells popped from a per-wave stack
 // kept in LDS (circular, spilling its bottom to a per-wave global stack when
@@ -45,6 +46,15 @@ __device__ __forceinline__ unsigned rank_below(unsigned long long mask) {
 }
 
 __device__ __forceinline__ unsigned uniform(unsigned v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Orders this wave's own LDS and global accesses: its lanes then read what its
+// other lanes wrote.  The hardware runs one wave's accesses in order, so this
+// costs nothing beyond keeping the compiler from moving them, where a workgroup
+// barrier waits for every outstanding access.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 
 __device__ __forceinline__ unsigned bitrev6(unsigned l) {
     return ((l & 1u) << 5) | ((l & 2u) << 3) | ((l & 4u) << 1) | ((l & 8u) >> 1) | ((l & 16u) >> 3) |
@@ -208,21 +218,22 @@ template <int PREC> __device__ __forceinline__ unsigned res_slot(unsigned c, uns
 // Evaluates the particle-cell entries `fl` (`nfl`, an anchor's shared cells in
 // the pool, or none) and `pcl` (`npcl`, in LDS) and the particle-particle
 // entries `ppl` (`nppl`), all whole 64-entry tiles (a list's last tile is padded
-// with the massless far cell or particle), for all `gn` group particles and
+// with the massless far cell or particle), for the group particles [g0, g1) and
 // adds the results into s_res (one value per lane per chunk): one reduction per
 // chunk covers all the lists.  Whole tiles need no per-lane test or substitute
-// in the tile loops.
+// in the tile loops.  A particle's sums depend on the lists alone, not on the
+// chunk or the wave that holds it.
 template <int PREC>
 __device__ void evaluate(const WalkArgs &a, const uint32_t *fl, unsigned nfl, const uint32_t *pcl, unsigned npcl,
-                         const uint32_t *ppl, unsigned nppl, unsigned gn, float px, float py, float pz, float *s_res,
-                         float *s_cmp) {
+                         const uint32_t *ppl, unsigned nppl, unsigned g0, unsigned g1, float px, float py, float pz,
+                         float *s_res, float *s_cmp) {
     constexpr int CHUNK = chunk_of<PREC>();
     constexpr int NV = 4 * CHUNK;
     constexpr bool TERM = PREC == 2;
     const unsigned ln = lane64();
     const float eps2 = a.eps2;
-    for (unsigned c0 = 0; c0 < gn; c0 += CHUNK) {
-        const unsigned cn = min((unsigned)CHUNK, gn - c0);
+    for (unsigned c0 = g0; c0 < g1; c0 += CHUNK) {
+        const unsigned cn = min((unsigned)CHUNK, g1 - c0);
         float xi[CHUNK], yi[CHUNK], zi[CHUNK];
 #pragma unroll
         for (int ii = 0; ii < CHUNK; ii++) {
@@ -308,36 +319,53 @@ __device__ void evaluate(const WalkArgs &a, const uint32_t *fl, unsigned nfl, co
             for (int j = 0; j < NV; j++) v[j] = v[j] - cv[j];
         }
         const float r = transpose_reduce<NV>(v);
-        const unsigned slot = res_slot<PREC>(c0 / CHUNK, ln);
+        const unsigned slot = res_slot<PREC>((c0 - g0) / CHUNK, ln);
         if (PREC) add<true>(s_res[slot], s_cmp[slot], r);
         else s_res[slot] += r;
     }
 }
 
-// Evaluates the list's whole 64-entry tiles, moves the remaining entries to
-// the front and returns their number.
-template <int PREC, bool PC>
-__device__ unsigned flush_list(const WalkArgs &a, uint32_t *list, unsigned n, unsigned gn, float px, float py,
-                               float pz, float *s_res, float *s_cmp) {
+// What the first wave of a workgroup asks the others to evaluate.
+enum : unsigned { EVAL_PC = 0, EVAL_PP = 1, EVAL_LAST = 2, EVAL_NONE = 3 };
+struct EvalCmd {
+    unsigned what, npc, npp;
+};
+
+// Evaluates the list's whole 64-entry tiles (the first wave's call; with NW > 1
+// the other waves take their particles meanwhile), moves the remaining entries
+// to the front and returns their number.
+template <int PREC, bool PC, int NW>
+__device__ unsigned flush_list(const WalkArgs &a, uint32_t *list, unsigned n, unsigned g1, float px, float py,
+                               float pz, float *s_res, float *s_cmp, EvalCmd *s_cmd) {
     const unsigned ne = n & ~63u;
-    __syncthreads();  // list entries written by other lanes are visible
+    wave_sync();  // list entries written by other lanes are visible
     if (ne) {
-        if (PC) evaluate<PREC>(a, nullptr, 0u, list, ne, list, 0u, gn, px, py, pz, s_res, s_cmp);
-        else evaluate<PREC>(a, nullptr, 0u, list, 0u, list, ne, gn, px, py, pz, s_res, s_cmp);
+        if (NW > 1) {
+            *s_cmd = EvalCmd{PC ? EVAL_PC : EVAL_PP, ne, ne};
+            __syncthreads();
+        }
+        if (PC) evaluate<PREC>(a, nullptr, 0u, list, ne, list, 0u, 0u, g1, px, py, pz, s_res, s_cmp);
+        else evaluate<PREC>(a, nullptr, 0u, list, 0u, list, ne, 0u, g1, px, py, pz, s_res, s_cmp);
+        if (NW > 1) __syncthreads();  // the others are done with the list
     }
     const unsigned r = n - ne;
     if (r) {
         const unsigned ln = lane64();
         const unsigned v = ln < r ? list[ne + ln] : 0u;
-        __syncthreads();
+        wave_sync();
         if (ln < r) list[ln] = v;
-        __syncthreads();
+        wave_sync();
     }
     return r;
 }
 
-template <int PREC, bool SHARED>
-__global__ __launch_bounds__(64, 4) void k_walk(WalkArgs a) {
+// One group per workgroup of NW waves.  The first wave builds the group's lists;
+// all of them evaluate the lists, each for its share of the particles.  NW = 1
+// is the walk of a full chip.  Where there are fewer groups than the chip holds
+// waves, the walk lasts as long as its heaviest group, and NW waves shorten
+// that: see walk_group_waves.
+template <int PREC, bool SHARED, int NW>
+__global__ __launch_bounds__(64 * NW, 4) void k_walk(WalkArgs a) {
     constexpr unsigned MASK = WALK_LSTACK - 1;
     static_assert((WALK_LSTACK & MASK) == 0 && WALK_LSTACK >= 512, "stack ring must hold one step's pushes");
     static_assert(PREFIX_S_CAP <= WALK_LSTACK, "an anchor's cells left fit the empty ring");
@@ -347,11 +375,16 @@ __global__ __launch_bounds__(64, 4) void k_walk(WalkArgs a) {
     constexpr unsigned PC_LDS = PREC ? WALK_PC_LDS - 192 : WALK_PC_LDS;
     __shared__ uint32_t s_pc[PC_LDS];
     __shared__ uint32_t s_pp[WALK_PP_LDS];
-    __shared__ float s_res[256];
-    __shared__ float s_cmp[PREC ? 256 : 64];
+    __shared__ float s_res_all[256];
+    __shared__ float s_cmp_all[PREC ? 256 : 64];
     __shared__ uint32_t s_idx[64];  // group particle evaluated in each lane
     __shared__ uint32_t s_perm[64];  // caller's index of each group particle
+    __shared__ EvalCmd s_cmd;
+    __shared__ unsigned s_slot;
     const unsigned ln = lane64();
+    const unsigned wid = NW > 1 ? uniform(threadIdx.x >> 6) : 0u;
+    float *const s_res = s_res_all + wid * (256 / NW);
+    float *const s_cmp = s_cmp_all + (PREC ? wid * (256 / NW) : 0u);
     uint32_t *gstk = a.wstack + (size_t)blockIdx.x * STACK_CAP;
     if (a.hdr->flags & (FLAG_NONFINITE | FLAG_NEGMASS | FLAG_CELLCAP)) return;
     // particles a lane may add to the particle-particle list per round, so that
@@ -366,7 +399,14 @@ __global__ __launch_bounds__(64, 4) void k_walk(WalkArgs a) {
         // lane-dependent branch sits inside this loop: the compiler may split a
         // loop on a loop-invariant divergent condition, which would separate
         // lane 0 from the cross-lane operations of the other lanes.
-        const unsigned slot = queue_next(a.head, ngroups, qc);
+        unsigned slot;
+        if (NW > 1) {
+            if (wid == 0) s_slot = queue_next(a.head, ngroups, qc);
+            __syncthreads();
+            slot = uniform(s_slot);
+        } else {
+            slot = queue_next<false>(a.head, ngroups, qc);  // a large tree: more groups than workgroups
+        }
         if (slot >= ngroups) break;
         const unsigned g = a.order ? uniform(a.order[slot]) : slot;
         const uint2 gr = a.groups[g];
@@ -395,9 +435,10 @@ __global__ __launch_bounds__(64, 4) void k_walk(WalkArgs a) {
         const bool due = ln < gn && (!a.active || a.active[pm] != 0);
         const unsigned long long dm = __ballot(due);
         const unsigned ge = (unsigned)__popcll(dm);
+        // (every wave of the workgroup writes the same values)
         if (due) s_idx[rank_below(dm)] = ln;
         s_perm[ln] = pm;
-        __syncthreads();
+        wave_sync();
         const unsigned pv = s_idx[ln];
         const unsigned pj = ln < ge ? pv : 0u;
         float4 p;
@@ -406,17 +447,29 @@ __global__ __launch_bounds__(64, 4) void k_walk(WalkArgs a) {
         p.z = __shfl(p0.z, pj, 64);
         p.w = 0.0f;
 #pragma unroll
-        for (int c = 0; c < 4; c++) {
+        for (int c = 0; c < 4 / NW; c++) {
             s_res[c * 64 + ln] = 0.0f;
             if (PREC) s_cmp[c * 64 + ln] = 0.0f;
         }
+        // this wave's particles
+        const unsigned share = (ge + NW - 1u) / NW;
+        const unsigned g0 = min(wid * share, ge), g1 = min(g0 + share, ge);
 
+        unsigned f_off = 0, f_n = 0;  // the shared accepted cells, whole tiles in the pool
+        bool seeded = false;
+        if (SHARED) {
+            seeded = uniform(rec.w) == 1u;
+            if (seeded) {
+                f_off = uniform(rec.x);
+                f_n = (uniform(rec.y) + 63u) & ~63u;
+            }
+        }
+        unsigned npc = 0, npp = 0;
+        bool overflow = false;
+        if (wid == 0) {
         // logical stack = global spill [0, gtop) followed by the LDS ring [sb, st)
         unsigned sb = 0, st = 0, gtop = 0;
-        unsigned npc = 0, npp = 0, tot_pc = 0, tot_pp = 0;
-        bool overflow = false;
-        bool seeded = false;
-        unsigned f_off = 0, f_n = 0;  // the shared accepted cells, whole tiles in the pool
+        unsigned tot_pc = 0, tot_pp = 0;
         if (SHARED) {
             // the lists shared by the groups below this group's anchor cell: its
             // accepted cells are evaluated in place, from the pool, with the
@@ -424,15 +477,11 @@ __global__ __launch_bounds__(64, 4) void k_walk(WalkArgs a) {
             // left (sorted by level, shallowest at the bottom, so that stack levels
             // never decrease towards the top), in the LDS ring, which is empty here
             // and holds all of them (<= PREFIX_S_CAP)
-            seeded = uniform(rec.w) == 1u;
             if (seeded) {
-                const unsigned off = uniform(rec.x), nf = uniform(rec.y), ns = uniform(rec.z);
-                const unsigned nfp = (nf + 63u) & ~63u;
-                for (unsigned i = ln; i < ns; i += 64) s_stk[i] = a.pool[off + nfp + i];
+                const unsigned ns = uniform(rec.z);
+                for (unsigned i = ln; i < ns; i += 64) s_stk[i] = a.pool[f_off + f_n + i];
                 st = ns;
-                f_off = off;
-                f_n = nfp;
-                tot_pc += nf;
+                tot_pc += uniform(rec.y);
             }
         }
         if (!seeded) {
@@ -445,16 +494,15 @@ __global__ __launch_bounds__(64, 4) void k_walk(WalkArgs a) {
             const unsigned first = rn ? tr.z + min(ln, rn - 1) : root;
             if (ln < st) s_stk[ln] = first;
         }
-        __threadfence_block();
-        __syncthreads();
+        wave_sync();
         while (st != sb || gtop > 0) {
             if (st == sb) {  // LDS part empty: refill from the top of the global spill
                 const unsigned k = min(gtop, WALK_LSTACK / 2);
-                __threadfence_block();
+                wave_sync();
                 for (unsigned i = ln; i < k; i += 64) s_stk[(sb - k + i) & MASK] = gstk[gtop - k + i];
                 sb -= k;
                 gtop -= k;
-                __syncthreads();
+                wave_sync();
             }
             const unsigned m = min(st - sb, 64u);
             const bool valid = ln < m;
@@ -478,7 +526,7 @@ __global__ __launch_bounds__(64, 4) void k_walk(WalkArgs a) {
             const unsigned long long am = __ballot(accept);
             const unsigned na = (unsigned)__popcll(am);
             if (npc + na > pc_cap)
-                npc = flush_list<PREC, true>(a, s_pc, npc, ge, p.x, p.y, p.z, s_res, s_cmp);
+                npc = flush_list<PREC, true, NW>(a, s_pc, npc, g1, p.x, p.y, p.z, s_res, s_cmp, &s_cmd);
             if (accept) s_pc[npc + rank_below(am)] = c;
             npc += na;
             tot_pc += na;
@@ -503,7 +551,7 @@ __global__ __launch_bounds__(64, 4) void k_walk(WalkArgs a) {
                 const unsigned off = excl & 0xffffu;
                 if (sum + 63u <= a.pp_cap) {
                     if (npp + sum > a.pp_cap)
-                        npp = flush_list<PREC, false>(a, s_pp, npp, ge, p.x, p.y, p.z, s_res, s_cmp);
+                        npp = flush_list<PREC, false, NW>(a, s_pp, npp, g1, p.x, p.y, p.z, s_res, s_cmp, &s_cmd);
                     for (unsigned j = 0; j < rem; j++) s_pp[npp + off + j] = src + j;
                     npp += sum;
                     tot_pp += sum;
@@ -515,7 +563,7 @@ __global__ __launch_bounds__(64, 4) void k_walk(WalkArgs a) {
                 unsigned sum;
                 const unsigned off = small_excl_scan(take, &sum);
                 if (npp + sum > a.pp_cap)
-                    npp = flush_list<PREC, false>(a, s_pp, npp, ge, p.x, p.y, p.z, s_res, s_cmp);
+                    npp = flush_list<PREC, false, NW>(a, s_pp, npp, g1, p.x, p.y, p.z, s_res, s_cmp, &s_cmd);
                 for (unsigned j = 0; j < take; j++) s_pp[npp + off + j] = src + j;
                 npp += sum;
                 tot_pp += sum;
@@ -537,27 +585,47 @@ __global__ __launch_bounds__(64, 4) void k_walk(WalkArgs a) {
                 for (unsigned i = ln; i < sp; i += 64) gstk[gtop + i] = s_stk[(sb + i) & MASK];
                 sb += sp;
                 gtop += sp;
-                __syncthreads();
+                wave_sync();
             }
             for (unsigned j = 0; j < nc; j++) s_stk[(st + off + j) & MASK] = t.z + j;
             st += nsum;
-            __syncthreads();
+            wave_sync();
         }
         if (overflow) {
             atomicOr(&a.hdr->flags, FLAG_STACK);
-            continue;
-        }
-        if (f_n + npc + npp) {
+        } else {
             // both lists' last tiles padded with the massless far cell and
             // particle (npc <= pc_cap and npp <= pp_cap, so the padded lists
             // stay within their LDS arrays, whole tiles long)
             const unsigned npc_t = (npc + 63u) & ~63u, npp_t = (npp + 63u) & ~63u;
             if (npc + ln < npc_t) s_pc[npc + ln] = a.dcell;
             if (npp + ln < npp_t) s_pp[npp + ln] = a.dpart;
-            __syncthreads();  // list entries written by other lanes are visible
-            evaluate<PREC>(a, f_n ? a.pool + f_off : nullptr, f_n, s_pc, npc_t, s_pp, npp_t, ge, p.x, p.y, p.z,
-                           s_res, s_cmp);
+            npc = npc_t;
+            npp = npp_t;
+            a.gcounts[g] = make_uint2(tot_pc, tot_pp);  // same value from every lane
         }
+        wave_sync();  // list entries written by other lanes are visible
+        if (NW > 1) {
+            s_cmd = EvalCmd{overflow ? EVAL_NONE : EVAL_LAST, npc, npp};
+            __syncthreads();
+        }
+        } else {  // the other waves: their particles of each evaluation the first one asks for
+            for (;;) {
+                __syncthreads();
+                const unsigned what = uniform(s_cmd.what);
+                npc = uniform(s_cmd.npc);
+                npp = uniform(s_cmd.npp);
+                overflow = what == EVAL_NONE;
+                if (what >= EVAL_LAST) break;
+                evaluate<PREC>(a, nullptr, 0u, s_pc, what == EVAL_PC ? npc : 0u, s_pp, what == EVAL_PP ? npp : 0u, g0, g1,
+                               p.x, p.y, p.z, s_res, s_cmp);
+                __syncthreads();
+            }
+        }
+        if (overflow) continue;
+        if (f_n + npc + npp)
+            evaluate<PREC>(a, f_n ? a.pool + f_off : nullptr, f_n, s_pc, npc, s_pp, npp, g0, g1, p.x, p.y, p.z, s_res,
+                           s_cmp);
 
         // results back to the caller's order
         constexpr int CHUNK = chunk_of<PREC>();
@@ -566,9 +634,9 @@ __global__ __launch_bounds__(64, 4) void k_walk(WalkArgs a) {
         // bits (32 per chunk, lanes ln and ln ^ 1 alike: the even one stores)
         const unsigned idx = HALF ? (bitrev6(ln) & 31u) : bitrev6(ln);
         const unsigned comp = idx & 3u;
-        for (unsigned c = 0; c * CHUNK < ge; c++) {
-            const unsigned pi = c * CHUNK + (idx >> 2) + ((HALF && (ln & 1u)) ? 64u : 0u);
-            if (pi < ge) {
+        for (unsigned c = 0; c * CHUNK < g1 - g0; c++) {
+            const unsigned pi = g0 + c * CHUNK + (idx >> 2) + ((HALF && (ln & 1u)) ? 64u : 0u);
+            if (pi < g1) {
                 const unsigned slot = res_slot<PREC>(c, ln);
                 float val = s_res[slot];
                 if (PREC) val = val - s_cmp[slot];
@@ -578,7 +646,6 @@ __global__ __launch_bounds__(64, 4) void k_walk(WalkArgs a) {
                 else a.pot[orig] = val;
             }
         }
-        a.gcounts[g] = make_uint2(tot_pc, tot_pp);  // same value from every lane
     }
 }
 
@@ -644,16 +711,26 @@ __global__ __launch_bounds__(256) void k_walk_claim(const Header *__restrict__ h
     }
 }
 
-// F and S of anchor cell A into this wave's scratch (F at pf, S sorted by level
-// at pf + PREFIX_F_CAP + PREFIX_S_CAP).  False when a list outgrows its room or
-// the stack its bound (the groups then walk from the root).  A step takes up to
-// PREFIX_STEP cells per lane off the stack: the pass is bound by the dependent
-// round trips of its longest traversal, not by its arithmetic.
-__device__ bool anchor_lists(const WalkArgs &a, unsigned A, uint32_t *s_stk, uint32_t *gstk, uint32_t *pf,
+// F and S of anchor cell A into this workgroup's scratch (F at pf, S sorted by
+// level at pf + PREFIX_F_CAP + PREFIX_S_CAP).  False when a list outgrows its
+// room or the stack its bound (the groups then walk from the root).  A step takes
+// up to 256 cells off the stack, one per thread: the pass is bound by the
+// dependent round trips of its traversals, about 10 steps each.  One wave taking
+// 4 cells per lane had a step's four batches one after the other: the pass took
+// 65 / 71 / 80 us at n = 32768 / 2^20 / 2^22, with four waves 42 / 45 / 55, and
+// without eight empty queues tried at its end 19 / 23 / 33.
+struct PrefixShared {
+    uint32_t stk[PREFIX_RING];
+    unsigned cnt[2][PREFIX_WAVES][3];               // accepted, left, children of each wave, by parity of the step
+    unsigned lev[KEY_LEVELS + 1][PREFIX_S_CAP / 64];  // cells of a level in each batch of 64
+    unsigned off[2];
+};
+
+__device__ bool anchor_lists(const WalkArgs &a, unsigned A, PrefixShared &sh, uint32_t *gstk, uint32_t *pf,
                              unsigned *nf_out, unsigned *ns_out) {
-    constexpr unsigned K = PREFIX_STEP, RING = PREFIX_RING, MASK = RING - 1;
-    static_assert((RING & MASK) == 0 && RING >= 2 * 64 * 8 * K, "ring must hold one step's pushes");
-    const unsigned ln = lane64();
+    constexpr unsigned NT = PREFIX_THREADS, RING = PREFIX_RING, MASK = RING - 1;
+    static_assert((RING & MASK) == 0 && RING >= 2 * NT * 8, "ring must hold one step's pushes");
+    const unsigned t = threadIdx.x, ln = lane64(), w = uniform(t >> 6);
     uint32_t *praw = pf + PREFIX_F_CAP, *pseed = praw + PREFIX_S_CAP;
     const uint4 ta = a.topo[A];
     const unsigned af = uniform(ta.x), alev = uniform((ta.w >> 8) & 255u), root = uniform(ta.w >> 16);
@@ -663,63 +740,60 @@ __device__ bool anchor_lists(const WalkArgs &a, unsigned A, uint32_t *s_stk, uin
     const unsigned rn = uniform(tr.w & 255u);
     unsigned sb = 0, st = rn ? rn : 1u, gtop = 0, nf = 0, ns = 0;
     bool ok = true;
-    const unsigned first = rn ? tr.z + min(ln, rn - 1) : root;
-    if (ln < st) s_stk[ln] = first;
+    if (t < st) sh.stk[t] = rn ? tr.z + t : root;
     __syncthreads();
-    while (st != sb || gtop > 0) {
+    for (unsigned par = 0; st != sb || gtop > 0; par ^= 1u) {
         if (st == sb) {  // LDS part empty: refill from the top of the global spill
             const unsigned k = min(gtop, RING / 2);
-            __threadfence_block();
-            for (unsigned i = ln; i < k; i += 64) s_stk[(sb - k + i) & MASK] = gstk[gtop - k + i];
+            for (unsigned i = t; i < k; i += NT) sh.stk[(sb - k + i) & MASK] = gstk[gtop - k + i];
             sb -= k;
             gtop -= k;
             __syncthreads();
         }
-        const unsigned m = min(st - sb, 64u * K);
-        unsigned c[K];
-        uint4 t[K];
-        float4 mc[K];
-#pragma unroll
-        for (unsigned k = 0; k < K; k++) {
-            const unsigned i = k * 64u + ln;
-            c[k] = i < m ? s_stk[(st - m + i) & MASK] : 0u;
-        }
-#pragma unroll
-        for (unsigned k = 0; k < K; k++) {
-            t[k] = a.topo[c[k]];
-            mc[k] = a.cmac[c[k]];
-        }
+        const unsigned m = min(st - sb, NT);
+        const bool valid = t < m;
+        const unsigned c = valid ? sh.stk[(st - m + t) & MASK] : 0u;
         st -= m;
-        unsigned nc[K], nsum = 0;
+        const uint4 tc = a.topo[c];
+        const float4 mc = a.cmac[c];
+        const unsigned lvl = (tc.w >> 8) & 255u, nch = tc.w & 255u;
+        const bool anc = tc.x <= af && af < tc.x + tc.y && lvl <= alev;
+        // both tests in every lane, no short-circuit: the MAC load then goes
+        // out with the topology load (see the group walk)
+        const bool reach = !(far_d2(bmin, bmax, mc) > mc.w);
+        const bool far = mac_accept(bmin, bmax, mc);
+        const bool open = valid & (anc | reach);
+        const bool accept = valid & !open & far;
+        const bool left = valid && !accept && (!open || nch == 0);
+        const unsigned long long am = __ballot(accept), lm = __ballot(left);
+        const unsigned nc = open ? nch : 0u;
+        unsigned tk;
+        const unsigned o = small_excl_scan(nc, &tk);
+        // this wave's counts to the others, theirs back: the popped entries have
+        // been read when the barrier is passed
+        sh.cnt[par][w][0] = (unsigned)__popcll(am);
+        sh.cnt[par][w][1] = (unsigned)__popcll(lm);
+        sh.cnt[par][w][2] = tk;
+        __syncthreads();
+        unsigned before[3] = {0u, 0u, 0u}, all[3] = {0u, 0u, 0u};
 #pragma unroll
-        for (unsigned k = 0; k < K; k++) {
-            const bool valid = k * 64u + ln < m;
-            const unsigned lvl = (t[k].w >> 8) & 255u, nch = t[k].w & 255u;
-            const bool anc = t[k].x <= af && af < t[k].x + t[k].y && lvl <= alev;
-            // both tests in every lane, no short-circuit: the MAC loads then go
-            // out with the topology loads (see the group walk)
-            const bool reach = !(far_d2(bmin, bmax, mc[k]) > mc[k].w);
-            const bool far = mac_accept(bmin, bmax, mc[k]);
-            const bool open = valid & (anc | reach);
-            const bool accept = valid & !open & far;
-            const bool left = valid && !accept && (!open || nch == 0);
-            const unsigned long long am = __ballot(accept);
-            const unsigned na = (unsigned)__popcll(am);
-            const unsigned long long lm = __ballot(left);
-            const unsigned nl = (unsigned)__popcll(lm);
-            if (nf + na > PREFIX_F_CAP || ns + nl > PREFIX_S_CAP) ok = false;
-            if (ok && accept) pf[nf + rank_below(am)] = c[k];
-            if (ok && left) praw[ns + rank_below(lm)] = c[k];
-            nf += na;
-            ns += nl;
-            nc[k] = open ? nch : 0u;
-            unsigned tk;
-            const unsigned o = small_excl_scan(nc[k], &tk);
-            nc[k] |= (nsum + o) << 8;  // this lane's first push slot above st, with its count
-            nsum += tk;
+        for (unsigned v = 0; v < PREFIX_WAVES; v++) {
+#pragma unroll
+            for (unsigned k = 0; k < 3; k++) {
+                const unsigned x = uniform(sh.cnt[par][v][k]);
+                before[k] += v < w ? x : 0u;
+                all[k] += x;
+            }
         }
-        if (!ok) break;
-        const unsigned used = st - sb;
+        if (nf + all[0] > PREFIX_F_CAP || ns + all[1] > PREFIX_S_CAP) {  // the same for the whole workgroup
+            ok = false;
+            break;
+        }
+        if (accept) pf[nf + before[0] + rank_below(am)] = c;
+        if (left) praw[ns + before[1] + rank_below(lm)] = c;
+        nf += all[0];
+        ns += all[1];
+        const unsigned nsum = all[2], used = st - sb;
         if (used + nsum > RING) {  // spill the bottom of the LDS ring
             const unsigned need = used + nsum - RING;
             const unsigned sp = min(used, max(need, RING / 2));
@@ -727,90 +801,143 @@ __device__ bool anchor_lists(const WalkArgs &a, unsigned A, uint32_t *s_stk, uin
                 ok = false;
                 break;
             }
-            for (unsigned i = ln; i < sp; i += 64) gstk[gtop + i] = s_stk[(sb + i) & MASK];
+            for (unsigned i = t; i < sp; i += NT) gstk[gtop + i] = sh.stk[(sb + i) & MASK];
             sb += sp;
             gtop += sp;
             __syncthreads();
         }
-#pragma unroll
-        for (unsigned k = 0; k < K; k++) {
-            const unsigned cnt = nc[k] & 255u, off = nc[k] >> 8;
-            for (unsigned j = 0; j < cnt; j++) s_stk[(st + off + j) & MASK] = t[k].z + j;
-        }
+        for (unsigned j = 0; j < nc; j++) sh.stk[(st + before[2] + o + j) & MASK] = tc.z + j;
         st += nsum;
         __syncthreads();
     }
-    __threadfence_block();
-    if (ok) {  // S by level, shallowest first: a counting pass over the levels
-        unsigned cell[PREFIX_S_CAP / 64], lv[PREFIX_S_CAP / 64];
+    __syncthreads();
+    if (ok) {  // S by level, shallowest first, in order within a level: ranks in batches of 64
+        constexpr unsigned NB = PREFIX_S_CAP / 64, PER = NB / PREFIX_WAVES;
+        for (unsigned k = t; k < (KEY_LEVELS + 1u) * NB; k += NT) (&sh.lev[0][0])[k] = 0;
+        __syncthreads();
+        unsigned cell[PER], lv[PER], rank[PER];
 #pragma unroll
-        for (unsigned k = 0; k < PREFIX_S_CAP / 64; k++) {
-            const unsigned i = k * 64 + ln;
-            cell[k] = i < ns ? praw[i] : 0u;
-            lv[k] = i < ns ? (a.topo[cell[k]].w >> 8) & 255u : 255u;
+        for (unsigned x = 0; x < PER; x++) {
+            const unsigned b = w * PER + x, i = b * 64 + ln;
+            const bool in = i < ns;
+            cell[x] = in ? praw[i] : 0u;
+            lv[x] = in ? (a.topo[cell[x]].w >> 8) & 255u : 0u;
+            unsigned long long peers = __ballot(in);
+#pragma unroll
+            for (int bit = 0; bit < 5; bit++) {
+                static_assert(KEY_LEVELS < 32, "5-bit levels");
+                const bool v = (lv[x] >> bit) & 1u;
+                const unsigned long long bm = __ballot(v);
+                peers &= v ? bm : ~bm;
+            }
+            rank[x] = rank_below(peers);
+            if (in && rank[x] == 0) sh.lev[lv[x]][b] = (unsigned)__popcll(peers);
         }
-        unsigned pos = 0;
-        for (unsigned l = 0; l <= (unsigned)KEY_LEVELS; l++) {
+        __syncthreads();
+        if (t < 64u) {  // places of the level's batches: a scan of the table, level by level
+            constexpr unsigned N = (KEY_LEVELS + 1) * NB, P = (N + 63u) / 64u;
+            unsigned *tab = &sh.lev[0][0];
+            unsigned v[P], sum = 0;
 #pragma unroll
-            for (unsigned k = 0; k < PREFIX_S_CAP / 64; k++) {
-                const bool h = lv[k] == l;
-                const unsigned long long hm = __ballot(h);
-                if (h) pseed[pos + rank_below(hm)] = cell[k];
-                pos += (unsigned)__popcll(hm);
+            for (unsigned k = 0; k < P; k++) {
+                v[k] = t * P + k < N ? tab[t * P + k] : 0u;
+                sum += v[k];
+            }
+            unsigned run = wave_incl_scan(sum) - sum;
+#pragma unroll
+            for (unsigned k = 0; k < P; k++) {
+                if (t * P + k < N) tab[t * P + k] = run;
+                run += v[k];
             }
         }
-        __threadfence_block();
+        __syncthreads();
+#pragma unroll
+        for (unsigned x = 0; x < PER; x++) {
+            const unsigned b = w * PER + x;
+            if (b * 64 + ln < ns) pseed[sh.lev[lv[x]][b] + rank[x]] = cell[x];
+        }
+        __syncthreads();
     }
     *nf_out = nf;
     *ns_out = ns;
     return ok;
 }
 
-// One pass over the anchor list (persistent waves, per-XCD queues as in the
-// walk; one anchor per queue slot): a wave builds its anchor's lists, stores
+// One pass over the anchor list (persistent workgroups, per-XCD queues as in the
+// walk; one anchor per queue slot): a workgroup builds its anchor's lists, stores
 // them in the pool and their place in arec[anchor] (valid word 1; all zero when
 // they did not fit, and the anchor's groups walk from the root).
-__global__ __launch_bounds__(64) void k_walk_prefix(WalkArgs a, unsigned *__restrict__ prefix_head,
-                                                    const unsigned *__restrict__ acount,
-                                                    const uint32_t *__restrict__ alist,
-                                                    unsigned long long *__restrict__ pool_head,
-                                                    uint4 *__restrict__ arec, uint32_t *__restrict__ pool,
-                                                    unsigned long long pool_cap,
-                                                    uint32_t *__restrict__ pscr, unsigned *__restrict__ nfail) {
-    __shared__ uint32_t s_stk[PREFIX_RING];
-    const unsigned ln = lane64();
+__global__ __launch_bounds__(PREFIX_THREADS) void k_walk_prefix(WalkArgs a, unsigned *__restrict__ prefix_head,
+                                                                const unsigned *__restrict__ acount,
+                                                                const uint32_t *__restrict__ alist,
+                                                                unsigned long long *__restrict__ pool_head,
+                                                                uint4 *__restrict__ arec, uint32_t *__restrict__ pool,
+                                                                unsigned long long pool_cap,
+                                                                uint32_t *__restrict__ pscr,
+                                                                unsigned *__restrict__ nfail) {
+    __shared__ PrefixShared sh;
+    const unsigned t = threadIdx.x, ln = lane64(), w = uniform(t >> 6);
     uint32_t *gstk = a.wstack + (size_t)blockIdx.x * STACK_CAP;
     uint32_t *pf = pscr + (size_t)blockIdx.x * PREFIX_SCRATCH;
     if (a.hdr->flags & (FLAG_NONFINITE | FLAG_NEGMASS | FLAG_CELLCAP)) return;
     const unsigned nanchor = uniform(*acount);
     QueueCursor qc = queue_start();
     for (;;) {
-        const unsigned slot = queue_next(prefix_head, nanchor, qc);
+        if (w == 0) sh.off[0] = queue_next(prefix_head, nanchor, qc);
+        __syncthreads();
+        const unsigned slot = uniform(sh.off[0]);
         if (slot >= nanchor) break;
         const unsigned A = uniform(alist[slot]);
         unsigned nf, ns;
-        bool ok = anchor_lists(a, A, s_stk, gstk, pf, &nf, &ns);
-        nf = uniform(nf);
-        ns = uniform(ns);
+        bool ok = anchor_lists(a, A, sh, gstk, pf, &nf, &ns);
         // F takes whole 64-entry tiles in the pool (padded with the massless far
         // cell): the groups evaluate it in place
         const unsigned nfp = (nf + 63u) & ~63u;
-        unsigned long long off64 = 0;
-        if (ok) {  // every lane calls the atomic (lane 0 adds), see queue_next
-            off64 = atomicAdd(pool_head, ln == 0 ? (unsigned long long)(nfp + ns) : 0ull);
+        if (w == 0) {
+            unsigned long long off64 = ~0ull;
+            if (ok) off64 = atomicAdd(pool_head, ln == 0 ? (unsigned long long)(nfp + ns) : 0ull);
             off64 = ((unsigned long long)uniform((unsigned)(off64 >> 32)) << 32) | uniform((unsigned)off64);
-            ok = off64 + nfp + ns <= pool_cap;
+            const bool fits = ok && off64 + nfp + ns <= pool_cap;
+            if (!fits) atomicAdd(nfail, ln == 0 ? 1u : 0u);  // the same for the whole wave
+            sh.off[0] = (unsigned)off64;  // < 2^32 when it fits
+            sh.off[1] = fits ? 1u : 0u;
         }
-        if (!ok) atomicAdd(nfail, ln == 0 ? 1u : 0u);  // ok is wave-uniform
-        const unsigned off = (unsigned)off64;  // < 2^32 when ok
+        __syncthreads();
+        const unsigned off = uniform(sh.off[0]);
+        ok = uniform(sh.off[1]) != 0u;
         if (ok) {
-            for (unsigned i = ln; i < nfp; i += 64) pool[off + i] = i < nf ? pf[i] : a.dcell;
+            for (unsigned i = t; i < nfp; i += PREFIX_THREADS) pool[off + i] = i < nf ? pf[i] : a.dcell;
             const uint32_t *pseed = pf + PREFIX_F_CAP + PREFIX_S_CAP;
-            for (unsigned i = ln; i < ns; i += 64) pool[off + nfp + i] = pseed[i];
+            for (unsigned i = t; i < ns; i += PREFIX_THREADS) pool[off + nfp + i] = pseed[i];
         }
-        // every lane stores the same record: no lane-dependent branch in this loop
+        // every thread stores the same record: no lane-dependent branch in this loop
         arec[A] = ok ? make_uint4(off, nf, ns, 1u) : make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();  // sh.off and the scratch are free again
     }
+}
+
+// Waves per group for a tree of n particles.  A chip full of groups wants one:
+// the waves that wait while the first builds the lists hold registers that
+// another group's wave could use.  With few groups the heaviest one sets the
+// time.  Walk stage with 1 / 2 / 4 waves per group (Plummer sphere, theta 0.75,
+// us): n = 1000 96 / 66 / 52, 20000 195 / 131 / 121, 32768 209 / 148 / 146,
+// 65536 260 / 217 / 229, 131072 390 / 370 / 415, 200000 480 / 481 / 555, 300007
+// 617 / 636 / 746, 2^20 1513 / 1731 / 2334.  The results are the same bits.
+int walk_group_waves(unsigned n) { return n <= 32768u ? 4 : n <= 160000u ? 2 : 1; }
+
+// As many workgroups as the launch parameter's waves have spill stacks.  Of 4096
+// workgroups of 2 or 4 waves the chip holds a half or a quarter at once; the
+// others follow as those end, so up to 4096 groups need no queue.
+template <int PREC, int NW>
+void launch_walk_groups(const WalkArgs &a, bool shared, unsigned grid, hipStream_t s) {
+    if (shared) hipLaunchKernelGGL((k_walk<PREC, true, NW>), dim3(grid), dim3(64 * NW), 0, s, a);
+    else hipLaunchKernelGGL((k_walk<PREC, false, NW>), dim3(grid), dim3(64 * NW), 0, s, a);
+}
+template <int PREC>
+void launch_walk_waves(const WalkArgs &a, bool shared, int nw, unsigned waves, hipStream_t s) {
+    if (nw == 4) launch_walk_groups<PREC, 4>(a, shared, waves, s);
+    else if (nw == 2) launch_walk_groups<PREC, 2>(a, shared, waves, s);
+    else launch_walk_groups<PREC, 1>(a, shared, waves, s);
 }
 
 }  // namespace
@@ -818,7 +945,6 @@ __global__ __launch_bounds__(64) void k_walk_prefix(WalkArgs a, unsigned *__rest
 hipError_t launch_walk(const Buffers &b, unsigned n, unsigned nsys, float eps2, float G, int precision,
                        const uint32_t *order, const uint32_t *qlen, const uint8_t *active, float *acc, float *pot,
                        int anchor_up, hipStream_t s) {
-    (void)n;
     WalkArgs a;
     a.hdr = b.hdr;
     a.topo = b.topo;
@@ -852,20 +978,14 @@ hipError_t launch_walk(const Buffers &b, unsigned n, unsigned nsys, float eps2, 
                            b.arec);
         hipLaunchKernelGGL(k_walk_claim, dim3(grid), dim3(256), 0, s, b.hdr, b.anchor, order, qlen, b.arec, b.alist,
                            &b.hdr->anchor_count);
-        hipLaunchKernelGGL(k_walk_prefix, dim3(b.walk_waves), dim3(64), 0, s, a, b.hdr->prefix_head,
+        hipLaunchKernelGGL(k_walk_prefix, dim3(min(b.walk_waves, 1024u)), dim3(PREFIX_THREADS), 0, s, a, b.hdr->prefix_head,
                            &b.hdr->anchor_count, b.alist, &b.hdr->pool_head, b.arec, b.pool, b.pool_cap, b.pscr,
                            &b.hdr->anchor_fail);
     }
-    if (precision == 2) {
-        if (shared) hipLaunchKernelGGL((k_walk<2, true>), dim3(b.walk_waves), dim3(64), 0, s, a);
-        else hipLaunchKernelGGL((k_walk<2, false>), dim3(b.walk_waves), dim3(64), 0, s, a);
-    } else if (precision == 1) {
-        if (shared) hipLaunchKernelGGL((k_walk<1, true>), dim3(b.walk_waves), dim3(64), 0, s, a);
-        else hipLaunchKernelGGL((k_walk<1, false>), dim3(b.walk_waves), dim3(64), 0, s, a);
-    } else {
-        if (shared) hipLaunchKernelGGL((k_walk<0, true>), dim3(b.walk_waves), dim3(64), 0, s, a);
-        else hipLaunchKernelGGL((k_walk<0, false>), dim3(b.walk_waves), dim3(64), 0, s, a);
-    }
+    const int nw = walk_group_waves(n);
+    if (precision == 2) launch_walk_waves<2>(a, shared, nw, b.walk_waves, s);
+    else if (precision == 1) launch_walk_waves<1>(a, shared, nw, b.walk_waves, s);
+    else launch_walk_waves<0>(a, shared, nw, b.walk_waves, s);
     return hipGetLastError();
 }
 
