@@ -82,11 +82,6 @@ __global__ __launch_bounds__(256) void k_features(const Header *__restrict__ hdr
 // waves per SIMD; bounds asking for three or four waves make it spill).
 // --------------------------------------------------------------------------
 
-__device__ __forceinline__ void load_weights(const __half *__restrict__ w16, float *s_w) {
-    for (int i = threadIdx.x; i < MLP_NPARAM; i += blockDim.x) s_w[i] = __half2float(w16[i]);
-    __syncthreads();
-}
-
 // LDS image for the forward pass: W1, b1 as stored, W2 transposed, b2, w3, b3.
 static_assert(OFF_W2 % 4 == 0, "float4 reads of the transposed second layer");
 constexpr int FWD_W2T = OFF_W2;
@@ -139,105 +134,177 @@ __global__ __launch_bounds__(256) void k_mlp_fwd(const __half *__restrict__ w16,
 }
 
 // --------------------------------------------------------------------------
-// Backward pass of the mean squared error over a batch of sampled rows,
-// 64 samples per block: every sample's activations and deltas go to LDS, then
-// thread t sums row t of each weight gradient over the 64 samples in sample
-// order.  Partial gradients per block are summed over blocks in block order.
+// Backward pass of the mean squared error over a batch of sampled rows.  A
+// workgroup of four waves takes tiles of 16 samples; the 64-wide products (second
+// layer forward, its transpose backward, the second layer's weight gradient) run
+// on the float32 matrix instruction (16 x 16 outputs, 4 terms), wave w for hidden
+// units 16 w .. 16 w + 15, and the weight gradients stay in its accumulators over
+// the workgroup's tiles.  Partial gradients per workgroup are then summed in a
+// fixed order.
+// What bounds it is latency: a batch of 1024 is 64 tiles, about ten dependent
+// LDS and matrix steps each.  With one thread per sample and 64 samples per
+// workgroup, 16 workgroups ran 64-term loops out of LDS for 84 us.
 // --------------------------------------------------------------------------
 
-constexpr int GS = 64;  // samples per block
+constexpr int GT = 16;            // samples per tile
+constexpr int GRAD_THREADS = 256;
+constexpr unsigned GRAD_BLOCKS = 1024;  // workgroups at most: larger batches take several tiles each
+constexpr int GP = MLP_H + 4;     // row pitch of the activations in LDS
 
-__global__ __launch_bounds__(GS) void k_mlp_grad(const __half *__restrict__ w16, const float *__restrict__ x,
-                                                 const float *__restrict__ target, const int *__restrict__ idx,
-                                                 unsigned batch, float *__restrict__ partial,
-                                                 float *__restrict__ loss_part) {
-    __shared__ float s_w[MLP_NPARAM];
-    __shared__ float s_x[GS][MLP_IN];
-    __shared__ float s_h1[GS][MLP_H + 1];
-    __shared__ float s_h2[GS][MLP_H + 1];
-    __shared__ float s_d2[GS][MLP_H + 1];
-    __shared__ float s_d1[GS][MLP_H + 1];
-    __shared__ float s_dy[GS], s_e2[GS];
-    load_weights(w16, s_w);
-    const unsigned t = threadIdx.x;
-    const unsigned s = blockIdx.x * GS + t;
-    const bool valid = s < batch;
-    const int row = valid ? idx[s] : 0;
-    float xi[MLP_IN];
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+inline unsigned grad_blocks(unsigned batch) { return min((batch + GT - 1u) / GT, GRAD_BLOCKS); }
+
+// acc += A B, one 16 x 16 tile over 64 terms: A row l & 15 from ap (stride 1 in
+// the term), B column from bp (stride bs).  Lane l takes terms (l >> 4) * 16 + s
+// in step s: any order of the terms will do as long as A and B agree.
+template <typename T>
+__device__ __forceinline__ f32x4 mfma_64(const float *ap, const T *bp, int bs, f32x4 acc) {
+    const int k0 = (int)(threadIdx.x >> 4 & 3u) * 16;
 #pragma unroll
-    for (int k = 0; k < MLP_IN; k++) {
-        xi[k] = valid ? x[(size_t)row * MLP_IN + k] : 0.0f;
-        s_x[t][k] = xi[k];
-    }
-    // forward, keeping activations
-    for (int i = 0; i < MLP_H; i++) {
-        float a = s_w[OFF_B1 + i];
-        for (int k = 0; k < MLP_IN; k++) a = fmaf(s_w[OFF_W1 + i * MLP_IN + k], xi[k], a);
-        s_h1[t][i] = fmaxf(a, 0.0f);
-    }
-    float y = s_w[OFF_B3];
-    for (int i = 0; i < MLP_H; i++) {
-        float a = s_w[OFF_B2 + i];
-        for (int j = 0; j < MLP_H; j++) a = fmaf(s_w[OFF_W2 + i * MLP_H + j], s_h1[t][j], a);
-        const float h = fmaxf(a, 0.0f);
-        s_h2[t][i] = h;
-        y = fmaf(s_w[OFF_W3 + i], h, y);
-    }
-    const float err = valid ? y - target[row] : 0.0f;
-    const float dy = 2.0f * err / (float)batch;
-    s_dy[t] = dy;
-    s_e2[t] = err * err;
-    for (int i = 0; i < MLP_H; i++) s_d2[t][i] = s_h2[t][i] > 0.0f ? dy * s_w[OFF_W3 + i] : 0.0f;
-    for (int j = 0; j < MLP_H; j++) {
-        float a = 0.0f;
-        for (int i = 0; i < MLP_H; i++) a = fmaf(s_w[OFF_W2 + i * MLP_H + j], s_d2[t][i], a);
-        s_d1[t][j] = s_h1[t][j] > 0.0f ? a : 0.0f;
-    }
-    __syncthreads();
-    // weight gradients, row t, summed over the block's samples in order
-    float *out = partial + (size_t)blockIdx.x * MLP_NPARAM;
-    for (int j = 0; j < MLP_H; j++) {
-        float a = 0.0f;
-        for (int q = 0; q < GS; q++) a = fmaf(s_d2[q][t], s_h1[q][j], a);
-        out[OFF_W2 + t * MLP_H + j] = a;
-    }
-    for (int k = 0; k < MLP_IN; k++) {
-        float a = 0.0f;
-        for (int q = 0; q < GS; q++) a = fmaf(s_d1[q][t], s_x[q][k], a);
-        out[OFF_W1 + t * MLP_IN + k] = a;
-    }
-    float b1 = 0.0f, b2 = 0.0f, w3 = 0.0f;
-    for (int q = 0; q < GS; q++) {
-        b1 += s_d1[q][t];
-        b2 += s_d2[q][t];
-        w3 = fmaf(s_dy[q], s_h2[q][t], w3);
-    }
-    out[OFF_B1 + t] = b1;
-    out[OFF_B2 + t] = b2;
-    out[OFF_W3 + t] = w3;
-    if (t == 0) {
-        float b3 = 0.0f, l = 0.0f;
-        for (int q = 0; q < GS; q++) {
-            b3 += s_dy[q];
-            l += s_e2[q];
-        }
-        out[OFF_B3] = b3;
-        loss_part[blockIdx.x] = l;
-    }
+    for (int s = 0; s < 16; s++)
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ap[k0 + s], (float)bp[(k0 + s) * bs], acc, 0, 0, 0);
+    return acc;
 }
 
+__global__ __launch_bounds__(GRAD_THREADS) void k_mlp_grad(const __half *__restrict__ w16, const float *__restrict__ x,
+                                                           const float *__restrict__ target,
+                                                           const int *__restrict__ idx, unsigned batch,
+                                                           float *__restrict__ partial,
+                                                           float *__restrict__ loss_part) {
+    static_assert(MLP_H == 64 && MLP_IN == 8 && GRAD_THREADS == 256, "one wave per 16 hidden units");
+    __shared__ _Float16 s_w[MLP_NPARAM + 1];
+    __shared__ float s_x[GT][MLP_IN], s_h1[GT][GP], s_h2[GT][GP], s_d2[GT][GP], s_d1[GT][GP];
+    __shared__ float s_dy[GT], s_e2[GT], s_t[GT];
+    const int t = (int)threadIdx.x, w = t >> 6, ln = t & 63, col = ln & 15, quad = ln >> 4;
+    const _Float16 *w16f = reinterpret_cast<const _Float16 *>(w16);
+    for (int i = t; i < MLP_NPARAM; i += GRAD_THREADS) s_w[i] = w16f[i];
+    const unsigned tiles = (batch + GT - 1u) / GT;
+    f32x4 g2[4] = {};                 // dW2[16 w + 4 quad + r][16 c + col]
+    float g1[2] = {0.0f, 0.0f};       // dW1 of parameters t, t + 256
+    float gb = 0.0f, gl = 0.0f;       // t < 64 b1, < 128 b2, < 192 w3, 192 b3; 193 loss
+    for (unsigned tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        if (t < GT * MLP_IN) {
+            const unsigned s = tile * GT + (unsigned)t / MLP_IN;
+            const bool valid = s < batch;
+            const int row = valid ? idx[s] : 0;
+            s_x[t / MLP_IN][t % MLP_IN] = valid ? x[(size_t)row * MLP_IN + t % MLP_IN] : 0.0f;
+            if (t % MLP_IN == 0) s_t[t / MLP_IN] = valid ? target[row] : 0.0f;
+        }
+        __syncthreads();
+        // first layer: unit ln of samples 4 w .. 4 w + 3
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            float a = (float)s_w[OFF_B1 + ln];
+#pragma unroll
+            for (int k = 0; k < MLP_IN; k++) a = fmaf((float)s_w[OFF_W1 + ln * MLP_IN + k], s_x[4 * w + q][k], a);
+            s_h1[4 * w + q][ln] = fmaxf(a, 0.0f);
+        }
+        __syncthreads();
+        // second layer: units 16 w + col; rows of the result are samples 4 quad + r
+        const int u = 16 * w + col;
+        {
+            const float b = (float)s_w[OFF_B2 + u];
+            f32x4 h = {b, b, b, b};
+            h = mfma_64(s_h1[col], s_w + OFF_W2 + u * MLP_H, 1, h);
+#pragma unroll
+            for (int r = 0; r < 4; r++) s_h2[4 * quad + r][u] = fmaxf(h[r], 0.0f);
+        }
+        __syncthreads();
+        // output, error and its derivative: sample t >> 4, 4 units per lane
+        {
+            const int q = t >> 4;
+            float y = 0.0f;
+#pragma unroll
+            for (int k = 0; k < 4; k++) y = fmaf((float)s_w[OFF_W3 + col + 16 * k], s_h2[q][col + 16 * k], y);
+#pragma unroll
+            for (int o = 8; o > 0; o >>= 1) y += __shfl_xor(y, o, 16);
+            y += (float)s_w[OFF_B3];
+            const float err = tile * GT + (unsigned)q < batch ? y - s_t[q] : 0.0f;
+            const float dy = 2.0f * err / (float)batch;
+            s_dy[q] = dy;  // the same value from 16 lanes
+            s_e2[q] = err * err;
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const int i = col + 16 * k;
+                s_d2[q][i] = s_h2[q][i] > 0.0f ? dy * (float)s_w[OFF_W3 + i] : 0.0f;
+            }
+        }
+        __syncthreads();
+        // deltas of the first layer, units u
+        {
+            f32x4 d = {};
+            d = mfma_64(s_d2[col], s_w + OFF_W2 + u, MLP_H, d);
+#pragma unroll
+            for (int r = 0; r < 4; r++) s_d1[4 * quad + r][u] = s_h1[4 * quad + r][u] > 0.0f ? d[r] : 0.0f;
+        }
+        // second layer's weight gradient: rows 16 w .., over the tile's 16 samples
+#pragma unroll
+        for (int c = 0; c < 4; c++)
+#pragma unroll
+            for (int s = 0; s < 4; s++)
+                g2[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(s_d2[4 * s + quad][16 * w + col],
+                                                             s_h1[4 * s + quad][16 * c + col], g2[c], 0, 0, 0);
+        __syncthreads();
+        // the others, one or two parameters per thread
+#pragma unroll
+        for (int p = 0; p < 2; p++) {
+            const int i = (t + 256 * p) / MLP_IN, k = t % MLP_IN;
+#pragma unroll
+            for (int q = 0; q < GT; q++) g1[p] = fmaf(s_d1[q][i], s_x[q][k], g1[p]);
+        }
+        if (t < 64) {
+            for (int q = 0; q < GT; q++) gb += s_d1[q][t];
+        } else if (t < 128) {
+            for (int q = 0; q < GT; q++) gb += s_d2[q][t - 64];
+        } else if (t < 192) {
+            for (int q = 0; q < GT; q++) gb = fmaf(s_dy[q], s_h2[q][t - 128], gb);
+        } else if (t == 192) {
+            for (int q = 0; q < GT; q++) gb += s_dy[q];
+        } else if (t == 193) {
+            for (int q = 0; q < GT; q++) gl += s_e2[q];
+        }
+        __syncthreads();
+    }
+    float *out = partial + (size_t)blockIdx.x * MLP_NPARAM;
+#pragma unroll
+    for (int c = 0; c < 4; c++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) out[OFF_W2 + (16 * w + 4 * quad + r) * MLP_H + 16 * c + col] = g2[c][r];
+    out[OFF_W1 + t] = g1[0];
+    out[OFF_W1 + 256 + t] = g1[1];
+    if (t < 64) out[OFF_B1 + t] = gb;
+    else if (t < 128) out[OFF_B2 + t - 64] = gb;
+    else if (t < 192) out[OFF_W3 + t - 128] = gb;
+    else if (t == 192) out[OFF_B3] = gb;
+    else if (t == 193) loss_part[blockIdx.x] = gl;
+}
+
+// Sums the workgroups' partials: 16 parameters per workgroup, 16 threads per
+// parameter over the partials 16 apart, then those 16 sums in a fixed tree.  The
+// last workgroup sums the loss the same way.
 __global__ __launch_bounds__(256) void k_mlp_reduce(const float *__restrict__ partial, unsigned nblk,
                                                     const float *__restrict__ loss_part, unsigned batch,
                                                     float *__restrict__ grad, float *__restrict__ loss) {
-    for (unsigned p = blockIdx.x * 256u + threadIdx.x; p < (unsigned)MLP_NPARAM; p += gridDim.x * 256u) {
-        float a = 0.0f;
-        for (unsigned b = 0; b < nblk; b++) a += partial[(size_t)b * MLP_NPARAM + p];
-        grad[p] = a;
+    __shared__ float s[16][17];
+    const unsigned c = threadIdx.x & 15u, r = threadIdx.x >> 4;
+    const bool is_loss = blockIdx.x == gridDim.x - 1u;
+    const unsigned p = blockIdx.x * 16u + c;
+    const float *src = is_loss ? loss_part : partial + p;
+    const size_t stride = is_loss ? 1u : (size_t)MLP_NPARAM;
+    float a = 0.0f;
+    if (is_loss ? c == 0u : p < (unsigned)MLP_NPARAM) {
+#pragma unroll 4
+        for (unsigned b = r; b < nblk; b += 16u) a += src[b * stride];
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0 && loss) {
-        float l = 0.0f;
-        for (unsigned b = 0; b < nblk; b++) l += loss_part[b];
-        *loss = l / (float)batch;
+    s[r][c] = a;
+    __syncthreads();
+    a = s[c][r];  // lane c of a row of 16: partial sum c of parameter r
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) a += __shfl_xor(a, o, 16);
+    if (c == 0u) {
+        if (!is_loss && blockIdx.x * 16u + r < (unsigned)MLP_NPARAM) grad[blockIdx.x * 16u + r] = a;
+        if (is_loss && r == 0u && loss) *loss = a / (float)batch;
     }
 }
 
@@ -273,18 +340,18 @@ hipError_t launch_mlp_forward(const void *w16, const float *x, unsigned rows, co
 }
 
 size_t mlp_scratch_bytes(unsigned batch) {
-    const size_t nblk = (batch + GS - 1) / GS;
+    const size_t nblk = grad_blocks(batch);
     return nblk * MLP_NPARAM * sizeof(float) + nblk * sizeof(float) + 256;
 }
 
 hipError_t launch_mlp_grad(const void *w16, const float *x, const float *target, const int *idx, unsigned batch,
                            float *grad, float *loss, void *scratch, hipStream_t s) {
-    const unsigned nblk = (batch + GS - 1) / GS;
+    const unsigned nblk = grad_blocks(batch);
     float *partial = (float *)scratch;
     float *loss_part = partial + (size_t)nblk * MLP_NPARAM;
-    hipLaunchKernelGGL(k_mlp_grad, dim3(nblk), dim3(GS), 0, s, (const __half *)w16, x, target, idx, batch, partial,
-                       loss_part);
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((MLP_NPARAM + 255) / 256), dim3(256), 0, s, partial, nblk, loss_part,
+    hipLaunchKernelGGL(k_mlp_grad, dim3(nblk), dim3(GRAD_THREADS), 0, s, (const __half *)w16, x, target, idx, batch,
+                       partial, loss_part);
+    hipLaunchKernelGGL(k_mlp_reduce, dim3((MLP_NPARAM + 15) / 16 + 1), dim3(256), 0, s, partial, nblk, loss_part,
                        batch, grad, loss);
     return hipGetLastError();
 }
