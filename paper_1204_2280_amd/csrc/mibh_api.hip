@@ -15,7 +15,7 @@
 using namespace mibh;
 
 // queue mode of a walk over the groups holding an active particle (internal)
-constexpr int ORDER_ACTIVE = 3;
+constexpr int ORDER_ACTIVE = ORDER_MODE_ACTIVE;
 // the neighbour-list offset scan keeps its tile sums in the queue-order counts
 constexpr int SCAN_MAX_TILES = ORDER_BUCKETS * ORDER_BLOCKS;
 
@@ -177,6 +177,8 @@ size_t layout(int64_t n_max, const mibh_params &p, char *base, Buffers *b) {
     t.gref = (uint32_t *)take(4 * n);
     t.bsum = (unsigned long long *)take(8 * 4);
     t.qorder = (uint32_t *)take(4 * n);
+    t.gflag = (uint8_t *)take(n);
+    t.acnt = (uint32_t *)take(4 * ((n + 511) / 512));
     const bool shared_walk = p.anchor_up > 0;
     t.anchor = shared_walk ? (uint32_t *)take(4 * n) : nullptr;
     t.alist = shared_walk ? (uint32_t *)take(4 * n) : nullptr;

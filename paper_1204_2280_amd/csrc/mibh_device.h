@@ -196,6 +196,8 @@ struct Buffers {
     uint32_t *gref;         // block time steps: work of a group at its first walk after a build (0: none)
     unsigned long long *bsum;  // block time steps: [0] work now, [1] reference work, [2] due particles
     uint32_t *qorder;       // walk queue: groups in processing order (work-ordered modes)
+    uint8_t *gflag;         // active walks: group holds an active particle
+    uint32_t *acnt;         // active walks: such groups per 512
     uint32_t *anchor;       // shared-prefix walk: anchor cell of each group
     uint32_t *alist;        // shared-prefix walk: the anchor cells, each once
     uint4 *arec;            // shared-prefix walk, per cell: pool offset, |F|, |S|, 1 if the lists are valid
@@ -367,8 +369,9 @@ hipError_t launch_adam(float *w32, void *w16, const float *grad, float *m, float
                        float beta1, float beta2, float eps, hipStream_t s);
 // Writes b.qorder: the groups ordered by work, heaviest first; mode 1: work
 // predicted by the estimator (b.pred), 2: exact counts of the last walk; mode
-// 3: groups holding a particle with active[input index] != 0 first (their
-// number, after the call, is b.ohist[ORDER_BLOCKS]), in Morton order.
+// ORDER_MODE_ACTIVE: groups holding a particle with active[input index] != 0
+// first (their number, after the call, is b.ohist[ORDER_BLOCKS]), in Morton order.
+constexpr int ORDER_MODE_ACTIVE = 3;
 hipError_t launch_queue_order(const Buffers &b, int mode, const uint8_t *active, unsigned nsys, hipStream_t s);
 // Packs input (x, y, z, m) into b.ppack and flags non-finite or negative values.
 hipError_t launch_pack(const Buffers &b, const float *pos, const float *mass, unsigned n, hipStream_t s);

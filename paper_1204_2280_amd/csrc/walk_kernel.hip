@@ -990,6 +990,102 @@ hipError_t launch_walk(const Buffers &b, unsigned n, unsigned nsys, float eps2, 
 }
 
 // --------------------------------------------------------------------------
+// Queue of an active walk: the groups that hold an active particle, then the
+// others, both in Morton order.  Bound by the latency of perm and the mask behind
+// it: a wave reads a group's particles at once, eight groups in flight.  20 us at
+// 2^20 particles (15 + 5); by the counting sort below, with one thread per group
+// that read its particles one after the other in two of the three kernels, 52 us.
+// A block's first slot is the sum of the counts of the blocks before it.
+// --------------------------------------------------------------------------
+namespace {
+
+constexpr unsigned ACT_BLOCK = 512;  // groups per workgroup and threads
+
+__global__ __launch_bounds__(ACT_BLOCK) void k_active_flag(const Header *__restrict__ hdr,
+                                                           const uint2 *__restrict__ groups,
+                                                           const uint32_t *__restrict__ perm,
+                                                           const uint8_t *__restrict__ active,
+                                                           uint8_t *__restrict__ gflag, uint32_t *__restrict__ bcnt) {
+    constexpr unsigned IN_FLIGHT = 8;
+    __shared__ unsigned s_cnt[ACT_BLOCK / 64];
+    if (hdr->flags & (FLAG_NONFINITE | FLAG_NEGMASS | FLAG_CELLCAP)) return;
+    const unsigned ng = hdr->ngroups, ln = lane64(), w = uniform(threadIdx.x >> 6);
+    for (unsigned blk = blockIdx.x; blk * ACT_BLOCK < ng; blk += gridDim.x) {
+        const unsigned g0 = blk * ACT_BLOCK + w * 64;  // this wave's groups, one per lane
+        const uint2 gr = groups[min(g0 + ln, ng - 1u)];
+        unsigned long long any = 0;  // bit k: group g0 + k holds an active particle
+        for (unsigned k0 = 0; k0 < 64; k0 += IN_FLIGHT) {
+            uint8_t v[IN_FLIGHT];
+#pragma unroll
+            for (unsigned u = 0; u < IN_FLIGHT; u++) {
+                const unsigned first = __builtin_amdgcn_readlane(gr.x, k0 + u);
+                const unsigned cnt = __builtin_amdgcn_readlane(gr.y, k0 + u) & 255u;
+                v[u] = active[perm[first + min(ln, cnt - 1u)]];
+            }
+#pragma unroll
+            for (unsigned u = 0; u < IN_FLIGHT; u++) any |= __ballot(v[u] != 0) ? 1ull << (k0 + u) : 0ull;
+        }
+        const bool mine = g0 + ln < ng && ((any >> ln) & 1ull);
+        if (g0 + ln < ng) gflag[g0 + ln] = mine ? 1 : 0;
+        const unsigned cnt = (unsigned)__popcll(__ballot(mine));
+        if (ln == 0) s_cnt[w] = cnt;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            unsigned sum = 0;
+            for (unsigned v = 0; v < ACT_BLOCK / 64; v++) sum += s_cnt[v];
+            bcnt[blk] = sum;
+        }
+        __syncthreads();
+    }
+}
+
+__global__ __launch_bounds__(ACT_BLOCK) void k_active_queue(const Header *__restrict__ hdr,
+                                                            const uint8_t *__restrict__ gflag,
+                                                            const uint32_t *__restrict__ bcnt,
+                                                            uint32_t *__restrict__ order, uint32_t *__restrict__ qlen) {
+    __shared__ unsigned s_sum[2][ACT_BLOCK / 64];
+    if (hdr->flags & (FLAG_NONFINITE | FLAG_NEGMASS | FLAG_CELLCAP)) return;
+    const unsigned ng = hdr->ngroups, ln = lane64(), w = threadIdx.x >> 6;
+    const unsigned nblk = (ng + ACT_BLOCK - 1u) / ACT_BLOCK;
+    for (unsigned blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
+        unsigned before = 0, all = 0;  // visited groups of the blocks before, of all blocks
+        for (unsigned b = threadIdx.x; b < nblk; b += ACT_BLOCK) {
+            const unsigned v = bcnt[b];
+            all += v;
+            before += b < blk ? v : 0u;
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            before += __shfl_xor(before, o, 64);
+            all += __shfl_xor(all, o, 64);
+        }
+        if (ln == 0) {
+            s_sum[0][w] = before;
+            s_sum[1][w] = all;
+        }
+        __syncthreads();
+        before = all = 0;
+        for (unsigned v = 0; v < ACT_BLOCK / 64; v++) {
+            before += s_sum[0][v];
+            all += s_sum[1][v];
+        }
+        __syncthreads();
+        const unsigned g = blk * ACT_BLOCK + threadIdx.x;
+        const bool mine = g < ng && gflag[g] != 0;
+        const unsigned long long m = __ballot(mine);
+        if (ln == 0) s_sum[0][w] = (unsigned)__popcll(m);
+        __syncthreads();
+        unsigned vis = before + rank_below(m);  // visited groups before g
+        for (unsigned v = 0; v < w; v++) vis += s_sum[0][v];
+        if (g < ng) order[mine ? vis : all + (g - vis)] = g;
+        if (blk == 0 && threadIdx.x == 0) *qlen = all;
+        __syncthreads();
+    }
+}
+
+}  // namespace
+
+// --------------------------------------------------------------------------
 // Queue order: a stable counting sort of the groups by work bucket, heaviest
 // bucket first.  work = count * 2^prediction (estimator) or
 // count * (1 + n_pc + n_pp) (exact counts of the last walk); bucket =
@@ -1012,20 +1108,12 @@ struct OrderArgs {
     const uint2 *groups;
     const float *pred;       // mode 1
     const uint2 *counts;     // mode 2
-    const uint32_t *perm;    // mode 3: sorted position -> input index
-    const uint8_t *active;   // mode 3: per input particle, nonzero = active
     int mode;
 };
 
-// Queue bucket of group g: 0 for the heaviest work (modes 1, 2), or 0 for a
-// group holding an active particle and 1 otherwise (mode 3).
+// Queue bucket of group g: 0 for the heaviest work.
 __device__ __forceinline__ unsigned work_bucket(const OrderArgs &o, unsigned g) {
     const uint2 gr = o.groups[g];
-    if (o.mode == 3) {
-        bool any = false;
-        for (unsigned k = gr.x; k < gr.x + (gr.y & 255u); k++) any = any || o.active[o.perm[k]] != 0;
-        return any ? 0u : 1u;
-    }
     const float gn = (float)(gr.y & 255u);
     const float *pred = o.pred;
     const uint2 *counts = o.counts;
@@ -1063,10 +1151,7 @@ __global__ __launch_bounds__(ORDER_THREADS) void k_order_hist(OrderArgs o, uint3
 }
 
 // Exclusive prefix sum, in place, of ohist[ORDER_BUCKETS][ORDER_BLOCKS] read
-// as one row-major sequence.  It skips with the histogram and scatter kernels:
-// run on a table the histogram did not refill, it would scan the previous
-// prefix sums again, and the queue length it leaves (ohist[ORDER_BLOCKS] in the
-// active mode) would exceed the number of groups.
+// as one row-major sequence.  It skips with the histogram and scatter kernels.
 __global__ __launch_bounds__(ORDER_SCAN_THREADS) void k_order_scan(const Header *__restrict__ hdr,
                                                                    uint32_t *__restrict__ ohist) {
     constexpr int PER = ORDER_BUCKETS * ORDER_BLOCKS / ORDER_SCAN_THREADS;
@@ -1142,14 +1227,21 @@ __global__ __launch_bounds__(ORDER_THREADS) void k_order_scatter(OrderArgs o, co
 }  // namespace
 
 hipError_t launch_queue_order(const Buffers &b, int mode, const uint8_t *active, unsigned nsys, hipStream_t s) {
+    if (mode == ORDER_MODE_ACTIVE) {
+        // the number of visited groups goes where the counting sort would leave it
+        const unsigned grid = min((b.n_max + ACT_BLOCK - 1u) / ACT_BLOCK, 1024u);
+        hipLaunchKernelGGL(k_active_flag, dim3(grid), dim3(ACT_BLOCK), 0, s, b.hdr, b.groups, b.vals[0], active, b.gflag,
+                           b.acnt);
+        hipLaunchKernelGGL(k_active_queue, dim3(grid), dim3(ACT_BLOCK), 0, s, b.hdr, b.gflag, b.acnt, b.qorder,
+                           b.ohist + ORDER_BLOCKS);
+        return hipGetLastError();
+    }
     OrderArgs o;
     o.hdr = b.hdr;
     o.n_max = b.n_max;
     o.groups = b.groups;
     o.pred = b.pred;
     o.counts = b.gcounts;
-    o.perm = b.vals[0];
-    o.active = active;
     o.mode = mode;
     hipLaunchKernelGGL(k_order_hist, dim3(ORDER_BLOCKS), dim3(ORDER_THREADS), 0, s, o, b.ohist);
     hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(ORDER_SCAN_THREADS), 0, s, b.hdr, b.ohist);
