@@ -402,7 +402,8 @@ enum { MIBH_ORDER_MORTON = 0, MIBH_ORDER_ESTIMATOR = 1, MIBH_ORDER_EXACT = 2 };
 mibh_status mibh_group_features(mibh_ctx *ctx, float theta, float *d_feat);
 
 /* Order of the walk's group queue in compute_forces (the default is MORTON).
- * MORTON: the groups in Morton order.  ESTIMATOR and EXACT: longest
+ * MORTON: the groups in Morton order, in large trees with the end of each
+ * XCD's share by particle count (most first).  ESTIMATOR and EXACT: longest
  * processing time first, a stable counting sort by floor(4 log2 work),
  * heaviest bucket first and Morton order within a bucket, where work is
  * count * 2^y predicted with the float16 weights d_w16 (kept by pointer, read

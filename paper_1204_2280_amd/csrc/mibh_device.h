@@ -130,6 +130,55 @@ __device__ __forceinline__ unsigned queue_next(unsigned *heads, unsigned n, Queu
     return n;
 }
 
+// Order of the walk's queue in large trees: the last GORD_WINDOW slots of each
+// XCD's eighth by the groups' particle counts, largest first.  Blocks of
+// GORD_BLOCK slots count their groups by (eighth, count); a block meets two
+// eighths at most when there are GORD_MIN slots or more (shorter queues keep
+// Morton order).  A walk ends when its last group does, and a group of 64
+// particles takes about four times as long as one of 16: with the small groups
+// last, the waves end together.  Only the end of a queue matters for that, and
+// the order costs L2 hits (neighbouring groups read the same cells): walks with
+// windows of 2048 / 4096 / 8192 / 16384 / all slots take, in us, 1430 / 1395 /
+// 1418 / 1415 / 1440 at 2^20 Plummer particles, 2800 / 2680 / 2750 / 2780 / - at
+// 2^21 and 5515 / 5470 / 5430 / 5565 / 5850 at 2^22 (Morton order: 1540 at 2^20,
+// 5635 at 2^22).
+constexpr unsigned GORD_BLOCK = 512;
+constexpr unsigned GORD_CLASSES = 64;
+constexpr unsigned GORD_MIN = WALK_QUEUES * GORD_BLOCK;
+constexpr unsigned GORD_WINDOW = 4096;
+__device__ __forceinline__ unsigned gord_begin(unsigned n, unsigned q) {  // first slot of queue q of n slots
+    return (unsigned)((unsigned long long)n * q / WALK_QUEUES);
+}
+__device__ __forceinline__ unsigned gord_eighth(unsigned n, unsigned i) {  // the queue that holds slot i
+    const unsigned q = (unsigned)((unsigned long long)WALK_QUEUES * i / n);
+    return q + (gord_begin(n, q + 1u) <= i ? 1u : 0u);
+}
+__device__ __forceinline__ unsigned gord_window(unsigned n, unsigned q) {  // first slot of queue q's window
+    const unsigned lo = gord_begin(n, q), hi = gord_begin(n, q + 1u);
+    return hi - lo > GORD_WINDOW ? hi - GORD_WINDOW : lo;
+}
+__device__ __forceinline__ unsigned gord_class(uint2 group) { return (GORD_CLASSES - (group.y & 255u)) % GORD_CLASSES; }
+
+// Counts of the groups in the queue's windows; `order` NULL: Morton order.  Called
+// by whole workgroups of 256.
+__device__ __forceinline__ void gord_count(const uint2 *groups, const uint32_t *order, unsigned n, uint32_t *ghist) {
+    __shared__ unsigned s_h[2 * GORD_CLASSES];
+    if (n < GORD_MIN) return;
+    for (unsigned b = blockIdx.x; b * GORD_BLOCK < n; b += gridDim.x) {
+        if (threadIdx.x < 2 * GORD_CLASSES) s_h[threadIdx.x] = 0;
+        __syncthreads();
+        const unsigned i0 = b * GORD_BLOCK, e0 = gord_eighth(n, i0);
+        for (unsigned i = i0 + threadIdx.x; i < min(i0 + GORD_BLOCK, n); i += 256u) {
+            const unsigned e = gord_eighth(n, i);
+            if (i >= gord_window(n, e))
+                atomicAdd(&s_h[(e - e0) * GORD_CLASSES + gord_class(groups[order ? order[i] : i])], 1u);
+        }
+        __syncthreads();
+        if (threadIdx.x < 2 * GORD_CLASSES) ghist[(size_t)b * 2 * GORD_CLASSES + threadIdx.x] = s_h[threadIdx.x];
+        __syncthreads();
+    }
+}
+
 // Walk queue order by predicted or measured work: quarter-octave buckets of
 // log2(work), heaviest first, Morton order within a bucket.
 constexpr int ORDER_BUCKETS = 128;
@@ -196,6 +245,9 @@ struct Buffers {
     uint32_t *gref;         // block time steps: work of a group at its first walk after a build (0: none)
     unsigned long long *bsum;  // block time steps: [0] work now, [1] reference work, [2] due particles
     uint32_t *qorder;       // walk queue: groups in processing order (work-ordered modes)
+    uint32_t *ghist;        // [blocks of GORD_BLOCK groups][2][GORD_CLASSES] groups by eighth and count
+    uint32_t *gahist;       // the same for an active walk's queue
+    uint32_t *gorder;       // queue of large trees
     uint8_t *gflag;         // active walks: group holds an active particle
     uint32_t *acnt;         // active walks: such groups per 512
     uint32_t *anchor;       // shared-prefix walk: anchor cell of each group
@@ -353,6 +405,8 @@ hipError_t launch_build(const Buffers &b, unsigned n, unsigned nsys, int ncrit, 
 hipError_t launch_multipoles(const Buffers &b, unsigned n, unsigned nsys, hipStream_t s);
 // theta: the float32 opening angle widened to float64
 hipError_t launch_mac_prep(const Buffers &b, unsigned nsys, double theta, hipStream_t s);
+// whether the walk of a tree of n particles takes the end of its queue by size
+bool walk_sorts_groups(unsigned n);
 // order: the queue (NULL: groups in Morton order); qlen: device count of queue
 // entries to walk (NULL: every group)
 // anchor_up > 0: groups share the traversal of their ancestor anchor_up levels up

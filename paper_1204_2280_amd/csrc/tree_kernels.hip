@@ -710,10 +710,13 @@ __global__ __launch_bounds__(BUILD_THREADS) void k_build_write(
     }
 }
 
-// Children of an internal cell are the consecutive next-level cells that start inside it.
-__global__ __launch_bounds__(256) void k_build_nchild(const Header *__restrict__ hdr,
-                                                      uint4 *__restrict__ topo, unsigned cap_cells) {
+// Children of an internal cell are the consecutive next-level cells that start
+// inside it.  The kernel also counts the groups for the order of the walk.
+__global__ __launch_bounds__(256) void k_build_nchild(const Header *__restrict__ hdr, const uint2 *__restrict__ groups,
+                                                      uint4 *__restrict__ topo, unsigned cap_cells,
+                                                      uint32_t *__restrict__ ghist) {
     if (hdr->flags & FLAG_CELLCAP) return;  // cell numbers beyond the capacity were never written
+    if (ghist) gord_count(groups, nullptr, hdr->ngroups, ghist);
     const unsigned nc = min(hdr->ncells, cap_cells);
     for (unsigned c = blockIdx.x * 256u + threadIdx.x; c < nc; c += gridDim.x * 256u) {
         const uint4 t = topo[c];
@@ -739,7 +742,8 @@ hipError_t launch_build(const Buffers &b, unsigned n, unsigned nsys, int ncrit, 
     hipLaunchKernelGGL(k_build_write, dim3(nblk), dim3(BUILD_THREADS), 0, s, b.lvinfo, keys, n, nsys, b.sys_off,
                        gcap, b.blkcnt, b.ctot, nblk, b.hdr, b.topo, b.groups, b.cap_cells);
     const unsigned grid = min((b.cap_cells + 255u) / 256u, 4096u);
-    hipLaunchKernelGGL(k_build_nchild, dim3(grid), dim3(256), 0, s, b.hdr, b.topo, b.cap_cells);
+    hipLaunchKernelGGL(k_build_nchild, dim3(grid), dim3(256), 0, s, b.hdr, b.groups, b.topo, b.cap_cells,
+                       walk_sorts_groups(n) ? b.ghist : nullptr);
     return hipGetLastError();
 }
 

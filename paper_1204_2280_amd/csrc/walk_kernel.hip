@@ -672,23 +672,110 @@ __global__ __launch_bounds__(64 * NW, 4) void k_walk(WalkArgs a) {
 // Anchor of every group: the cell at level max(level - up, 0) that holds the
 // group's first particle (cells of one level are numbered in particle order).
 // The anchor's record is cleared here; k_walk_claim then lists each anchor once.
-__global__ __launch_bounds__(256) void k_walk_anchor(const Header *__restrict__ hdr, const uint2 *__restrict__ groups,
-                                                     const uint4 *__restrict__ topo, int up,
-                                                     uint32_t *__restrict__ anchor, uint4 *__restrict__ arec) {
+// With `gorder` the kernel also places the queue's groups (every group, or the
+// first *qlen of `order`): each eighth's window by particle count, largest first,
+// in the old order within a count.  Every workgroup adds up the counts of its
+// eighths' window blocks; the ranks inside a block come from ballots, so the order
+// is the same on every run.
+__global__ __launch_bounds__(GORD_BLOCK) void k_walk_anchor(const Header *__restrict__ hdr,
+                                                            const uint2 *__restrict__ groups,
+                                                            const uint4 *__restrict__ topo, int up,
+                                                            uint32_t *__restrict__ anchor, uint4 *__restrict__ arec,
+                                                            const uint32_t *__restrict__ order,
+                                                            const uint32_t *__restrict__ qlen,
+                                                            const uint32_t *__restrict__ ghist,
+                                                            uint32_t *__restrict__ gorder) {
+    constexpr unsigned NW = GORD_BLOCK / 64, STRIPS = GORD_BLOCK / GORD_CLASSES;
+    static_assert(NW == STRIPS && GORD_CLASSES == 64, "one wave per strip of blocks");
+    __shared__ unsigned s_sum[2][2][STRIPS][GORD_CLASSES];  // [half][before this block, all]
+    __shared__ unsigned s_at[2][GORD_CLASSES];              // first slot of this block's groups
+    __shared__ unsigned s_cnt[NW][2 * GORD_CLASSES];
     if (hdr->flags & (FLAG_NONFINITE | FLAG_NEGMASS | FLAG_CELLCAP)) return;
     const unsigned ng = hdr->ngroups;
-    for (unsigned g = blockIdx.x * 256u + threadIdx.x; g < ng; g += gridDim.x * 256u) {
-        const uint2 gr = groups[g];
-        const int glev = (int)((gr.y >> 8) & 255u);
-        const int lev = glev > up ? glev - up : 0;
-        unsigned lo = hdr->lvl_begin[lev], hi = hdr->lvl_begin[lev + 1];  // topo[lo].x <= gr.x
-        while (hi - lo > 1) {
-            const unsigned mid = lo + (hi - lo) / 2;
-            if (topo[mid].x <= gr.x) lo = mid; else hi = mid;
+    const unsigned nq = qlen ? min(*qlen, ng) : ng;
+    const unsigned t = threadIdx.x, w = t >> 6, c = lane64();
+    for (unsigned blk = blockIdx.x; blk * GORD_BLOCK < ng; blk += gridDim.x) {
+        const unsigned i = blk * GORD_BLOCK + t;
+        if (i < ng) {
+            const uint2 gr = groups[i];
+            const int glev = (int)((gr.y >> 8) & 255u);
+            const int lev = glev > up ? glev - up : 0;
+            unsigned lo = hdr->lvl_begin[lev], hi = hdr->lvl_begin[lev + 1];  // topo[lo].x <= gr.x
+            while (hi - lo > 1) {
+                const unsigned mid = lo + (hi - lo) / 2;
+                if (topo[mid].x <= gr.x) lo = mid; else hi = mid;
+            }
+            anchor[i] = lo;
+            arec[lo] = make_uint4(0u, 0u, 0u, 0u);
         }
-        anchor[g] = lo;
-        arec[lo] = make_uint4(0u, 0u, 0u, 0u);
+        if (!gorder || blk * GORD_BLOCK >= nq) continue;  // the same for the whole workgroup
+        const unsigned g = i < nq ? (order ? order[i] : i) : 0u;
+        if (nq < GORD_MIN) {
+            if (i < nq) gorder[i] = g;
+            continue;
+        }
+        const unsigned e0 = gord_eighth(nq, blk * GORD_BLOCK);
+        const unsigned elast = gord_eighth(nq, min(blk * GORD_BLOCK + GORD_BLOCK, nq) - 1u);
+#pragma unroll
+        for (unsigned h = 0; h < 2; h++) {  // sums of class c over strip w of the blocks
+            unsigned before = 0, all = 0;
+            if (e0 + h <= elast) {
+                const unsigned lo = gord_begin(nq, e0 + h), hi = gord_begin(nq, e0 + h + 1u);
+                for (unsigned b = gord_window(nq, e0 + h) / GORD_BLOCK + w; b * GORD_BLOCK < hi; b += STRIPS) {
+                    // an eighth is a block's second one only in the block it starts in
+                    const unsigned half = b * GORD_BLOCK < lo ? 1u : 0u;
+                    const unsigned v = ghist[((size_t)b * 2 + half) * GORD_CLASSES + c];
+                    all += v;
+                    before += b < blk ? v : 0u;
+                }
+            }
+            s_sum[h][0][w][c] = before;
+            s_sum[h][1][w][c] = all;
+        }
+        (&s_cnt[0][0])[t] = 0;
+        (&s_cnt[0][0])[t + GORD_BLOCK] = 0;
+        __syncthreads();
+        if (w < 2u) {  // wave h: slots of eighth e0 + h by class
+            unsigned before = 0, all = 0;
+#pragma unroll
+            for (unsigned v = 0; v < STRIPS; v++) {
+                before += s_sum[w][0][v][c];
+                all += s_sum[w][1][v][c];
+            }
+            s_at[w][c] = gord_window(nq, min(e0 + w, WALK_QUEUES - 1u)) + (wave_incl_scan(all) - all) + before;
+        }
+        // rank among the wave's groups of the same eighth and class
+        const unsigned e = i < nq ? gord_eighth(nq, i) : 0u;
+        const bool ranked = i < nq && i >= gord_window(nq, e);
+        const unsigned d = ranked ? (e - e0) * GORD_CLASSES + gord_class(groups[g]) : 0u;
+        unsigned long long peers = __ballot(ranked);
+#pragma unroll
+        for (int bit = 0; bit < 7; bit++) {
+            const bool v = (d >> bit) & 1u;
+            const unsigned long long m = __ballot(v);
+            peers &= v ? m : ~m;
+        }
+        const unsigned rank = rank_below(peers);
+        if (ranked && rank == 0) s_cnt[w][d] = (unsigned)__popcll(peers);
+        __syncthreads();
+        if (i < nq) {
+            unsigned pos = i;
+            if (ranked) {
+                pos = s_at[d / GORD_CLASSES][d % GORD_CLASSES] + rank;
+                for (unsigned v = 0; v < w; v++) pos += s_cnt[v][d];
+            }
+            gorder[pos] = g;
+        }
+        __syncthreads();
     }
+}
+
+// Counts of an active walk's queue (a full walk's come with the tree).
+__global__ __launch_bounds__(256) void k_walk_count(const Header *__restrict__ hdr, const uint2 *__restrict__ groups,
+                                                    const uint32_t *__restrict__ order,
+                                                    const uint32_t *__restrict__ qlen, uint32_t *__restrict__ ghist) {
+    if (hdr->flags & (FLAG_NONFINITE | FLAG_NEGMASS | FLAG_CELLCAP)) return;
+    gord_count(groups, order, min(*qlen, hdr->ngroups), ghist);
 }
 
 // Anchor list: the anchors of the groups the walk visits (every group, or the
@@ -922,7 +1009,10 @@ __global__ __launch_bounds__(PREFIX_THREADS) void k_walk_prefix(WalkArgs a, unsi
 // time.  Walk stage with 1 / 2 / 4 waves per group (Plummer sphere, theta 0.75,
 // us): n = 1000 96 / 66 / 52, 20000 195 / 131 / 121, 32768 209 / 148 / 146,
 // 65536 260 / 217 / 229, 131072 390 / 370 / 415, 200000 480 / 481 / 555, 300007
-// 617 / 636 / 746, 2^20 1513 / 1731 / 2334.  The results are the same bits.
+// 617 / 636 / 746, 2^20 1513 / 1731 / 2334.  With the queue's end by size one
+// wave gains more than two: 277 / 266 at 100003, 277 / 310 at 131072 of a Plummer
+// sphere, but 505 / 432 at 100003 of a Hernquist sphere, whose heaviest groups
+// weigh more; the line stays.  The results are the same bits.
 int walk_group_waves(unsigned n) { return n <= 32768u ? 4 : n <= 160000u ? 2 : 1; }
 
 // As many workgroups as the launch parameter's waves have spill stacks.  Of 4096
@@ -941,6 +1031,14 @@ void launch_walk_waves(const WalkArgs &a, bool shared, int nw, unsigned waves, h
 }
 
 }  // namespace
+
+// Small trees give every group a workgroup at once: the order is the hardware's,
+// and one by size spreads each XCD's heavy groups over fewer CUs (the walk of a
+// 65536-particle Plummer sphere by work: 282 us against 217 in Morton order).  With
+// more groups than workgroups the walk gains from 80000 particles (230 us against
+// 270) over 300007 (485 against 630) to 2^20 (1395 against 1540); an active walk
+// of every tenth of 2^20 particles takes 364 us against 450.
+bool walk_sorts_groups(unsigned n) { return n > 65536u; }
 
 hipError_t launch_walk(const Buffers &b, unsigned n, unsigned nsys, float eps2, float G, int precision,
                        const uint32_t *order, const uint32_t *qlen, const uint8_t *active, float *acc, float *pot,
@@ -974,8 +1072,15 @@ hipError_t launch_walk(const Buffers &b, unsigned n, unsigned nsys, float eps2, 
     const bool shared = anchor_up > 0 && b.anchor;
     if (shared) {
         const unsigned grid = min((b.n_max + 255u) / 256u, 2048u);
-        hipLaunchKernelGGL(k_walk_anchor, dim3(grid), dim3(256), 0, s, b.hdr, b.groups, b.topo, anchor_up, b.anchor,
-                           b.arec);
+        // a queue in Morton order is put in order of size; the work-ordered ones are taken as they are
+        const unsigned ablk = min((n + GORD_BLOCK - 1u) / GORD_BLOCK, 1024u);
+        uint32_t *gorder = (!order || qlen) && walk_sorts_groups(n) ? b.gorder : nullptr;
+        uint32_t *ghist = qlen ? b.gahist : b.ghist;
+        if (gorder && qlen)
+            hipLaunchKernelGGL(k_walk_count, dim3(ablk), dim3(256), 0, s, b.hdr, b.groups, order, qlen, ghist);
+        hipLaunchKernelGGL(k_walk_anchor, dim3(ablk), dim3(GORD_BLOCK), 0, s, b.hdr, b.groups, b.topo, anchor_up, b.anchor,
+                           b.arec, order, qlen, ghist, gorder);
+        if (gorder) a.order = gorder;
         hipLaunchKernelGGL(k_walk_claim, dim3(grid), dim3(256), 0, s, b.hdr, b.anchor, order, qlen, b.arec, b.alist,
                            &b.hdr->anchor_count);
         hipLaunchKernelGGL(k_walk_prefix, dim3(min(b.walk_waves, 1024u)), dim3(PREFIX_THREADS), 0, s, a, b.hdr->prefix_head,
