@@ -75,42 +75,8 @@ constexpr int DEFAULT_WALK_WAVES = 4096;  // 16 per compute unit on 256 CUs
 
 size_t align_up(size_t x) { return (x + ALIGN - 1) & ~(ALIGN - 1); }
 
-// System offsets travel to the device as a kernel argument, so a captured
-// graph holds them by value and no host staging buffer is needed.
-struct SysOffsets {
-    unsigned nsys;
-    unsigned off[MAX_SYSTEMS + 1];
-};
-
-// The start of a build: system offsets, the first sort bucket of each system,
-// the header and the walk's padding entries.  The flags of the previous build
-// move into the sticky word, so that a driver running many steps still sees a
-// condition that one of its earlier builds met.
-__global__ void k_begin_build(SysOffsets o, uint32_t *__restrict__ sys_off, uint32_t *__restrict__ bkt_off,
-                              Header *__restrict__ hdr, float4 *__restrict__ cmac, float4 *__restrict__ ceval,
-                              float4 *__restrict__ spos, unsigned cap_cells, unsigned n_max) {
-    for (unsigned i = threadIdx.x; i <= o.nsys; i += blockDim.x) {
-        sys_off[i] = o.off[i];
-        unsigned nb = 0;
-        for (unsigned s = 0; s < i; s++) nb += sort_buckets(o.off[s + 1] - o.off[s]);
-        bkt_off[i] = nb;
-    }
-    if (threadIdx.x == 0) {
-        // the walk's padding cell and particle: massless, far away
-        cmac[cap_cells] = make_float4(WALK_FAR, WALK_FAR, WALK_FAR, 0.0f);
-        ceval[2 * (size_t)cap_cells] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        ceval[2 * (size_t)cap_cells + 1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        spos[n_max] = make_float4(WALK_FAR, WALK_FAR, WALK_FAR, 0.0f);
-        hdr->nsys = o.nsys;
-        hdr->sticky |= hdr->flags;
-        hdr->flags = 0;
-        hdr->n = o.off[o.nsys];
-        hdr->ncells = 0;
-        hdr->ngroups = 0;
-        for (int l = 0; l < 24; l++) hdr->lvl_begin[l] = 0;
-    }
-    if (threadIdx.x < WALK_QUEUES) hdr->walk_head[QUEUE_STRIDE * threadIdx.x] = 0;
-}
+// The start of a build where no later kernel's first workgroup takes it.
+__global__ __launch_bounds__(256) void k_begin_build(BuildStart st) { begin_build(st); }
 
 bool params_valid(const mibh_params &p) {
     return p.ncrit >= 1 && p.group_cap >= p.ncrit && p.group_cap <= 64 && p.eps2 >= 0.0f &&
@@ -363,31 +329,42 @@ mibh_status mibh_build_tree_batch(mibh_ctx *ctx, const float *d_pos, const float
         if (h_offsets[s + 1] <= h_offsets[s]) return fail(MIBH_EINVAL, "system %d is empty or offsets decrease", s);
     const int64_t n = h_offsets[nsys];
     if (n > ctx->n_max) return fail(MIBH_EINVAL, "n = %lld > n_max = %lld", (long long)n, (long long)ctx->n_max);
-    SysOffsets o;
-    o.nsys = (unsigned)nsys;
-    for (int s = 0; s <= nsys; s++) o.off[s] = (unsigned)h_offsets[s];
     const unsigned un = (unsigned)n, us = (unsigned)nsys;
+    const Buffers &b = ctx->b;
+    BuildStart start = {};
+    SysOffsets &o = start.o;
+    o.nsys = us;
+    for (int s = 0; s <= nsys; s++) o.off[s] = (unsigned)h_offsets[s];
+    start.sys_off = b.sys_off;
+    start.bkt_off = b.bkt_off;
+    start.hdr = b.hdr;
+    start.cmac = b.cmac;
+    start.ceval = b.ceval;
+    start.spos = b.spos;
+    start.cap_cells = b.cap_cells;
+    start.n_max = b.n_max;
+    start.bucket_mean = sort_bucket_mean(un);
     hipStream_t s = ctx->stream;
     if ((st = mark(ctx, -1))) return st;
-    const Buffers &b = ctx->b;
-    hipLaunchKernelGGL(k_begin_build, dim3(1), dim3(256), 0, s, o, b.sys_off, b.bkt_off, b.hdr, b.cmac, b.ceval, b.spos,
-                       b.cap_cells, b.n_max);
-    HIP_TRY(hipGetLastError(), "begin_build");
     // The bucket sort up to its 4096 buckets (5.59 million particles in one
     // system), whose splitters fill a workgroup's 64 KB of LDS; the radix sort
     // beyond.
     unsigned nb = 0, nb_max = 0;
     for (int k = 0; k < nsys; k++) {
-        const unsigned nk = sort_buckets(o.off[k + 1] - o.off[k]);
+        const unsigned nk = sort_buckets(o.off[k + 1] - o.off[k], start.bucket_mean);
         nb += nk;
         nb_max = std::max(nb_max, nk);
     }
     if (bucket_sort_fits(ctx->b, un, nb)) {
-        HIP_TRY(launch_bucket_partition(ctx->b, d_pos, d_mass, un, us, nb, nb_max, s), "partition");
+        if (nb == us && us > 1) {  // several systems of one bucket each: the sort's workgroups all need the start
+            hipLaunchKernelGGL(k_begin_build, dim3(1), dim3(256), 0, s, start);
+            HIP_TRY(hipGetLastError(), "begin_build");
+        }
+        HIP_TRY(launch_bucket_partition(b, start, d_pos, d_mass, un, us, nb, nb_max, s), "partition");
         if ((st = mark(ctx, MIBH_STAGE_SORT))) return st;
-        HIP_TRY(launch_bucket_sort(ctx->b, d_pos, d_mass, un, us, nb, s), "bucket sort");
+        HIP_TRY(launch_bucket_sort(b, us == 1 ? &start : nullptr, d_pos, d_mass, un, us, nb, s), "bucket sort");
     } else {
-        HIP_TRY(launch_bbox(ctx->b, d_pos, d_mass, us, s), "bbox");
+        HIP_TRY(launch_bbox(b, start, d_pos, d_mass, us, s), "bbox");
         HIP_TRY(launch_keys(ctx->b, d_pos, d_mass, un, us, s), "keys");
         HIP_TRY(launch_sort(ctx->b, un, us, s), "sort");
         if ((st = mark(ctx, MIBH_STAGE_SORT))) return st;

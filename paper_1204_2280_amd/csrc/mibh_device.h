@@ -210,6 +210,8 @@ static_assert(WALK_PC_LDS % 64 == 0 && WALK_PP_LDS % 64 == 0, "lists hold whole 
 constexpr float WALK_FAR = 1.0e18f;
 
 // Device pointers carved from the caller's workspace.
+struct BuildStart;
+
 struct Buffers {
     Header *hdr;
     SysCube *cube;          // [max_systems]
@@ -374,10 +376,11 @@ __device__ __forceinline__ int shared_digits(uint64_t a, uint64_t b) {
 
 // Host launchers (kernels live in the .hip files).
 // boxes of *nparts stretches of each system into b.bbox_part
-hipError_t launch_bbox_partial(const Buffers &b, const float *pos, const float *mass, unsigned nsys, unsigned *nparts,
-                               hipStream_t s);
+hipError_t launch_bbox_partial(const Buffers &b, const BuildStart &start, const float *pos, const float *mass,
+                               unsigned nsys, unsigned *nparts, hipStream_t s);
 // the same and the root cubes
-hipError_t launch_bbox(const Buffers &b, const float *pos, const float *mass, unsigned nsys, hipStream_t s);
+hipError_t launch_bbox(const Buffers &b, const BuildStart &start, const float *pos, const float *mass, unsigned nsys,
+                       hipStream_t s);
 hipError_t launch_keys(const Buffers &b, const float *pos, const float *mass, unsigned n, unsigned nsys,
                        hipStream_t s);
 hipError_t launch_sort(const Buffers &b, unsigned n, unsigned nsys, hipStream_t s);
@@ -386,20 +389,71 @@ hipError_t launch_sort(const Buffers &b, unsigned n, unsigned nsys, hipStream_t 
 inline int radix_first_buffer(unsigned nsys) { return nsys > 1 ? (SORT_PASSES + 1) & 1 : SORT_PASSES & 1; }
 // Bucket sort (sort_kernels.hip): buckets of a system of n particles.
 constexpr unsigned SORT_BUCKET = 4096;       // elements one workgroup sorts in LDS
-// elements of a bucket on average (sorting and moving at 2^22 before the sample
-// had several lists: 1024 421 us, 1365 398, 1700 391; at 100003 101 / 104 / 102)
-constexpr unsigned SORT_BUCKET_MEAN = 1365;
+// Elements of a bucket on average, for n in all systems.  Up to a chip's worth
+// of workgroups the largest bucket sets the time, and one of more than 2048 elements
+// takes two places per thread: sorting and moving with 512 / 768 / 1024 / 1365,
+// in us: 70 / 72 / 72 / 87 at 32768, 88 / 87 / 85 / 98 at 100003, 106 / 105 / 104 /
+// 107 at 300007, 155 / 149 / 131 / 141 at 2^20, 250 / 219 / 204 / 213 at 2^21.  At
+// 2^22 the chip is full and the sample per bucket, 4096 of 8 lists at most, thin:
+// 1024 330, 1365 312.
+__host__ __device__ inline unsigned sort_bucket_mean(unsigned n) { return n <= 1u << 21 ? 1024u : 1365u; }
 constexpr unsigned SORT_MAX_BUCKETS = 4096;  // splitters and counts of all buckets fit LDS
 // shared digits of a particle that the tree build takes from its keys
 constexpr int8_t CL_FROM_KEYS = 127;
-__host__ __device__ inline unsigned sort_buckets(unsigned n) {
-    return n <= SORT_BUCKET ? 1u : (n + SORT_BUCKET_MEAN - 1u) / SORT_BUCKET_MEAN;
+__host__ __device__ inline unsigned sort_buckets(unsigned n, unsigned mean) {
+    return n <= SORT_BUCKET ? 1u : (n + mean - 1u) / mean;
+}
+// System offsets travel to the device as a kernel argument, so a captured
+// graph holds them by value and no host staging buffer is needed.
+struct SysOffsets {
+    unsigned nsys;
+    unsigned off[MAX_SYSTEMS + 1];
+};
+// The start of a build: system offsets, the first sort bucket of each system,
+// the header and the walk's padding entries.  The flags of the previous build
+// move into the sticky word, so that a driver running many steps still sees a
+// condition that one of its earlier builds met.  One workgroup of the build's
+// first kernel does it, whose others need nothing of it (a launch of its own took
+// 4.7 us).
+struct BuildStart {
+    SysOffsets o;
+    uint32_t *sys_off, *bkt_off;
+    Header *hdr;
+    float4 *cmac, *ceval, *spos;
+    unsigned cap_cells, n_max, bucket_mean;
+};
+__device__ inline void begin_build(const BuildStart &st) {
+    const SysOffsets &o = st.o;
+    Header *hdr = st.hdr;
+    for (unsigned i = threadIdx.x; i <= o.nsys; i += blockDim.x) {
+        st.sys_off[i] = o.off[i];
+        unsigned nb = 0;
+        for (unsigned s = 0; s < i; s++) nb += sort_buckets(o.off[s + 1] - o.off[s], st.bucket_mean);
+        st.bkt_off[i] = nb;
+    }
+    if (threadIdx.x == 0) {
+        // the walk's padding cell and particle: massless, far away
+        st.cmac[st.cap_cells] = make_float4(WALK_FAR, WALK_FAR, WALK_FAR, 0.0f);
+        st.ceval[2 * (size_t)st.cap_cells] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        st.ceval[2 * (size_t)st.cap_cells + 1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        st.spos[st.n_max] = make_float4(WALK_FAR, WALK_FAR, WALK_FAR, 0.0f);
+        hdr->nsys = o.nsys;
+        hdr->sticky |= hdr->flags;
+        hdr->flags = 0;
+        hdr->n = o.off[o.nsys];
+        hdr->ncells = 0;
+        hdr->ngroups = 0;
+        for (int l = 0; l < 24; l++) hdr->lvl_begin[l] = 0;
+    }
+    if (threadIdx.x < WALK_QUEUES) hdr->walk_head[QUEUE_STRIDE * threadIdx.x] = 0;
 }
 bool bucket_sort_fits(const Buffers &b, unsigned n, unsigned nb);
-hipError_t launch_bucket_partition(const Buffers &b, const float *pos, const float *mass, unsigned n, unsigned nsys,
-                                   unsigned nb, unsigned nb_max, hipStream_t s);
-hipError_t launch_bucket_sort(const Buffers &b, const float *pos, const float *mass, unsigned n, unsigned nsys,
-                              unsigned nb, hipStream_t s);
+// The build's start is part of the partition, or, where every system is one
+// bucket, of the sort if `start` is given (one system: no other workgroup).
+hipError_t launch_bucket_partition(const Buffers &b, const BuildStart &start, const float *pos, const float *mass,
+                                   unsigned n, unsigned nsys, unsigned nb, unsigned nb_max, hipStream_t s);
+hipError_t launch_bucket_sort(const Buffers &b, const BuildStart *start, const float *pos, const float *mass,
+                              unsigned n, unsigned nsys, unsigned nb, hipStream_t s);
 hipError_t launch_reorder(const Buffers &b, unsigned n, unsigned nsys, hipStream_t s);
 hipError_t launch_build(const Buffers &b, unsigned n, unsigned nsys, int ncrit, int gcap, hipStream_t s);
 hipError_t launch_multipoles(const Buffers &b, unsigned n, unsigned nsys, hipStream_t s);

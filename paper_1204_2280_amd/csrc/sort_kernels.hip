@@ -21,7 +21,7 @@
 //
 // The radix sort reads and writes every key eight times in 24 launches, then
 // gathers the records.  Sorting and moving, bounding cube to records in order:
-// 28 / 71 / 97 / 141 / 296 us at n = 1000 / 20000 / 100003 / 2^20 / 2^22 against
+// 27 / 65 / 79 / 125 / 297 us at n = 1000 / 20000 / 100003 / 2^20 / 2^22 against
 // 124 / 161 / 169 / 216 / 488 us.  Small inputs are bound by the launches and
 // the sort's chain of merges; at 2^22 the sort of the buckets takes 120 us (57
 // bytes a particle, 0.4 of the copy rate; LDS latency of the merges), the
@@ -229,7 +229,7 @@ struct Sample {
     unsigned m, lists, len;
     uint64_t step;  // sample g: one particle of each of m stretches of the input, n / m long in 32-bit fixed point
     __device__ Sample(unsigned n, unsigned nb) {
-        m = min(SAMPLE_PER_BUCKET * nb, SAMPLE_LISTS * SAMPLE_LIST);  // less than n: nb is n / SORT_BUCKET_MEAN
+        m = min(SAMPLE_PER_BUCKET * nb, SAMPLE_LISTS * SAMPLE_LIST);  // less than n: a bucket holds 1024 on average
         lists = (m + SAMPLE_LIST - 1u) / SAMPLE_LIST;
         len = (m / lists) & ~(ITEMS - 1u);
         m = len * lists;
@@ -407,13 +407,20 @@ __global__ __launch_bounds__(1024) void k_bucket_count(const float *__restrict__
         s_idx[b] = spl_idx[b];
         s_cnt[b] = 0;
     }
-    __syncthreads();
     const unsigned base = blockIdx.x * nt * TILE_ITEMS;
+    float3 p[TILE_ITEMS];  // all of the thread's particles on their way at once
+#pragma unroll
+    for (unsigned u = 0; u < TILE_ITEMS; u++) {
+        const size_t i = 3 * (size_t)min(base + u * nt + t, n - 1u);
+        p[u] = make_float3(pos[i], pos[i + 1], pos[i + 2]);
+    }
+    __syncthreads();
+#pragma unroll
     for (unsigned u = 0; u < TILE_ITEMS; u++) {
         const unsigned i = base + u * nt + t;
         if (i < n) {
             const unsigned s = nsys > 1 ? system_of(sys_off, nsys, i) : 0u;
-            const uint64_t k = morton_key(cube[s], pos[3 * (size_t)i], pos[3 * (size_t)i + 1], pos[3 * (size_t)i + 2]);
+            const uint64_t k = morton_key(cube[s], p[u].x, p[u].y, p[u].z);
             // the last bucket of the system whose splitter is not after (k, i)
             unsigned lo = bkt_off[s], hi = bkt_off[s + 1];
             while (hi - lo > 1) {
@@ -709,14 +716,19 @@ __device__ __forceinline__ void sort_all_bits(const BucketArgs &a, unsigned q0, 
 // point) is sorted again by all bits of index and key, least significant digit
 // first, with the same sort, which a word's rank of the digit before makes
 // stable.
-template <bool DIRECT>
-__global__ __launch_bounds__(BS_THREADS, BS_WAVES) void k_bucket_sort(BucketArgs a) {
+// BEGIN: the one workgroup of a one-bucket build also starts it.
+template <bool DIRECT, bool BEGIN>
+__global__ __launch_bounds__(BS_THREADS, BS_WAVES) void k_bucket_sort(BucketArgs a, BuildStart st) {
     __shared__ uint64_t sv[phys_size(SORT_BUCKET)];
     __shared__ uint64_t s_mm[2 * BS_THREADS / 64];
     __shared__ float s_box[BS_THREADS / 64][8];
     __shared__ unsigned s_long;
     const unsigned t = threadIdx.x, b = blockIdx.x;
-    const unsigned b0 = a.start[b], cnt = a.start[b + 1] - b0;
+    if (BEGIN) {
+        begin_build(st);
+        __syncthreads();
+    }
+    const unsigned b0 = BEGIN ? 0u : a.start[b], cnt = BEGIN ? st.o.off[1] : a.start[b + 1] - b0;
     if (cnt == 0) return;
     const unsigned sys = DIRECT ? b : a.nsys > 1 ? system_of(a.sys_off, a.nsys, b0) : 0u;
     const bool first = DIRECT || b0 == a.sys_off[sys];
@@ -835,14 +847,14 @@ bool bucket_sort_fits(const Buffers &b, unsigned n, unsigned nb) {
 
 // Root cubes and the partition into nb buckets (nothing to do where every system
 // is one: its sort finds the cube).  nb_max: buckets of the largest system.
-hipError_t launch_bucket_partition(const Buffers &b, const float *pos, const float *mass, unsigned n, unsigned nsys,
-                                   unsigned nb, unsigned nb_max, hipStream_t s) {
+hipError_t launch_bucket_partition(const Buffers &b, const BuildStart &start, const float *pos, const float *mass,
+                                   unsigned n, unsigned nsys, unsigned nb, unsigned nb_max, hipStream_t s) {
     if (nb == nsys) return hipSuccess;
     BucketScratch sc;
     bucket_scratch(n, nb, (char *)b.mp, &sc);
     const unsigned tile = bucket_tile(n), nt = tile / TILE_ITEMS, ntiles = (n + tile - 1) / tile;
     unsigned nparts;
-    hipError_t e = launch_bbox_partial(b, pos, mass, nsys, &nparts, s);
+    hipError_t e = launch_bbox_partial(b, start, pos, mass, nsys, &nparts, s);
     if (e != hipSuccess) return e;
     const unsigned lists = min((SAMPLE_PER_BUCKET * nb_max + SAMPLE_LIST - 1u) / SAMPLE_LIST, SAMPLE_LISTS);
     hipLaunchKernelGGL(k_bucket_sample, dim3(lists, nsys), dim3(SAMPLE_THREADS), 0, s, pos, b.sys_off, b.bkt_off,
@@ -861,8 +873,8 @@ hipError_t launch_bucket_partition(const Buffers &b, const float *pos, const flo
 }
 
 // Sorts the buckets into keys[0], vals[0], spos and cl.
-hipError_t launch_bucket_sort(const Buffers &b, const float *pos, const float *mass, unsigned n, unsigned nsys,
-                              unsigned nb, hipStream_t s) {
+hipError_t launch_bucket_sort(const Buffers &b, const BuildStart *start, const float *pos, const float *mass,
+                              unsigned n, unsigned nsys, unsigned nb, hipStream_t s) {
     BucketScratch sc;
     bucket_scratch(n, nb, (char *)b.mp, &sc);
     BucketArgs a;
@@ -884,8 +896,12 @@ hipError_t launch_bucket_sort(const Buffers &b, const float *pos, const float *m
     a.tkey = sc.tkey;
     a.tidx = sc.tidx;
     a.ttag = sc.ttag;
-    if (direct) hipLaunchKernelGGL(k_bucket_sort<true>, dim3(nb), dim3(BS_THREADS), 0, s, a);
-    else hipLaunchKernelGGL(k_bucket_sort<false>, dim3(nb), dim3(BS_THREADS), 0, s, a);
+    const bool begin = direct && start;
+    BuildStart st = {};
+    if (begin) st = *start;
+    if (begin) hipLaunchKernelGGL((k_bucket_sort<true, true>), dim3(1), dim3(BS_THREADS), 0, s, a, st);
+    else if (direct) hipLaunchKernelGGL((k_bucket_sort<true, false>), dim3(nb), dim3(BS_THREADS), 0, s, a, st);
+    else hipLaunchKernelGGL((k_bucket_sort<false, false>), dim3(nb), dim3(BS_THREADS), 0, s, a, st);
     return hipGetLastError();
 }
 

@@ -104,13 +104,12 @@ __device__ __forceinline__ unsigned run_end(const uint64_t *__restrict__ keys, u
 // Bounding cube, one per system (grid row y = system)
 // --------------------------------------------------------------------------
 
-__global__ __launch_bounds__(256) void k_bbox_partial(const float *__restrict__ pos,
-                                                      const float *__restrict__ mass,
-                                                      const uint32_t *__restrict__ sys_off,
-                                                      float *__restrict__ part) {
+__global__ __launch_bounds__(256) void k_bbox_partial(BuildStart start, const float *__restrict__ pos,
+                                                      const float *__restrict__ mass, float *__restrict__ part) {
     __shared__ float s[4][8];
     const unsigned sys = blockIdx.y;
-    const unsigned b0 = sys_off[sys], b1 = sys_off[sys + 1];
+    const unsigned b0 = start.o.off[sys], b1 = start.o.off[sys + 1];
+    if (blockIdx.x == 0 && sys == 0) begin_build(start);
     BoxFlags b;
     for (unsigned i = b0 + blockIdx.x * 256u + threadIdx.x; i < b1; i += gridDim.x * 256u) {
         const size_t p = (size_t)i * 3;
@@ -134,17 +133,18 @@ __global__ __launch_bounds__(256) void k_bbox_final(const float *__restrict__ pa
     }
 }
 
-hipError_t launch_bbox_partial(const Buffers &b, const float *pos, const float *mass, unsigned nsys, unsigned *nparts,
-                               hipStream_t s) {
+hipError_t launch_bbox_partial(const Buffers &b, const BuildStart &start, const float *pos, const float *mass,
+                               unsigned nsys, unsigned *nparts, hipStream_t s) {
     const unsigned per = max((unsigned)BBOX_MIN_BLOCKS, (unsigned)BBOX_BLOCKS / nsys);
-    hipLaunchKernelGGL(k_bbox_partial, dim3(per, nsys), dim3(256), 0, s, pos, mass, b.sys_off, b.bbox_part);
+    hipLaunchKernelGGL(k_bbox_partial, dim3(per, nsys), dim3(256), 0, s, start, pos, mass, b.bbox_part);
     *nparts = per;
     return hipGetLastError();
 }
 
-hipError_t launch_bbox(const Buffers &b, const float *pos, const float *mass, unsigned nsys, hipStream_t s) {
+hipError_t launch_bbox(const Buffers &b, const BuildStart &start, const float *pos, const float *mass, unsigned nsys,
+                       hipStream_t s) {
     unsigned per;
-    hipError_t e = launch_bbox_partial(b, pos, mass, nsys, &per, s);
+    hipError_t e = launch_bbox_partial(b, start, pos, mass, nsys, &per, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_bbox_final, dim3(nsys), dim3(256), 0, s, b.bbox_part, per, b.hdr, b.cube);
     return hipGetLastError();
