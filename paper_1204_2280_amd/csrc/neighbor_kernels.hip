@@ -8,20 +8,22 @@
 //   * rho_i = sum over the neighbours within r_i = 2 h_i of m_j W(|d|, h_i),
 //     W the cubic spline of Monaghan & Lattanzio (1985).
 //
-// One wave64 per group, persistent waves on the walk's per-XCD group queues.  The
+// One wave64 per group, persistent waves on the walk's per-XCD group queues, and
+// eight for a group with many candidates or where groups are few.  The
 // traversal opens a cell when the gap between the group's bounding box and
 // the cell's particle box (both float32, from the multipole pass) is within
 // the group's largest radius, with a relative margin of 1e-5 on the squared
 // radius: the float32 gap can differ from the exact one by a few ulps, and the
 // margin makes the test a superset of the pairs the exact predicate admits.
 // Opened leaves put their particles on a candidate list in LDS; tiles of 64
-// candidates (one per lane) are tested against the group's particles 8 at a
-// time (positions broadcast from their lanes into scalar registers: 16 at a
-// time needed more scalar registers than a wave holds).  Counts go to the
-// lane of their particle by a select (no lane-dependent branch inside a loop
-// that holds cross-lane operations); list entries are placed by ballot ranks;
-// densities are summed per lane, reduced across the wave by three transposed
-// stages and three butterflies, and moved to their particle's lane.
+// candidates (one per lane) are tested against the group's particles one after
+// the other, taken from LDS, or for densities broadcast from their lanes into
+// scalar registers, 8 at a time.  Counts go to the lane of their particle by a
+// select (no lane-dependent branch inside a loop that holds cross-lane
+// operations); list entries are placed by ballot ranks; densities are summed per
+// lane, reduced across the wave by three transposed stages and three
+// butterflies, moved to their particle's lane, and added up over the waves in
+// their order: every run gives the same bits.
 #include "mibh_device.h"
 
 namespace mibh {
@@ -29,8 +31,9 @@ namespace mibh {
 namespace {
 
 constexpr unsigned NGB_LSTACK = 512;   // LDS part of the cell stack (spills to the global stack)
-constexpr unsigned NGB_LIST = 512;     // candidate list
-constexpr int NGB_CHUNK = 8;          // group particles per pass over the list
+constexpr unsigned NGB_LIST = 1536;    // candidate list of a group's wave
+constexpr unsigned NGB_WAVES = 8;      // waves of a group with more candidates
+constexpr unsigned NGB_LIST_HEAVY = 4096;
 constexpr float NGB_FAR = 1.0e18f;
 // Candidates a group lists before its cells are tested against its particles
 // one by one.  The test costs a group's wave 14 instructions per particle and
@@ -135,6 +138,7 @@ struct NgbArgs {
     const float *radius;     // per input particle: radius (count, list) or h (density)
     float scale;             // search radius = scale * radius (2 for density)
     uint32_t *wstack;
+    uint32_t *heavy;         // groups left to the second pass (NULL: no first pass, every group)
     uint32_t *count;         // per input particle
     const uint32_t *offset;  // list: first slot of each input particle
     uint32_t *index;         // list: neighbour input indices
@@ -143,84 +147,169 @@ struct NgbArgs {
 
 enum { NGB_COUNT = 0, NGB_LISTS = 1, NGB_DENSITY = 2 };
 
-// Tests the candidates list[0..nlist) against the group's particles.
-template <int MODE>
-__device__ void ngb_eval(const NgbArgs &a, const uint32_t *list, unsigned nlist, unsigned gn, float px, float py,
-                         float pz, float pr2, float ph, unsigned &cnt, unsigned obase, unsigned ocap, float &rho) {
+// Candidate k of a list of n (a particle far away past the end), and its place.
+__device__ __forceinline__ float4 candidate(const NgbArgs &a, const uint32_t *list, unsigned n, unsigned k,
+                                            unsigned &e) {
+    e = list[min(k, n - 1u)];
+    const float4 s = a.spos[e];
+    return k < n ? s : make_float4(NGB_FAR, NGB_FAR, NGB_FAR, 0.0f);
+}
+
+// Counts or lists the neighbours among the candidates of every NW-th tile of
+// list[0..n), from tile w on; s_p: the group's gn particles and squared radii (-1
+// past the last).  Bound by the latency of a tile's loads: a tile is loaded once
+// for all of the group's particles, and while the one before it is tested.  With
+// the positions broadcast into scalar registers, 8 particles per pass over the
+// tiles, counts of 2^21 particles took 1080 us; they take 973.
+template <bool LISTS, int NW>
+__device__ void ngb_test(const NgbArgs &a, const uint32_t *list, unsigned n, unsigned w, unsigned gn,
+                         const float4 *s_p, unsigned &cnt, unsigned obase, unsigned ocap) {
+    constexpr unsigned STEP = 8;
     const unsigned ln = lane64();
-    for (unsigned c0 = 0; c0 < gn; c0 += NGB_CHUNK) {
-        const unsigned cn = min((unsigned)NGB_CHUNK, gn - c0);
-        float xi[NGB_CHUNK], yi[NGB_CHUNK], zi[NGB_CHUNK], r2i[NGB_CHUNK], ihi[NGB_CHUNK], sgi[NGB_CHUNK];
+    if (64 * w >= n) return;
+    unsigned enext, onext = 0;
+    float4 next = candidate(a, list, n, 64 * w + ln, enext);
+    if (LISTS) onext = a.perm[enext];
+#pragma unroll 1
+    for (unsigned t0 = 64 * w; t0 < n; t0 += 64 * NW) {
+        const float4 s = next;
+        const unsigned oj = onext;
+        if (t0 + 64 * NW < n) {
+            next = candidate(a, list, n, t0 + 64 * NW + ln, enext);
+            if (LISTS) onext = a.perm[enext];
+        }
+#pragma unroll 1
+        for (unsigned j0 = 0; j0 < gn; j0 += STEP) {
 #pragma unroll
-        for (int ii = 0; ii < NGB_CHUNK; ii++) {
+            for (unsigned u = 0; u < STEP; u++) {
+                const unsigned j = j0 + u;
+                const float4 q = s_p[j];
+                const bool in = dist2(q.x, q.y, q.z, s.x, s.y, s.z) <= q.w;
+                const unsigned long long m = __ballot(in);
+                if (LISTS) {
+                    const unsigned base = __builtin_amdgcn_readlane(obase + cnt, j);
+                    const unsigned cap = __builtin_amdgcn_readlane(ocap, j);
+                    const unsigned slot = base + rank_below(m);
+                    if (in && slot < cap) a.index[slot] = oj;
+                }
+                cnt += ln == j ? (unsigned)__popcll(m) : 0u;
+            }
+        }
+    }
+}
+
+// Counts and density sums of the same candidates, 8 particles per pass over the
+// tiles, their values in scalar registers (32 per pass, read from LDS, spilled 75
+// scalar registers and took 887 us against 809 at 2^20 particles).
+template <int NW>
+__device__ void ngb_density(const NgbArgs &a, const uint32_t *list, unsigned n, unsigned w, unsigned gn, float px,
+                            float py, float pz, float pr2, float ph, unsigned &cnt, float &rho) {
+    constexpr int K = 3, CHUNK = 1 << K;
+    const unsigned ln = lane64();
+    if (64 * w >= n) return;
+    for (unsigned c0 = 0; c0 < gn; c0 += CHUNK) {
+        const unsigned cn = min((unsigned)CHUNK, gn - c0);
+        float xi[CHUNK], yi[CHUNK], zi[CHUNK], r2i[CHUNK], ihi[CHUNK], sgi[CHUNK];
+#pragma unroll
+        for (int ii = 0; ii < CHUNK; ii++) {
             const unsigned src = c0 + min((unsigned)ii, cn - 1);
             xi[ii] = readlane_f(px, src);
             yi[ii] = readlane_f(py, src);
             zi[ii] = readlane_f(pz, src);
             // a padding particle (ii >= cn) admits nothing
             r2i[ii] = (unsigned)ii < cn ? readlane_f(pr2, src) : -1.0f;
-            if (MODE == NGB_DENSITY) {
-                const float h = readlane_f(ph, src);
-                ihi[ii] = 1.0f / h;
-                sgi[ii] = ihi[ii] * ihi[ii] * ihi[ii] * 0.318309886183790672f;  // 1 / (pi h^3)
-            }
+            const float h = readlane_f(ph, src);
+            ihi[ii] = 1.0f / h;
+            sgi[ii] = ihi[ii] * ihi[ii] * ihi[ii] * 0.318309886183790672f;  // 1 / (pi h^3)
         }
-        float acc[NGB_CHUNK];
+        float acc[CHUNK];
 #pragma unroll
-        for (int ii = 0; ii < NGB_CHUNK; ii++) acc[ii] = 0.0f;
-        for (unsigned t0 = 0; t0 < nlist; t0 += 64) {
-            const unsigned k = t0 + ln;
-            const bool valid = k < nlist;
-            const unsigned e = valid ? list[k] : 0u;
-            float4 s = a.spos[e];
-            if (!valid) s = make_float4(NGB_FAR, NGB_FAR, NGB_FAR, 0.0f);
-            const unsigned oj = MODE == NGB_LISTS ? a.perm[e] : 0u;
+        for (int ii = 0; ii < CHUNK; ii++) acc[ii] = 0.0f;
+        unsigned e;
+        float4 next = candidate(a, list, n, 64 * w + ln, e);
+        for (unsigned t0 = 64 * w; t0 < n; t0 += 64 * NW) {
+            const float4 s = next;
+            if (t0 + 64 * NW < n) next = candidate(a, list, n, t0 + 64 * NW + ln, e);
 #pragma unroll
-            for (int ii = 0; ii < NGB_CHUNK; ii++) {
+            for (int ii = 0; ii < CHUNK; ii++) {
                 const float d2 = dist2(xi[ii], yi[ii], zi[ii], s.x, s.y, s.z);
                 const bool in = d2 <= r2i[ii];
-                const unsigned long long m = __ballot(in);
-                const unsigned nin = (unsigned)__popcll(m);
-                if (MODE == NGB_LISTS) {
-                    const unsigned base = __builtin_amdgcn_readlane(obase + cnt, c0 + ii);
-                    const unsigned cap = __builtin_amdgcn_readlane(ocap, c0 + ii);
-                    const unsigned slot = base + rank_below(m);
-                    if (in && slot < cap) a.index[slot] = oj;
-                }
-                if (MODE == NGB_DENSITY) {
-                    const float r = d2 > 0.0f ? d2 * __builtin_amdgcn_rsqf(d2) : 0.0f;
-                    acc[ii] += in ? s.w * spline(r, ihi[ii], sgi[ii]) : 0.0f;
-                }
+                const unsigned nin = (unsigned)__popcll(__ballot(in));
+                const float r = d2 > 0.0f ? d2 * __builtin_amdgcn_rsqf(d2) : 0.0f;
+                acc[ii] += in ? s.w * spline(r, ihi[ii], sgi[ii]) : 0.0f;
                 cnt += ln == c0 + (unsigned)ii ? nin : 0u;
             }
         }
-        if (MODE == NGB_DENSITY) {
-            constexpr int K = NGB_CHUNK == 16 ? 4 : 3;
-            static_assert((1 << K) == NGB_CHUNK, "chunk of 8 or 16");
-            const float tot = reduce_pow2<K>(acc);
-            const unsigned p = ln - c0;
-            const float mine = __shfl(tot, (int)(bitrev_k<K>(p & (NGB_CHUNK - 1u)) << (6 - K)), 64);
-            rho += ln >= c0 && ln < c0 + cn ? mine : 0.0f;
-        }
+        const float tot = reduce_pow2<K>(acc);
+        const unsigned p = ln - c0;
+        const float mine = __shfl(tot, (int)(bitrev_k<K>(p & (CHUNK - 1u)) << (6 - K)), 64);
+        rho += ln >= c0 && ln < c0 + cn ? mine : 0.0f;
     }
 }
 
-template <int MODE>
-__global__ __launch_bounds__(64, 4) void k_neighbors(NgbArgs a) {
-    constexpr unsigned MASK = NGB_LSTACK - 1;
-    __shared__ uint32_t s_stk[NGB_LSTACK];
-    __shared__ uint32_t s_list[NGB_LIST];
-    __shared__ float4 s_p[64];  // the group's particles and squared radii (the last one repeated)
-    const unsigned ln = lane64();
+// Two passes over the groups (one of NW = NGB_WAVES in small trees: see
+// launch_passes).  The first (NW = 1) gives each group a wave and
+// leaves those with more than NGB_LIST candidates, of which it has then only
+// walked the tree, to the second, which gives each a workgroup of NGB_WAVES waves:
+// a cell per thread and step of the traversal, and the tiles of candidates dealt
+// to the waves.  In a sphere's outskirts a radius that reaches 64 neighbours may
+// reach the whole core: with one wave for every group the pass lasted as long as
+// that group, whatever n.
+template <int MODE, int NW>
+__global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
+    constexpr bool HEAVY = NW > 1;
+    constexpr unsigned NT = 64 * NW, STEP = HEAVY ? 256u : 64u;  // cells taken per step at most
+    constexpr unsigned RING = HEAVY ? 16u * STEP : NGB_LSTACK, MASK = RING - 1;
+    constexpr unsigned LIST = HEAVY ? NGB_LIST_HEAVY : NGB_LIST;
+    static_assert((RING & MASK) == 0 && RING >= 8 * STEP && STEP <= NT, "stack ring must hold one step's pushes");
+    // Steps of 64 cells leave at most 512 pushes per level on the stack.  Wider
+    // ones are taken from WIDE cells or fewer, so that they leave RING at most;
+    // with 20 levels of 512 above those the spill, which moves in half rings,
+    // stays within STACK_CAP.
+    constexpr unsigned WIDE = RING / 2;
+    static_assert(!HEAVY || (WIDE + 8 * STEP <= RING && KEY_LEVELS * 512u <= STACK_CAP / WIDE * WIDE), "stack bound");
+    __shared__ uint32_t s_stk[RING];
+    __shared__ uint32_t s_list[LIST];
+    __shared__ float4 s_p[64];  // the group's particles and squared radii (-1 past the last)
+    __shared__ unsigned s_cnt[2][NW][4];
+    __shared__ unsigned s_pcnt[HEAVY ? NW : 1][64];  // each wave's counts
+    __shared__ float s_rho[HEAVY ? NW : 1][64];
+    const unsigned ln = lane64(), t = NW > 1 ? threadIdx.x : ln, w = NW > 1 ? uniform(threadIdx.x >> 6) : 0u;
     uint32_t *gstk = a.wstack + (size_t)blockIdx.x * STACK_CAP;
     if (a.hdr->flags & (FLAG_NONFINITE | FLAG_NEGMASS | FLAG_CELLCAP)) return;
-    constexpr unsigned per_round = NGB_LIST >> 6;  // 8 particles per lane: a round always fits an empty list
-    const unsigned ngroups = uniform(a.hdr->ngroups);
+    constexpr unsigned per_round = 8;  // particles per thread: a round always fits an empty list
+    static_assert(per_round * STEP <= LIST, "a round fits");
+    const unsigned ngroups = uniform(HEAVY && a.heavy ? a.hdr->ngb_heavy : a.hdr->ngroups);
     QueueCursor qc = queue_start();
-    for (;;) {
+    unsigned par = 0;
+    // sums over the workgroup of each wave's v (the same in all its lanes), before this wave and in all
+    auto exchange = [&](const unsigned (&v)[4], unsigned (&before)[4], unsigned (&all)[4]) {
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            before[k] = 0;
+            all[k] = v[k];
+        }
+        if (NW == 1) return;
+        par ^= 1u;
+#pragma unroll
+        for (int k = 0; k < 4; k++) s_cnt[par][w][k] = v[k];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            all[k] = 0;
+#pragma unroll
+            for (unsigned u = 0; u < NW; u++) {
+                const unsigned x = uniform(s_cnt[par][u][k]);
+                before[k] += u < w ? x : 0u;
+                all[k] += x;
+            }
+        }
+    };
+    for (unsigned slot = blockIdx.x;; slot += gridDim.x) {
         // every lane takes part in the queue atomic (see the walk's queue loop)
-        const unsigned g = queue_next(a.head, ngroups, qc);
-        if (g >= ngroups) break;
+        if (!HEAVY) slot = queue_next(a.head, ngroups, qc);
+        if (slot >= ngroups) break;
+        const unsigned g = HEAVY && a.heavy ? uniform(a.heavy[slot]) : slot;
         const uint2 gr = a.groups[g];
         const unsigned gf = uniform(gr.x), gn = uniform(gr.y & 255u);
         const unsigned root = uniform(gr.y >> 16);
@@ -230,7 +319,8 @@ __global__ __launch_bounds__(64, 4) void k_neighbors(NgbArgs a) {
         const float hr = a.radius[oi];
         const float rr = a.scale * hr;
         const float pr2 = rr * rr;
-        s_p[ln] = make_float4(p.x, p.y, p.z, pr2);
+        // (every wave writes the same values)
+        s_p[ln] = make_float4(p.x, p.y, p.z, ln < gn ? pr2 : -1.0f);
         float bmin[3] = {p.x, p.y, p.z}, bmax[3] = {p.x, p.y, p.z};
         float rmax = rr;
 #pragma unroll
@@ -253,25 +343,48 @@ __global__ __launch_bounds__(64, 4) void k_neighbors(NgbArgs a) {
         const uint4 tr = a.topo[root];
         const unsigned rn = uniform(tr.w & 255u);
         unsigned sb = 0, st = rn ? rn : 1u, gtop = 0, nl = 0;
-        bool overflow = false;
+        bool overflow = false, later = false;
+        auto test_list = [&]() {
+            __syncthreads();
+            if (MODE == NGB_DENSITY) {
+                ngb_density<NW>(a, s_list, nl, w, gn, p.x, p.y, p.z, pr2, hr, cnt, rho);
+            } else if (HEAVY && MODE == NGB_LISTS) {  // the waves' counts first: where each one's entries go
+                unsigned own = 0;
+                ngb_test<false, NW>(a, s_list, nl, w, gn, s_p, own, 0u, 0u);
+                s_pcnt[w][ln] = own;
+                __syncthreads();
+                unsigned at = cnt;
+#pragma unroll
+                for (unsigned u = 0; u < NW; u++) {
+                    const unsigned x = s_pcnt[u][ln];
+                    at += u < w ? x : 0u;
+                    cnt += x;
+                }
+                ngb_test<true, NW>(a, s_list, nl, w, gn, s_p, at, obase, ocap);
+            } else {
+                ngb_test<MODE == NGB_LISTS, NW>(a, s_list, nl, w, gn, s_p, cnt, obase, ocap);
+            }
+            nl = 0;
+            __syncthreads();
+        };
         const unsigned first = rn ? tr.z + min(ln, rn - 1) : root;
         if (ln < st) s_stk[ln] = first;
         __syncthreads();
         while (st != sb || gtop > 0) {
             if (st == sb) {  // refill the LDS part of the stack from the global spill
-                const unsigned k = min(gtop, NGB_LSTACK / 2);
+                const unsigned k = min(gtop, RING / 2);
                 __threadfence_block();
-                for (unsigned i = ln; i < k; i += 64) s_stk[(sb - k + i) & MASK] = gstk[gtop - k + i];
+                for (unsigned i = t; i < k; i += NT) s_stk[(sb - k + i) & MASK] = gstk[gtop - k + i];
                 sb -= k;
                 gtop -= k;
                 __syncthreads();
             }
-            const unsigned m = min(st - sb, 64u);
-            const bool valid = ln < m;
-            const unsigned c = valid ? s_stk[(st - m + ln) & MASK] : 0u;
+            const unsigned m = min(st - sb, HEAVY && gtop + (st - sb) <= WIDE ? STEP : 64u);
+            const bool valid = t < m;
+            const unsigned c = valid ? s_stk[(st - m + t) & MASK] : 0u;
             st -= m;
-            const uint4 t = a.topo[c];
-            const unsigned nch = t.w & 255u;
+            const uint4 tc = a.topo[c];
+            const unsigned nch = tc.w & 255u;
             bool open = false;
             float bx[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};  // the cell's particle box: min xyz, max xyz
             if (valid) {
@@ -284,8 +397,8 @@ __global__ __launch_bounds__(64, 4) void k_neighbors(NgbArgs a) {
 #pragma unroll
                 for (int d = 0; d < 3; d++) {
                     const float u = bx[d] - bmax[d];
-                    const float w = bmin[d] - bx[3 + d];
-                    const float gp = fmaxf(fmaxf(u, w), 0.0f);
+                    const float v = bmin[d] - bx[3 + d];
+                    const float gp = fmaxf(fmaxf(u, v), 0.0f);
                     gap2 = gap2 + gp * gp;
                 }
                 open = gap2 <= open2;
@@ -308,75 +421,101 @@ __global__ __launch_bounds__(64, 4) void k_neighbors(NgbArgs a) {
                 }
                 open = open & hit;
             }
-            // opened leaves -> candidate list: whole leaves in one round when
-            // each holds fewer than 32 particles and they fit an empty list,
-            // else in rounds; the list is evaluated when a round does not fit
-            unsigned rem = open && nch == 0 ? t.y : 0u, src = t.x;
-            if (__ballot(rem > 0) && !__ballot(rem > 31u)) {
-                unsigned sum;
-                const unsigned off = small_scan<5>(rem, &sum);
-                if (sum <= NGB_LIST) {
-                    if (nl + sum > NGB_LIST) {
-                        __syncthreads();
-                        ngb_eval<MODE>(a, s_list, nl, gn, p.x, p.y, p.z, pr2, hr, cnt, obase, ocap, rho);
-                        nl = 0;
-                        __syncthreads();
-                    }
-                    for (unsigned j = 0; j < rem; j++) s_list[nl + off + j] = src + j;
-                    nl += sum;
-                    cand += sum;
-                    rem = 0;
-                }
-            }
-            while (__ballot(rem > 0)) {
-                const unsigned take = min(rem, per_round);
-                unsigned sum;
-                const unsigned off = small_scan(take, &sum);
-                if (nl + sum > NGB_LIST) {
-                    __syncthreads();
-                    ngb_eval<MODE>(a, s_list, nl, gn, p.x, p.y, p.z, pr2, hr, cnt, obase, ocap, rho);
-                    nl = 0;
-                    __syncthreads();
-                }
-                for (unsigned j = 0; j < take; j++) s_list[nl + off + j] = src + j;
-                nl += sum;
-                cand += sum;
-                rem -= take;
-                src += take;
-            }
-            // opened internal cells -> children onto the stack
-            unsigned nsum;
+            // opened leaves' particles go to the candidate list, opened internal
+            // cells' children onto the stack: places by one scan of each.  Leaves
+            // go whole where each holds fewer than 32 particles and they fit an
+            // empty list, else in rounds; the list is tested when they do not fit.
+            unsigned rem = open && nch == 0 ? tc.y : 0u, src = tc.x;
             const unsigned nc = open && nch != 0 ? nch : 0u;
-            const unsigned off = small_scan(nc, &nsum);
+            unsigned wsum[4], before[4], all[4];
+            const bool big = __ballot(rem > 31u) != 0;
+            unsigned loff = 0;
+            wsum[0] = 0;
+            if (!big && __ballot(rem > 0)) loff = small_scan<5>(rem, &wsum[0]);
+            const unsigned coff = small_scan(nc, &wsum[1]);
+            wsum[2] = big ? 1u : 0u;
+            wsum[3] = 0;
+            exchange(wsum, before, all);  // (the popped entries have been read by now)
+            const unsigned nsum = all[1];
+            if (all[2] == 0 && all[0] <= LIST) {
+                if (all[0]) {
+                    if (nl + all[0] > LIST) {
+                        if (!HEAVY) {
+                            later = true;
+                            break;
+                        }
+                        test_list();
+                    }
+                    for (unsigned j = 0; j < rem; j++) s_list[nl + before[0] + loff + j] = src + j;
+                    nl += all[0];
+                    cand += all[0];
+                }
+            } else {
+                for (;;) {
+                    unsigned rsum[4] = {0u, 0u, 0u, 0u}, rb[4], ra[4];
+                    const unsigned take = min(rem, per_round);
+                    const unsigned off = small_scan(take, &rsum[0]);
+                    exchange(rsum, rb, ra);
+                    if (ra[0] == 0) break;
+                    if (nl + ra[0] > LIST) {
+                        if (!HEAVY) {
+                            later = true;
+                            break;
+                        }
+                        test_list();
+                    }
+                    for (unsigned j = 0; j < take; j++) s_list[nl + rb[0] + off + j] = src + j;
+                    nl += ra[0];
+                    cand += ra[0];
+                    rem -= take;
+                    src += take;
+                }
+                if (later) break;
+            }
             const unsigned used = st - sb;
-            if (used + nsum > NGB_LSTACK) {  // spill the bottom of the LDS ring
-                const unsigned need = used + nsum - NGB_LSTACK;
-                const unsigned sp = min(used, max(need, NGB_LSTACK / 2));
+            if (used + nsum > RING) {  // spill the bottom of the LDS ring
+                const unsigned need = used + nsum - RING;
+                const unsigned sp = min(used, max(need, RING / 2));
                 if (gtop + sp > STACK_CAP) {
                     overflow = true;
                     break;
                 }
-                for (unsigned i = ln; i < sp; i += 64) gstk[gtop + i] = s_stk[(sb + i) & MASK];
+                for (unsigned i = t; i < sp; i += NT) gstk[gtop + i] = s_stk[(sb + i) & MASK];
                 sb += sp;
                 gtop += sp;
                 __syncthreads();
             }
-            for (unsigned j = 0; j < nc; j++) s_stk[(st + off + j) & MASK] = t.z + j;
+            for (unsigned j = 0; j < nc; j++) s_stk[(st + before[1] + coff + j) & MASK] = tc.z + j;
             st += nsum;
             __syncthreads();
         }
-        if (!overflow && nl > 0) {
-            __syncthreads();
-            ngb_eval<MODE>(a, s_list, nl, gn, p.x, p.y, p.z, pr2, hr, cnt, obase, ocap, rho);
-        }
-        if (overflow) {
-            atomicOr(&a.hdr->flags, FLAG_STACK);
+        if (later) {
+            // (every lane stores the same word: no lane-dependent branch in this loop)
+            a.heavy[uniform(atomicAdd(&a.hdr->ngb_heavy, ln == 0 ? 1u : 0u))] = g;
             continue;
         }
-        if (ln < gn) {
+        if (!overflow && nl > 0) test_list();
+        if (overflow) {
+            atomicOr(&a.hdr->flags, FLAG_STACK);
+        } else if (HEAVY) {
+            if (MODE != NGB_LISTS) {
+                s_pcnt[w][ln] = cnt;
+                s_rho[w][ln] = rho;
+                __syncthreads();
+                if (w == 0 && ln < gn) {
+                    for (unsigned u = 1; u < NW; u++) {
+                        cnt += s_pcnt[u][ln];
+                        rho += s_rho[u][ln];
+                    }
+                    a.count[oi] = cnt;
+                    if (MODE == NGB_DENSITY) a.rho[oi] = rho;
+                }
+            }
+        } else if (ln < gn) {
             if (MODE != NGB_LISTS) a.count[oi] = cnt;
             if (MODE == NGB_DENSITY) a.rho[oi] = rho;
         }
+        if (HEAVY) __syncthreads();  // the LDS arrays are free again
     }
 }
 
@@ -443,10 +582,24 @@ __global__ __launch_bounds__(SCAN_TILE) void k_scan_apply(const uint32_t *__rest
     if (i == n - 1) out[n] = run + v;
 }
 
+// With few groups each takes NGB_WAVES waves at once; with many their waves fill
+// the chip and only the heavy ones do.  Density passes of a Plummer sphere (64
+// neighbours within 2h) one way / the other, us: 1000 46 / 102, 5000 74 / 202,
+// 20000 203 / 354, 65536 815 / 991, 131072 486 / 313, 250007 871 / 300 (one wave for
+// every group: 125, 315, 1096, 5196, 564, 346).
+template <int MODE>
+void launch_passes(NgbArgs a, unsigned n, unsigned waves, hipStream_t s) {
+    const bool one = n <= 65536u;
+    if (one) a.heavy = nullptr;
+    else hipLaunchKernelGGL((k_neighbors<MODE, 1>), dim3(waves), dim3(64), 0, s, a);
+    hipLaunchKernelGGL((k_neighbors<MODE, NGB_WAVES>), dim3(one ? waves : min(waves, 512u)), dim3(64 * NGB_WAVES), 0, s,
+                       a);
+}
+
 }  // namespace
 
 hipError_t launch_neighbors(const Buffers &b, int mode, const float *radius, uint32_t *count, const uint32_t *offset,
-                            uint32_t *index, float *rho, unsigned nsys, hipStream_t s) {
+                            uint32_t *index, float *rho, unsigned n, unsigned nsys, hipStream_t s) {
     NgbArgs a;
     a.hdr = b.hdr;
     a.head = b.hdr->walk_head;
@@ -458,18 +611,17 @@ hipError_t launch_neighbors(const Buffers &b, int mode, const float *radius, uin
     a.radius = radius;
     a.scale = mode == NGB_DENSITY ? 2.0f : 1.0f;
     a.wstack = b.wstack;
+    a.heavy = b.gorder;  // at most n groups; a walk writes it before it reads it
     a.count = count;
     a.offset = offset;
     a.index = index;
     a.rho = rho;
-    hipError_t e = launch_fill_u32(b.hdr->walk_head, WALK_QUEUES * QUEUE_STRIDE, 0u, s);
+    static_assert(offsetof(Header, ngb_heavy) == offsetof(Header, walk_head) + sizeof(Header::walk_head), "one fill");
+    hipError_t e = launch_fill_u32(b.hdr->walk_head, WALK_QUEUES * QUEUE_STRIDE + 1, 0u, s);
     if (e != hipSuccess) return e;
-    if (mode == NGB_COUNT)
-        hipLaunchKernelGGL(k_neighbors<NGB_COUNT>, dim3(b.walk_waves), dim3(64), 0, s, a);
-    else if (mode == NGB_LISTS)
-        hipLaunchKernelGGL(k_neighbors<NGB_LISTS>, dim3(b.walk_waves), dim3(64), 0, s, a);
-    else
-        hipLaunchKernelGGL(k_neighbors<NGB_DENSITY>, dim3(b.walk_waves), dim3(64), 0, s, a);
+    if (mode == NGB_COUNT) launch_passes<NGB_COUNT>(a, n, b.walk_waves, s);
+    else if (mode == NGB_LISTS) launch_passes<NGB_LISTS>(a, n, b.walk_waves, s);
+    else launch_passes<NGB_DENSITY>(a, n, b.walk_waves, s);
     return hipGetLastError();
 }
 

@@ -1,0 +1,64 @@
+"""Neighbour search with every group on eight waves (trees of up to 65536
+particles) against the two passes of larger trees (a wave per group, eight for
+the heavy ones): the same systems alone and inside a batch.  Counts and lists are
+compared exactly, densities within 1e-5 (float32 sums of positive terms in two
+orders: each rounds by at most 6e-8 times log2(n) + n / 64 partial sums).  The
+systems have groups with few candidates, with several full lists of them, with
+leaves of many particles at one point, and radii that reach nothing or all.
+"""
+import numpy as np
+import pytest
+
+from gpu_helpers import gpu_context
+from paper_1204_2280_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _system(k, n):
+    rng = np.random.default_rng(70 + k)
+    if k % 3 == 0:  # outskirts whose radii reach the core
+        pos, _, _ = W.plummer(n, 70 + k, with_velocities=False)
+        r = 2.0 * W.plummer_smoothing_lengths(pos, 48)
+    elif k % 3 == 1:  # points of 100 particles each, some radii hold everything
+        pos = rng.random((n, 3)).astype(np.float32)
+        pos[: n // 2] = pos[: n // 2][np.arange(n // 2) // 100]
+        r = np.where(np.arange(n) % 997 == 0, 2.0, 0.02)
+    else:
+        pos = rng.random((n, 3)).astype(np.float32)
+        r = np.where(np.arange(n) % 7 == 0, 0.0, 0.05)
+    return pos, rng.random(n).astype(np.float32) / n, r.astype(np.float32)
+
+
+@pytest.mark.parametrize("params", [{}, {"walk_waves": 24}])
+def test_passes_agree(params):
+    import torch
+    sizes = [30000, 6000, 25000, 1, 70, 9000]
+    parts = [_system(k, n) for k, n in enumerate(sizes)]
+    pos, mass, r = (torch.from_numpy(np.concatenate([p[q] for p in parts])).cuda() for q in range(3))
+    h = torch.clamp(0.5 * r, min=1e-3)
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    assert off[-1] > 65536
+    ctx = gpu_context(int(off[-1]), max_systems=len(sizes), **params)
+    ctx.build_tree_batch(pos, mass, off)
+    ctx.compute_multipoles()
+    print(f"[gpu] neighbour passes: batch {params}", flush=True)
+    cnt, o, idx = (t.cpu().numpy() for t in ctx.neighbor_list(r))
+    rho, dcnt = ctx.sph_density(h)
+    rho2, _ = ctx.sph_density(h)
+    assert torch.equal(rho, rho2)
+    for k, n in enumerate(sizes):
+        print(f"[gpu] neighbour passes: system {k} n={n}", flush=True)
+        s = slice(off[k], off[k + 1])
+        one = gpu_context(n, **params)
+        one.build_tree(pos[s].contiguous(), mass[s].contiguous())
+        one.compute_multipoles()
+        c1, o1, i1 = (t.cpu().numpy() for t in one.neighbor_list(r[s].contiguous()))
+        np.testing.assert_array_equal(cnt[s], c1)
+        np.testing.assert_array_equal(o[s] - o[off[k]], o1[:-1])
+        own = np.repeat(np.arange(n), c1)
+        a = idx[o[off[k]]:o[off[k + 1]]] - off[k]
+        np.testing.assert_array_equal(a[np.lexsort((a, own))], i1[np.lexsort((i1, own))])
+        rho1, d1 = one.sph_density(h[s].contiguous())
+        assert torch.equal(dcnt[s], d1)
+        assert float(((rho[s] - rho1).abs() / rho1).max()) <= 1e-5
