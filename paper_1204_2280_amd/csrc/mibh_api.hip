@@ -652,7 +652,7 @@ static mibh_status neighbors_check(mibh_ctx *ctx, const void *radius, const void
 mibh_status mibh_neighbor_count(mibh_ctx *ctx, const float *d_radius, uint32_t *d_count) {
     mibh_status st = neighbors_check(ctx, d_radius, d_count);
     if (st) return st;
-    HIP_TRY(launch_neighbors(ctx->b, 0, d_radius, d_count, nullptr, nullptr, nullptr, (unsigned)ctx->n, (unsigned)ctx->nsys,
+    HIP_TRY(launch_neighbors(ctx->b, 0, d_radius, d_count, nullptr, nullptr, 0, nullptr, (unsigned)ctx->n, (unsigned)ctx->nsys,
                              ctx->stream),
             "neighbors");
     return MIBH_OK;
@@ -665,7 +665,7 @@ mibh_status mibh_neighbor_list(mibh_ctx *ctx, const float *d_radius, uint32_t *d
     if (!d_offset || !total || (capacity > 0 && !d_index)) return fail(MIBH_EINVAL, "null pointer");
     if ((int64_t)ctx->n > (int64_t)SCAN_MAX_TILES * 1024)
         return fail(MIBH_EINVAL, "too many particles for the offset scan");
-    HIP_TRY(launch_neighbors(ctx->b, 0, d_radius, d_count, nullptr, nullptr, nullptr, (unsigned)ctx->n, (unsigned)ctx->nsys,
+    HIP_TRY(launch_neighbors(ctx->b, 0, d_radius, d_count, nullptr, nullptr, 0, nullptr, (unsigned)ctx->n, (unsigned)ctx->nsys,
                              ctx->stream),
             "neighbors");
     HIP_TRY(launch_scan_u32(d_count, (unsigned)ctx->n, d_offset, ctx->b.ohist, ctx->stream), "scan");
@@ -676,8 +676,16 @@ mibh_status mibh_neighbor_list(mibh_ctx *ctx, const float *d_radius, uint32_t *d
     *total = (int64_t)*h_tot;
     if (*total > capacity)
         return fail(MIBH_EOVERFLOW, "%lld neighbours, capacity %lld", (long long)*total, (long long)capacity);
-    HIP_TRY(launch_neighbors(ctx->b, 1, d_radius, d_count, d_offset, d_index, nullptr, (unsigned)ctx->n, (unsigned)ctx->nsys,
-                             ctx->stream),
+    return mibh_neighbor_fill(ctx, d_radius, d_count, d_offset, d_index, capacity);
+}
+
+mibh_status mibh_neighbor_fill(mibh_ctx *ctx, const float *d_radius, const uint32_t *d_count,
+                               const uint32_t *d_offset, uint32_t *d_index, int64_t capacity) {
+    mibh_status st = neighbors_check(ctx, d_radius, d_count);
+    if (st) return st;
+    if (!d_offset || (capacity > 0 && !d_index)) return fail(MIBH_EINVAL, "null pointer");
+    HIP_TRY(launch_neighbors(ctx->b, 1, d_radius, const_cast<uint32_t *>(d_count), d_offset, d_index, capacity, nullptr,
+                             (unsigned)ctx->n, (unsigned)ctx->nsys, ctx->stream),
             "neighbors");
     return MIBH_OK;
 }
@@ -686,7 +694,8 @@ mibh_status mibh_sph_density(mibh_ctx *ctx, const float *d_h, float *d_rho, uint
     mibh_status st = neighbors_check(ctx, d_h, d_rho);
     if (st) return st;
     if (!d_count) return fail(MIBH_EINVAL, "null count pointer");
-    HIP_TRY(launch_neighbors(ctx->b, 2, d_h, d_count, nullptr, nullptr, d_rho, (unsigned)ctx->n, (unsigned)ctx->nsys, ctx->stream),
+    HIP_TRY(launch_neighbors(ctx->b, 2, d_h, d_count, nullptr, nullptr, 0, d_rho, (unsigned)ctx->n, (unsigned)ctx->nsys,
+                             ctx->stream),
             "density");
     return MIBH_OK;
 }

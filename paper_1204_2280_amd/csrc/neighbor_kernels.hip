@@ -142,6 +142,7 @@ struct NgbArgs {
     uint32_t *count;         // per input particle
     const uint32_t *offset;  // list: first slot of each input particle
     uint32_t *index;         // list: neighbour input indices
+    unsigned capacity;       // list: entries of index
     float *rho;              // density
 };
 
@@ -336,7 +337,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
         unsigned cnt = 0, cand = 0;  // cand: candidates listed so far
         float rho = 0.0f;
         const unsigned obase = MODE == NGB_LISTS ? a.offset[oi] : 0u;
-        const unsigned ocap = MODE == NGB_LISTS ? a.offset[oi] + a.count[oi] : 0u;
+        const unsigned ocap = MODE == NGB_LISTS ? min(a.offset[oi] + a.count[oi], a.capacity) : 0u;
 
         // The root holds every particle, so every search opens it: its
         // children (the root itself when it is a leaf) start the stack.
@@ -599,7 +600,7 @@ void launch_passes(NgbArgs a, unsigned n, unsigned waves, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_neighbors(const Buffers &b, int mode, const float *radius, uint32_t *count, const uint32_t *offset,
-                            uint32_t *index, float *rho, unsigned n, unsigned nsys, hipStream_t s) {
+                            uint32_t *index, int64_t capacity, float *rho, unsigned n, unsigned nsys, hipStream_t s) {
     NgbArgs a;
     a.hdr = b.hdr;
     a.head = b.hdr->walk_head;
@@ -615,6 +616,7 @@ hipError_t launch_neighbors(const Buffers &b, int mode, const float *radius, uin
     a.count = count;
     a.offset = offset;
     a.index = index;
+    a.capacity = capacity < 0 ? 0u : (unsigned)std::min<int64_t>(capacity, 0xffffffffll);
     a.rho = rho;
     static_assert(offsetof(Header, ngb_heavy) == offsetof(Header, walk_head) + sizeof(Header::walk_head), "one fill");
     hipError_t e = launch_fill_u32(b.hdr->walk_head, WALK_QUEUES * QUEUE_STRIDE + 1, 0u, s);

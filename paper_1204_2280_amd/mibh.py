@@ -116,8 +116,9 @@ def lib():
         L.mibh_block_run.restype = st
         L.mibh_neighbor_count.argtypes = [P, P, P]
         L.mibh_neighbor_list.argtypes = [P, P, P, P, P, i64, C.POINTER(i64)]
+        L.mibh_neighbor_fill.argtypes = [P, P, P, P, P, i64]
         L.mibh_sph_density.argtypes = [P, P, P, P]
-        for f in ("mibh_neighbor_count", "mibh_neighbor_list", "mibh_sph_density"):
+        for f in ("mibh_neighbor_count", "mibh_neighbor_list", "mibh_neighbor_fill", "mibh_sph_density"):
             getattr(L, f).restype = st
         L.mibh_leapfrog.restype = st
         L.mibh_group_features.argtypes = [P, C.c_float, P]
@@ -446,17 +447,18 @@ class Context:
         count = torch.empty((self.n,), dtype=torch.int32, device=self.device)
         offset = torch.empty((self.n + 1,), dtype=torch.int32, device=self.device)
         total = C.c_int64(0)
-        if capacity is None:
-            with torch.cuda.device(self.device):
-                st = lib().mibh_neighbor_list(self.handle, radius.data_ptr(), count.data_ptr(), offset.data_ptr(),
-                                              None, 0, C.byref(total))
-            if st not in (0, -5):
-                _check(st)
-            capacity = total.value
-        index = torch.empty((max(int(capacity), 1),), dtype=torch.int32, device=self.device)
+        ptrs = (radius.data_ptr(), count.data_ptr(), offset.data_ptr())
         with torch.cuda.device(self.device):
-            _check(lib().mibh_neighbor_list(self.handle, radius.data_ptr(), count.data_ptr(), offset.data_ptr(),
-                                            index.data_ptr(), int(capacity), C.byref(total)))
+            if capacity is None:
+                st = lib().mibh_neighbor_list(self.handle, *ptrs, None, 0, C.byref(total))
+                if st not in (0, -5):
+                    _check(st)
+            index = torch.empty((max(int(total.value if capacity is None else capacity), 1),), dtype=torch.int32,
+                                device=self.device)
+            if capacity is None:
+                _check(lib().mibh_neighbor_fill(self.handle, *ptrs, index.data_ptr(), total.value))
+            else:
+                _check(lib().mibh_neighbor_list(self.handle, *ptrs, index.data_ptr(), int(capacity), C.byref(total)))
         return count, offset, index[:total.value]
 
     def sph_density(self, h):

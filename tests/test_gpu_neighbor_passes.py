@@ -62,3 +62,24 @@ def test_passes_agree(params):
         rho1, d1 = one.sph_density(h[s].contiguous())
         assert torch.equal(dcnt[s], d1)
         assert float(((rho[s] - rho1).abs() / rho1).max()) <= 1e-5
+
+
+@pytest.mark.parametrize("n", [3000, 70000])
+def test_fill_with_earlier_counts(n):
+    import torch
+    from paper_1204_2280_amd import mibh
+    pos, mass, r = (torch.from_numpy(x).cuda() for x in _system(0, n))
+    ctx = gpu_context(n)
+    ctx.build_tree(pos, mass)
+    ctx.compute_multipoles()
+    cnt, off, idx = ctx.neighbor_list(r)
+    total = int(off[n])
+    cnt2, off2, idx2 = ctx.neighbor_list(r, capacity=total + 10)
+    assert torch.equal(cnt, cnt2) and torch.equal(off, off2) and torch.equal(idx, idx2)
+    short = torch.full((total,), -7, dtype=torch.int32, device="cuda")
+    st = mibh.lib().mibh_neighbor_fill(ctx.handle, r.data_ptr(), cnt.data_ptr(), off.data_ptr(), short.data_ptr(),
+                                       total - 5)
+    assert st == 0
+    ctx.sync()
+    assert torch.equal(short[:-5], idx[:-5]) and bool((short[-5:] == -7).all())
+    assert mibh.lib().mibh_neighbor_fill(ctx.handle, r.data_ptr(), cnt.data_ptr(), None, short.data_ptr(), 5) == -1
