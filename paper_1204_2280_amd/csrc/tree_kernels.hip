@@ -1156,7 +1156,8 @@ hipError_t launch_multipoles(const Buffers &b, unsigned n, unsigned nsys, hipStr
 // fl(1/theta)), squared in float64, rounded once to float32.
 __global__ __launch_bounds__(256) void k_mac_prep(Header *__restrict__ hdr, const double *__restrict__ lside,
                                                   const double *__restrict__ delta, double theta,
-                                                  float4 *__restrict__ cmac, unsigned cap_cells) {
+                                                  float4 *__restrict__ cmac, uint4 *__restrict__ arec,
+                                                  unsigned cap_cells) {
 #pragma clang fp contract(off)
     if (hdr->flags & FLAG_CELLCAP) return;
     const unsigned nc = min(hdr->ncells, cap_cells);
@@ -1172,6 +1173,7 @@ __global__ __launch_bounds__(256) void k_mac_prep(Header *__restrict__ hdr, cons
     for (unsigned c = blockIdx.x * 256u + threadIdx.x; c < nc; c += gridDim.x * 256u) {
         const double ro = lside[c] / theta + delta[c];
         cmac[c].w = (float)(ro * ro);
+        if (arec) arec[c] = make_uint4(0u, 0u, 0u, 0u);  // no anchor yet
     }
 }
 
@@ -1179,7 +1181,7 @@ hipError_t launch_mac_prep(const Buffers &b, unsigned nsys, double theta, hipStr
     (void)nsys;
     const unsigned grid = min((b.cap_cells + 255u) / 256u, 4096u);
     hipLaunchKernelGGL(k_mac_prep, dim3(grid), dim3(256), 0, s, b.hdr, b.lside, b.delta, theta, b.cmac,
-                       b.cap_cells);
+                       b.arec, b.cap_cells);
     return hipGetLastError();
 }
 

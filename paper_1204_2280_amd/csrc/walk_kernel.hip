@@ -669,11 +669,17 @@ __global__ __launch_bounds__(64 * NW, 4) void k_walk(WalkArgs a) {
 // a walk from the root, and summed in another order.
 // --------------------------------------------------------------------------
 
-// Anchor of every group: the cell at level max(level - up, 0) that holds the
-// group's first particle (cells of one level are numbered in particle order).
-// The anchor's record is cleared here; k_walk_claim then lists each anchor once.
-// With `gorder` the kernel also places the queue's groups (every group, or the
-// first *qlen of `order`): each eighth's window by particle count, largest first,
+// Anchor of every group the walk visits (every group, or the queue's first *qlen
+// entries): the cell at level max(level - up, 0) that holds the group's first
+// particle (cells of one level are numbered in particle order).  Each anchor is
+// listed once, by the group that claims it: a compare-and-swap of its record's
+// valid word from 0, where the MAC kernel left it, to 2.  Only entries whose anchor
+// differs from the previous entry's try: in Morton order an anchor's groups are
+// contiguous unless groups of deeper levels sit between them, so few entries
+// compete (a wave's first entry tries without a look at the entry before: a
+// claiming kernel of its own, which had that, took 4.5 us more).
+// With `gorder` the kernel also places the queue's groups: each eighth's window by
+// particle count, largest first,
 // in the old order within a count.  Every workgroup adds up the counts of its
 // eighths' window blocks; the ranks inside a block come from ballots, so the order
 // is the same on every run.
@@ -684,7 +690,9 @@ __global__ __launch_bounds__(GORD_BLOCK) void k_walk_anchor(const Header *__rest
                                                             const uint32_t *__restrict__ order,
                                                             const uint32_t *__restrict__ qlen,
                                                             const uint32_t *__restrict__ ghist,
-                                                            uint32_t *__restrict__ gorder) {
+                                                            uint32_t *__restrict__ gorder,
+                                                            uint32_t *__restrict__ alist,
+                                                            unsigned *__restrict__ acount) {
     constexpr unsigned NW = GORD_BLOCK / 64, STRIPS = GORD_BLOCK / GORD_CLASSES;
     static_assert(NW == STRIPS && GORD_CLASSES == 64, "one wave per strip of blocks");
     __shared__ unsigned s_sum[2][2][STRIPS][GORD_CLASSES];  // [half][before this block, all]
@@ -694,22 +702,23 @@ __global__ __launch_bounds__(GORD_BLOCK) void k_walk_anchor(const Header *__rest
     const unsigned ng = hdr->ngroups;
     const unsigned nq = qlen ? min(*qlen, ng) : ng;
     const unsigned t = threadIdx.x, w = t >> 6, c = lane64();
-    for (unsigned blk = blockIdx.x; blk * GORD_BLOCK < ng; blk += gridDim.x) {
+    for (unsigned blk = blockIdx.x; blk * GORD_BLOCK < nq; blk += gridDim.x) {
         const unsigned i = blk * GORD_BLOCK + t;
-        if (i < ng) {
-            const uint2 gr = groups[i];
-            const int glev = (int)((gr.y >> 8) & 255u);
-            const int lev = glev > up ? glev - up : 0;
-            unsigned lo = hdr->lvl_begin[lev], hi = hdr->lvl_begin[lev + 1];  // topo[lo].x <= gr.x
-            while (hi - lo > 1) {
-                const unsigned mid = lo + (hi - lo) / 2;
-                if (topo[mid].x <= gr.x) lo = mid; else hi = mid;
-            }
-            anchor[i] = lo;
-            arec[lo] = make_uint4(0u, 0u, 0u, 0u);
-        }
-        if (!gorder || blk * GORD_BLOCK >= nq) continue;  // the same for the whole workgroup
         const unsigned g = i < nq ? (order ? order[i] : i) : 0u;
+        const uint2 gr = i < nq ? groups[g] : make_uint2(0u, 0u);
+        const int glev = (int)((gr.y >> 8) & 255u);
+        const int lev = glev > up ? glev - up : 0;
+        unsigned lo = hdr->lvl_begin[lev], hi = hdr->lvl_begin[lev + 1];  // topo[lo].x <= gr.x
+        while (hi - lo > 1) {
+            const unsigned mid = lo + (hi - lo) / 2;
+            if (topo[mid].x <= gr.x) lo = mid; else hi = mid;
+        }
+        const unsigned prev = __shfl_up(lo, 1, 64);
+        if (i < nq) {
+            anchor[g] = lo;
+            if ((c == 0 || prev != lo) && atomicCAS(&arec[lo].w, 0u, 2u) == 0u) alist[atomicAdd(acount, 1u)] = lo;
+        }
+        if (!gorder) continue;  // the same for the whole launch
         if (nq < GORD_MIN) {
             if (i < nq) gorder[i] = g;
             continue;
@@ -747,7 +756,7 @@ __global__ __launch_bounds__(GORD_BLOCK) void k_walk_anchor(const Header *__rest
         // rank among the wave's groups of the same eighth and class
         const unsigned e = i < nq ? gord_eighth(nq, i) : 0u;
         const bool ranked = i < nq && i >= gord_window(nq, e);
-        const unsigned d = ranked ? (e - e0) * GORD_CLASSES + gord_class(groups[g]) : 0u;
+        const unsigned d = ranked ? (e - e0) * GORD_CLASSES + gord_class(gr) : 0u;
         unsigned long long peers = __ballot(ranked);
 #pragma unroll
         for (int bit = 0; bit < 7; bit++) {
@@ -776,26 +785,6 @@ __global__ __launch_bounds__(256) void k_walk_count(const Header *__restrict__ h
                                                     const uint32_t *__restrict__ qlen, uint32_t *__restrict__ ghist) {
     if (hdr->flags & (FLAG_NONFINITE | FLAG_NEGMASS | FLAG_CELLCAP)) return;
     gord_count(groups, order, min(*qlen, hdr->ngroups), ghist);
-}
-
-// Anchor list: the anchors of the groups the walk visits (every group, or the
-// queue's first *qlen entries), each once, appended by the one group that claims
-// it (a compare-and-swap of the record's valid word from 0 to 2).  Only entries
-// whose anchor differs from the previous entry's try: in Morton order an
-// anchor's groups are contiguous unless groups of deeper levels sit between
-// them, so few entries compete.
-__global__ __launch_bounds__(256) void k_walk_claim(const Header *__restrict__ hdr,
-                                                    const uint32_t *__restrict__ anchor, const uint32_t *order,
-                                                    const uint32_t *qlen, uint4 *__restrict__ arec,
-                                                    uint32_t *__restrict__ alist, unsigned *__restrict__ acount) {
-    if (hdr->flags & (FLAG_NONFINITE | FLAG_NEGMASS | FLAG_CELLCAP)) return;
-    const unsigned ng = hdr->ngroups;
-    const unsigned nq = qlen ? min(*qlen, ng) : ng;
-    for (unsigned i = blockIdx.x * 256u + threadIdx.x; i < nq; i += gridDim.x * 256u) {
-        const unsigned A = anchor[order ? order[i] : i];
-        const bool starts = i == 0 || anchor[order ? order[i - 1] : i - 1] != A;
-        if (starts && atomicCAS(&arec[A].w, 0u, 2u) == 0u) alist[atomicAdd(acount, 1u)] = A;
-    }
 }
 
 // F and S of anchor cell A into this workgroup's scratch (F at pf, S sorted by
@@ -1071,7 +1060,6 @@ hipError_t launch_walk(const Buffers &b, unsigned n, unsigned nsys, float eps2, 
     a.pool = b.pool;
     const bool shared = anchor_up > 0 && b.anchor;
     if (shared) {
-        const unsigned grid = min((b.n_max + 255u) / 256u, 2048u);
         // a queue in Morton order is put in order of size; the work-ordered ones are taken as they are
         const unsigned ablk = min((n + GORD_BLOCK - 1u) / GORD_BLOCK, 1024u);
         uint32_t *gorder = (!order || qlen) && walk_sorts_groups(n) ? b.gorder : nullptr;
@@ -1079,10 +1067,8 @@ hipError_t launch_walk(const Buffers &b, unsigned n, unsigned nsys, float eps2, 
         if (gorder && qlen)
             hipLaunchKernelGGL(k_walk_count, dim3(ablk), dim3(256), 0, s, b.hdr, b.groups, order, qlen, ghist);
         hipLaunchKernelGGL(k_walk_anchor, dim3(ablk), dim3(GORD_BLOCK), 0, s, b.hdr, b.groups, b.topo, anchor_up, b.anchor,
-                           b.arec, order, qlen, ghist, gorder);
+                           b.arec, order, qlen, ghist, gorder, b.alist, &b.hdr->anchor_count);
         if (gorder) a.order = gorder;
-        hipLaunchKernelGGL(k_walk_claim, dim3(grid), dim3(256), 0, s, b.hdr, b.anchor, order, qlen, b.arec, b.alist,
-                           &b.hdr->anchor_count);
         hipLaunchKernelGGL(k_walk_prefix, dim3(min(b.walk_waves, 1024u)), dim3(PREFIX_THREADS), 0, s, a, b.hdr->prefix_head,
                            &b.hdr->anchor_count, b.alist, &b.hdr->pool_head, b.arec, b.pool, b.pool_cap, b.pscr,
                            &b.hdr->anchor_fail);
