@@ -998,11 +998,12 @@ __global__ __launch_bounds__(PREFIX_THREADS) void k_walk_prefix(WalkArgs a, unsi
 // time.  Walk stage with 1 / 2 / 4 waves per group (Plummer sphere, theta 0.75,
 // us): n = 1000 96 / 66 / 52, 20000 195 / 131 / 121, 32768 209 / 148 / 146,
 // 65536 260 / 217 / 229, 131072 390 / 370 / 415, 200000 480 / 481 / 555, 300007
-// 617 / 636 / 746, 2^20 1513 / 1731 / 2334.  With the queue's end by size one
-// wave gains more than two: 277 / 266 at 100003, 277 / 310 at 131072 of a Plummer
-// sphere, but 505 / 432 at 100003 of a Hernquist sphere, whose heaviest groups
-// weigh more; the line stays.  The results are the same bits.
-int walk_group_waves(unsigned n) { return n <= 32768u ? 4 : n <= 160000u ? 2 : 1; }
+// 617 / 636 / 746, 2^20 1513 / 1731 / 2334.  The results are the same bits.  With
+// the queue's end by size one wave gains more than two, so the second line lies
+// between where these meet at theta 0.75 (115000) and 0.5 (128000): with one wave
+// and with two, us, 100003 278 / 483 and 265 / 446, 125000 278 / 548 and 298 / 522,
+// 140000 288 / 562 and 318 / 568, 160000 303 / 577 and 354 / 638.
+int walk_group_waves(unsigned n) { return n <= 32768u ? 4 : n <= 122880u ? 2 : 1; }
 
 // As many workgroups as the launch parameter's waves have spill stacks.  Of 4096
 // workgroups of 2 or 4 waves the chip holds a half or a quarter at once; the
