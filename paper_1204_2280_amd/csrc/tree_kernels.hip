@@ -922,8 +922,6 @@ __device__ __forceinline__ void internal_cell(const CellBuffers &a, const Octet 
         Sc[j] = m[4 + o.qb];
         bc[j] = a.cbox[6 * (size_t)k + o.qb];
     }
-    double centre;
-    cell_geometry(a, e.w, (e.z >> 8) & 255u, e.z >> 16, o.ax, &centre);
     // Lanes 0..2 hold their centre-of-mass axis in xa (ma = ax there); the other
     // lanes' own axes differ, so their sums are not used.
     double M = 0.0, cm = 0.0, S = 0.0;
@@ -936,7 +934,12 @@ __device__ __forceinline__ void internal_cell(const CellBuffers &a, const Octet 
         cm = in ? c1 : cm;
         box = o.q < 3u ? fminf(box, bc[j]) : fmaxf(box, bc[j]);
     }
-    const double own = M > 0.0 ? cm / M : centre;
+    double own = cm / M;
+    if (__ballot(!(M > 0.0))) {  // massless cells take their centre
+        double centre;
+        cell_geometry(a, e.w, (e.z >> 8) & 255u, e.z >> 16, o.ax, &centre);
+        own = M > 0.0 ? own : centre;
+    }
     const double com = oct_shfl(own, o.ax);
     const double ca = oct_shfl(own, o.ma), cb = oct_shfl(own, o.mb);
 #pragma unroll
@@ -980,13 +983,16 @@ __device__ __forceinline__ void derive_cell(const CellBuffers &a, const uint4 &e
 //   k_multipole_merge: one workgroup per MP_FAN chunks takes the listed cells
 //     that end within its range in the same way and lists the others; it is
 //     launched until one range covers everything.
-// What bounds it: the chain of levels, about 2 us each (children from the L2,
-// float64 sums and a division, the barrier's wait for the stores), so the
-// quantities that no parent needs are derived after the last level.  A leaf
-// pass and one launch per level (21 launches) took 57 / 68 / 77 / 103 / 203 us
-// at n = 1000 / 20000 / 100003 / 2^20 / 2^22; this takes 21 / 43 / 50 / 82 /
-// 173 us (chunks of 1024: 21 / 41 / 60 / 88 / 196; one workgroup for all listed
-// cells instead of MP_FAN-way merges: 567 us at 2^22).
+// What bounds it: the chain of levels, more than 1 us each (float64 sums and a
+// division, the barrier), so the quantities that no parent needs are derived
+// after the last level, and a cell's centre, which the moments need only of
+// massless cells, too.  A leaf pass and one launch per level (21 launches) took
+// 57 / 68 / 77 / 103 / 203 us at n = 1000 / 20000 / 100003 / 2^20 / 2^22; this
+// takes 20 / 41 / 46 / 74 / 162 us (with every cell's centre 21 / 43 / 50 / 81 /
+// 174; chunks of 1024 then 21 / 41 / 60 / 88 / 196; one workgroup for all listed
+// cells instead of MP_FAN-way merges: 567 us at 2^22).  A chunk's moments kept in
+// LDS for the parents change nothing up to 2^19 particles and take 85 / 217 us at
+// 2^20 / 2^22: one workgroup per compute unit.
 constexpr unsigned MP_THREADS = 256;
 constexpr unsigned MP_OCTS = MP_THREADS / OCT;
 constexpr unsigned MP_CELLS = 512;  // internal cells of a chunk listed in LDS (more: the level ranges are walked)
