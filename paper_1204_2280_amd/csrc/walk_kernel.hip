@@ -375,16 +375,18 @@ __global__ __launch_bounds__(64 * NW, 4) void k_walk(WalkArgs a) {
     constexpr unsigned PC_LDS = PREC ? WALK_PC_LDS - 192 : WALK_PC_LDS;
     __shared__ uint32_t s_pc[PC_LDS];
     __shared__ uint32_t s_pp[WALK_PP_LDS];
-    __shared__ float s_res_all[256];
-    __shared__ float s_cmp_all[PREC ? 256 : 64];
+    // results of 64 particles, at least one chunk's per wave
+    constexpr unsigned RES = NW <= 4 ? 256u / NW : 64u;
+    __shared__ float s_res_all[NW * RES];
+    __shared__ float s_cmp_all[PREC ? NW * RES : 64];
     __shared__ uint32_t s_idx[64];  // group particle evaluated in each lane
     __shared__ uint32_t s_perm[64];  // caller's index of each group particle
     __shared__ EvalCmd s_cmd;
     __shared__ unsigned s_slot;
     const unsigned ln = lane64();
     const unsigned wid = NW > 1 ? uniform(threadIdx.x >> 6) : 0u;
-    float *const s_res = s_res_all + wid * (256 / NW);
-    float *const s_cmp = s_cmp_all + (PREC ? wid * (256 / NW) : 0u);
+    float *const s_res = s_res_all + wid * RES;
+    float *const s_cmp = s_cmp_all + (PREC ? wid * RES : 0u);
     uint32_t *gstk = a.wstack + (size_t)blockIdx.x * STACK_CAP;
     if (a.hdr->flags & (FLAG_NONFINITE | FLAG_NEGMASS | FLAG_CELLCAP)) return;
     // particles a lane may add to the particle-particle list per round, so that
@@ -447,7 +449,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_walk(WalkArgs a) {
         p.z = __shfl(p0.z, pj, 64);
         p.w = 0.0f;
 #pragma unroll
-        for (int c = 0; c < 4 / NW; c++) {
+        for (int c = 0; c < (int)(RES / 64u); c++) {
             s_res[c * 64 + ln] = 0.0f;
             if (PREC) s_cmp[c * 64 + ln] = 0.0f;
         }
@@ -1002,11 +1004,13 @@ __global__ __launch_bounds__(PREFIX_THREADS) void k_walk_prefix(WalkArgs a, unsi
 // the queue's end by size one wave gains more than two, so the second line lies
 // between where these meet at theta 0.75 (115000) and 0.5 (128000): with one wave
 // and with two, us, 100003 278 / 483 and 265 / 446, 125000 278 / 548 and 298 / 522,
-// 140000 288 / 562 and 318 / 568, 160000 303 / 577 and 354 / 638.
-int walk_group_waves(unsigned n) { return n <= 32768u ? 4 : n <= 122880u ? 2 : 1; }
+// 140000 288 / 562 and 318 / 568, 160000 303 / 577 and 354 / 638.  Eight waves
+// against four, theta 0.75, us with the anchor pass: 1000 47.8 / 50.1, 3000 63.2 /
+// 67.8, 6000 77.3 / 83.9, 10000 106 / 88.
+int walk_group_waves(unsigned n) { return n <= 8192u ? 8 : n <= 32768u ? 4 : n <= 122880u ? 2 : 1; }
 
 // As many workgroups as the launch parameter's waves have spill stacks.  Of 4096
-// workgroups of 2 or 4 waves the chip holds a half or a quarter at once; the
+// workgroups of 2, 4 or 8 waves the chip holds a part at once; the
 // others follow as those end, so up to 4096 groups need no queue.
 template <int PREC, int NW>
 void launch_walk_groups(const WalkArgs &a, bool shared, unsigned grid, hipStream_t s) {
@@ -1015,7 +1019,8 @@ void launch_walk_groups(const WalkArgs &a, bool shared, unsigned grid, hipStream
 }
 template <int PREC>
 void launch_walk_waves(const WalkArgs &a, bool shared, int nw, unsigned waves, hipStream_t s) {
-    if (nw == 4) launch_walk_groups<PREC, 4>(a, shared, waves, s);
+    if (nw == 8) launch_walk_groups<PREC, 8>(a, shared, waves, s);
+    else if (nw == 4) launch_walk_groups<PREC, 4>(a, shared, waves, s);
     else if (nw == 2) launch_walk_groups<PREC, 2>(a, shared, waves, s);
     else launch_walk_groups<PREC, 1>(a, shared, waves, s);
 }
