@@ -122,6 +122,7 @@ size_t layout(int64_t n_max, const mibh_params &p, char *base, Buffers *b) {
     t.cl = (int8_t *)take(n);
     t.lvinfo = (uchar4 *)take(4 * n);
     t.blkcnt = (uint32_t *)take(4 * NCOUNTERS * nblk);
+    t.blkoff = (uint32_t *)take(4 * NCOUNTERS * nblk);
     t.ctot = (uint32_t *)take(4 * NCOUNTERS);
     size_t nranges = 0;  // of the multipole pass: chunks, then one in MP_FAN until one is left
     for (size_t r = (n + MP_CHUNK - 1) / MP_CHUNK; r > 1; r = (r + MP_FAN - 1) / MP_FAN) nranges += r;

@@ -230,7 +230,8 @@ struct Buffers {
     float4 *spos;           // sorted x, y, z, m
     int8_t *cl;             // common leading octal digits with the previous key (-1 at 0)
     uchar4 *lvinfo;         // per particle: first level started, leaf level, group level, group start
-    uint32_t *blkcnt;       // [NCOUNTERS][nblk]
+    uint32_t *blkcnt;       // [NCOUNTERS][nblk] counts of the build's blocks
+    uint32_t *blkoff;       // their exclusive prefix sums over the blocks
     uint32_t *ctot;         // [NCOUNTERS]
     uint32_t *mlist;        // multipoles: cells that leave their range of particles, per range size and level
     uint4 *topo;            // cells: first, count, child_first, system<<16 | level<<8 | nchild

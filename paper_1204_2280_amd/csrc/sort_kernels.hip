@@ -8,7 +8,8 @@
 //     kernel): the buckets' splitters.
 //   k_bucket_count: every particle's bucket (a binary search for its key over
 //     the splitters in LDS) and the counts of each tile's buckets.
-//   k_bucket_scan: the counts' prefix sums over the tiles, bucket by bucket.
+//   k_bucket_scan: the counts' prefix sums over the tiles, bucket by bucket (with
+//     few tiles part of the next kernel).
 //   k_bucket_scatter: particle records and indices to their buckets.
 //   k_bucket_sort: one workgroup per bucket sorts it in LDS and writes keys,
 //     permutation, records and shared digits in their final order: the moving
@@ -21,7 +22,7 @@
 //
 // The radix sort reads and writes every key eight times in 24 launches, then
 // gathers the records.  Sorting and moving, bounding cube to records in order:
-// 27 / 65 / 79 / 125 / 297 us at n = 1000 / 20000 / 100003 / 2^20 / 2^22 against
+// 27 / 64 / 77 / 125 / 297 us at n = 1000 / 20000 / 100003 / 2^20 / 2^22 against
 // 124 / 161 / 169 / 216 / 488 us.  Small inputs are bound by the launches and
 // the sort's chain of merges; at 2^22 the sort of the buckets takes 120 us (57
 // bytes a particle, 0.4 of the copy rate; LDS latency of the merges), the
@@ -477,6 +478,10 @@ __global__ __launch_bounds__(64 * SCAN_SEGS) void k_bucket_scan(uint32_t *__rest
 // where they were read, 2^22 records went to HBM in 287 MB of partial lines
 // (84 MB of data) and 112 us.  Consecutive tiles go to one XCD (workgroup i runs
 // on XCD i mod 8), so that the short runs they add to a bucket meet in its L2.
+// SCAN: few tiles and no more buckets than threads; every workgroup adds up the
+// columns of counts itself, a thread each (no launch between, 4.5 us).
+constexpr unsigned SCATTER_SCAN_TILES = 64;
+template <bool SCAN>
 __global__ __launch_bounds__(1024) void k_bucket_scatter(const float *__restrict__ pos, const float *__restrict__ mass,
                                                          const unsigned short *__restrict__ bkt, unsigned n,
                                                          const uint32_t *__restrict__ counts, unsigned ntiles,
@@ -497,12 +502,24 @@ __global__ __launch_bounds__(1024) void k_bucket_scatter(const float *__restrict
     const unsigned per = (nb + nt - 1u) / nt;
     const unsigned c0 = min(t * per, nb), c1 = min(c0 + per, nb);
     const uint32_t *row = counts + (size_t)tile * nb;
-    unsigned sum = 0, own = 0;
+    unsigned sum = 0, own = 0, earlier = 0;
     for (unsigned b = c0; b < c1; b++) {
-        const unsigned tot = total[b];
+        unsigned tot = 0, mine = 0;  // mine: this tile's elements of the bucket
+        if (SCAN) {
+#pragma unroll 8
+            for (unsigned r = 0; r < ntiles; r++) {
+                const unsigned c = counts[(size_t)r * nb + b];
+                earlier += r < tile ? c : 0u;
+                mine = r == tile ? c : mine;
+                tot += c;
+            }
+        } else {
+            tot = total[b];
+            mine = (tile + 1u < ntiles ? row[nb + b] : tot) - row[b];
+        }
         sum += tot;
-        s_at[b] = (tile + 1u < ntiles ? row[nb + b] : tot) - row[b];  // this tile's elements of the bucket
-        own += s_at[b];
+        s_at[b] = mine;
+        own += mine;
     }
     const unsigned inc = wave_incl(sum), inco = wave_incl(own);
     if ((t & 63u) == 63u) {
@@ -518,9 +535,9 @@ __global__ __launch_bounds__(1024) void k_bucket_scatter(const float *__restrict
     for (unsigned b = c0; b < c1; b++) {
         const unsigned c = s_at[b];
         s_at[b] = runo;
-        s_out[b] = run + row[b] - runo;  // modulo 2^32
+        s_out[b] = run + (SCAN ? earlier : row[b]) - runo;  // modulo 2^32
         if (tile == 0) start[b] = run;
-        run += total[b];
+        run += SCAN ? sum : total[b];  // (one bucket per thread)
         runo += c;
     }
     if (tile == 0 && t == 0) start[nb] = n;
@@ -864,11 +881,17 @@ hipError_t launch_bucket_partition(const Buffers &b, const BuildStart &start, co
                            sc.list_key, sc.list_idx, sc.spl_key, sc.spl_idx);
     hipLaunchKernelGGL(k_bucket_count, dim3(ntiles), dim3(nt), 16 * (size_t)nb, s, pos, n, nsys, b.sys_off, b.bkt_off,
                        b.cube, sc.spl_key, sc.spl_idx, nb, sc.bkt, sc.counts);
-    hipLaunchKernelGGL(k_bucket_scan, dim3((nb + 63u) / 64u), dim3(64 * SCAN_SEGS), 0, s, sc.counts, ntiles, nb, sc.total);
     const unsigned grid = 8u * ((ntiles + 7u) / 8u);
-    hipLaunchKernelGGL(k_bucket_scatter, dim3(grid), dim3(nt), 8 * (size_t)nb + 4 * (size_t)tile,
-                       s, pos, mass, sc.bkt, n, sc.counts,
-                       ntiles, sc.total, nb, sc.start, b.vals[1], b.ppack);
+    const size_t lds = 8 * (size_t)nb + 4 * (size_t)tile;
+    if (ntiles <= SCATTER_SCAN_TILES && nb <= nt) {
+        hipLaunchKernelGGL(k_bucket_scatter<true>, dim3(grid), dim3(nt), lds, s, pos, mass, sc.bkt, n, sc.counts, ntiles,
+                           nullptr, nb, sc.start, b.vals[1], b.ppack);
+    } else {
+        hipLaunchKernelGGL(k_bucket_scan, dim3((nb + 63u) / 64u), dim3(64 * SCAN_SEGS), 0, s, sc.counts, ntiles, nb,
+                           sc.total);
+        hipLaunchKernelGGL(k_bucket_scatter<false>, dim3(grid), dim3(nt), lds, s, pos, mass, sc.bkt, n, sc.counts, ntiles,
+                           sc.total, nb, sc.start, b.vals[1], b.ppack);
+    }
     return hipGetLastError();
 }
 
