@@ -70,7 +70,8 @@ typedef struct {
     float eps2;         /* Plummer softening length squared (default 0) */
     float G;            /* gravitational constant (default 1) */
     int32_t precision;  /* MIBH_PLAIN, MIBH_KAHAN or MIBH_KAHAN_TERM accumulation (default plain) */
-    int32_t walk_waves; /* waves of the persistent walk launch; 0 = 4096 (16 per CU of a
+    int32_t walk_waves; /* workgroups of the persistent walk launch (a wave each in large
+                           trees, up to eight in small ones); 0 = 4096 (16 per CU of a
                            256-CU MI355X) */
     int32_t pc_cap;     /* per-wave particle-cell list entries (in LDS) before an evaluation
                            flush, 128 <= pc_cap <= 1024 (default 1024) */
@@ -110,7 +111,7 @@ mibh_status mibh_create(const mibh_params *p, int64_t n_max, void *d_workspace,
 /* Frees the host-side context (the workspace stays the caller's). */
 mibh_status mibh_destroy(mibh_ctx *ctx);
 
-/* Tree construction: bounding cube, 60-bit Morton keys, stable radix sort,
+/* Tree construction: bounding cube, 60-bit Morton keys, stable sort,
  * reorder of positions and masses, breadth-first sparse octree and groups
  * (the sorting / moving / tree-construction parts of the Results section).
  * d_pos [n][3] and d_mass [n] must stay valid and unchanged until the next
@@ -374,7 +375,7 @@ mibh_status mibh_export(mibh_ctx *ctx, int what, void *d_dst, size_t bytes);
 
 /* Stage timing with HIP events on the context's stream, for the sections the
  * paper times separately (Results section, Fig. 1): sorting (bounding cube,
- * keys, radix sort), moving (reorder), tree construction (octree, groups),
+ * keys, partition), moving (sort of the buckets, reorder), tree construction (octree, groups),
  * multipole moments, MAC preparation and the tree traverse (walk kernel).
  * mibh_profile_begin(ctx, max_steps) starts recording one set of events per
  * step (a step ends at compute_forces) for up to max_steps steps; stages a

@@ -2,11 +2,12 @@
 // Results section) on gfx950.
 //
 // One wave64 per group (the vector-machine idea of Barnes 1990: one
-// interaction list shared by a group of nearby particles; two or four waves where
+// interaction list shared by a group of nearby particles; two to eight waves where
 // groups are few, see walk_group_waves), persistent waves pulling groups from
 // eight queues, one per XCD, each an atomic head on a cache line of its own over
 // one eighth of the processing order: the groups in Morton order (the waves of an
-// XCD then walk spatial neighbours, whose cells they share in that XCD's L2) or a
+// XCD then walk spatial neighbours, whose cells they share in that XCD's L2), in
+// large trees with the end of each queue by group size, or a
 // work-ordered permutation, heaviest groups first.  A wave whose queue is empty
 // takes groups from the others.
 //
@@ -1032,7 +1033,7 @@ void launch_walk_waves(const WalkArgs &a, bool shared, int nw, unsigned waves, h
 // 65536-particle Plummer sphere by work: 282 us against 217 in Morton order).  With
 // more groups than workgroups the walk gains from 80000 particles (230 us against
 // 270) over 300007 (485 against 630) to 2^20 (1395 against 1540); an active walk
-// of every tenth of 2^20 particles takes 364 us against 450.
+// of 15% of 2^20 particles takes 364 us against 450.
 bool walk_sorts_groups(unsigned n) { return n > 65536u; }
 
 hipError_t launch_walk(const Buffers &b, unsigned n, unsigned nsys, float eps2, float G, int precision,
