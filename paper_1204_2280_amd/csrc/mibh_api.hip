@@ -147,6 +147,7 @@ size_t layout(int64_t n_max, const mibh_params &p, char *base, Buffers *b) {
     t.gorder = (uint32_t *)take(4 * n);
     t.ghist = (uint32_t *)take(4 * 2 * GORD_CLASSES * ((n + GORD_BLOCK - 1) / GORD_BLOCK));
     t.gahist = (uint32_t *)take(4 * 2 * GORD_CLASSES * ((n + GORD_BLOCK - 1) / GORD_BLOCK));
+    t.nheavy = (uint32_t *)take(4 * n);
     t.gflag = (uint8_t *)take(n);
     t.acnt = (uint32_t *)take(4 * ((n + 511) / 512));
     const bool shared_walk = p.anchor_up > 0;

@@ -254,6 +254,7 @@ struct Buffers {
     uint32_t *ghist;        // [blocks of GORD_BLOCK groups][2][GORD_CLASSES] groups by eighth and count
     uint32_t *gahist;       // the same for an active walk's queue
     uint32_t *gorder;       // queue of large trees
+    uint32_t *nheavy;       // neighbour searches: groups left to the second pass
     uint8_t *gflag;         // active walks: group holds an active particle
     uint32_t *acnt;         // active walks: such groups per 512
     uint32_t *anchor;       // shared-prefix walk: anchor cell of each group
@@ -465,6 +466,8 @@ hipError_t launch_multipoles(const Buffers &b, unsigned n, unsigned nsys, hipStr
 hipError_t launch_mac_prep(const Buffers &b, unsigned nsys, double theta, hipStream_t s);
 // whether the walk of a tree of n particles takes the end of its queue by size
 bool walk_sorts_groups(unsigned n);
+// every group in that order into b.gorder
+hipError_t launch_group_order(const Buffers &b, unsigned n, hipStream_t s);
 // order: the queue (NULL: groups in Morton order); qlen: device count of queue
 // entries to walk (NULL: every group)
 // anchor_up > 0: groups share the traversal of their ancestor anchor_up levels up

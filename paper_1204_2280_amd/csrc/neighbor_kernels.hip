@@ -33,6 +33,8 @@ namespace {
 constexpr unsigned NGB_LSTACK = 512;   // LDS part of the cell stack (spills to the global stack)
 constexpr unsigned NGB_LIST = 1536;    // candidate list of a group's wave
 constexpr unsigned NGB_WAVES = 8;      // waves of a group with more candidates
+constexpr unsigned NGB_PART = 8;       // particles of a part of a heavy group
+constexpr unsigned NGB_ONE_PASS = 32768;  // particles up to which every group has NGB_WAVES waves
 constexpr unsigned NGB_LIST_HEAVY = 4096;
 constexpr float NGB_FAR = 1.0e18f;
 // Candidates a group lists before its cells are tested against its particles
@@ -138,6 +140,7 @@ struct NgbArgs {
     const float *radius;     // per input particle: radius (count, list) or h (density)
     float scale;             // search radius = scale * radius (2 for density)
     uint32_t *wstack;
+    const uint32_t *order;   // first pass: the groups in the queues' order (NULL: Morton)
     uint32_t *heavy;         // groups left to the second pass (NULL: no first pass, every group)
     uint32_t *count;         // per input particle
     const uint32_t *offset;  // list: first slot of each input particle
@@ -251,9 +254,11 @@ __device__ void ngb_density(const NgbArgs &a, const uint32_t *list, unsigned n, 
 // Two passes over the groups (one of NW = NGB_WAVES in small trees: see
 // launch_passes).  The first (NW = 1) gives each group a wave and
 // leaves those with more than NGB_LIST candidates, of which it has then only
-// walked the tree, to the second, which gives each a workgroup of NGB_WAVES waves:
-// a cell per thread and step of the traversal, and the tiles of candidates dealt
-// to the waves.  In a sphere's outskirts a radius that reaches 64 neighbours may
+// walked the tree, to the second, which gives each NGB_PART of their particles a
+// workgroup of NGB_WAVES waves, as a group of their own: a cell per thread and step
+// of the traversal, and the tiles of candidates dealt to the waves.  The first pass
+// takes large trees' groups in the walk's order, the end of each queue by size
+// (density of 250007 particles 313 us in Morton order, 240 so).  In a sphere's outskirts a radius that reaches 64 neighbours may
 // reach the whole core: with one wave for every group the pass lasted as long as
 // that group, whatever n.
 template <int MODE, int NW>
@@ -280,7 +285,9 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
     if (a.hdr->flags & (FLAG_NONFINITE | FLAG_NEGMASS | FLAG_CELLCAP)) return;
     constexpr unsigned per_round = 8;  // particles per thread: a round always fits an empty list
     static_assert(per_round * STEP <= LIST, "a round fits");
-    const unsigned ngroups = uniform(HEAVY && a.heavy ? a.hdr->ngb_heavy : a.hdr->ngroups);
+    // slots: the groups, or the heavy ones' parts
+    const unsigned part = HEAVY && a.heavy ? NGB_PART : 64u, nparts = 64u / part;
+    const unsigned ngroups = uniform(HEAVY && a.heavy ? a.hdr->ngb_heavy : a.hdr->ngroups) * nparts;
     QueueCursor qc = queue_start();
     unsigned par = 0;
     // sums over the workgroup of each wave's v (the same in all its lanes), before this wave and in all
@@ -310,9 +317,12 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
         // every lane takes part in the queue atomic (see the walk's queue loop)
         if (!HEAVY) slot = queue_next(a.head, ngroups, qc);
         if (slot >= ngroups) break;
-        const unsigned g = HEAVY && a.heavy ? uniform(a.heavy[slot]) : slot;
+        const unsigned k = HEAVY ? slot / nparts : slot;
+        const unsigned g = HEAVY ? (a.heavy ? uniform(a.heavy[k]) : k) : (a.order ? uniform(a.order[k]) : k);
         const uint2 gr = a.groups[g];
-        const unsigned gf = uniform(gr.x), gn = uniform(gr.y & 255u);
+        const unsigned p0 = HEAVY ? slot % nparts * part : 0u, gall = uniform(gr.y & 255u);
+        if (HEAVY && p0 >= gall) continue;  // the same for the whole workgroup
+        const unsigned gf = uniform(gr.x) + p0, gn = min(gall - p0, part);
         const unsigned root = uniform(gr.y >> 16);
         const unsigned mine = gf + min(ln, gn - 1);
         const float4 p = a.spos[mine];
@@ -584,13 +594,14 @@ __global__ __launch_bounds__(SCAN_TILE) void k_scan_apply(const uint32_t *__rest
 }
 
 // With few groups each takes NGB_WAVES waves at once; with many their waves fill
-// the chip and only the heavy ones do.  Density passes of a Plummer sphere (64
-// neighbours within 2h) one way / the other, us: 1000 46 / 102, 5000 74 / 202,
-// 20000 203 / 354, 65536 815 / 991, 131072 486 / 313, 250007 871 / 300 (one wave for
-// every group: 125, 315, 1096, 5196, 564, 346).
+// the chip and only the heavy ones do, in parts.  Density passes of a Plummer sphere
+// (64 neighbours within 2h) one way / the other, us: 1000 46 / 103, 5000 74 / 175,
+// 20000 202 / 273, 50000 480 / 407, 65536 823 / 500 (one wave for every group: 125,
+// 315, 1096, -, 5196; heavy groups in one part: 65536 991, 70000 881 against 502,
+// 131072 313 against 250; parts of 16 or 4: 70000 600, 517).
 template <int MODE>
 void launch_passes(NgbArgs a, unsigned n, unsigned waves, hipStream_t s) {
-    const bool one = n <= 65536u;
+    const bool one = n <= NGB_ONE_PASS;
     if (one) a.heavy = nullptr;
     else hipLaunchKernelGGL((k_neighbors<MODE, 1>), dim3(waves), dim3(64), 0, s, a);
     hipLaunchKernelGGL((k_neighbors<MODE, NGB_WAVES>), dim3(one ? waves : min(waves, 512u)), dim3(64 * NGB_WAVES), 0, s,
@@ -612,7 +623,8 @@ hipError_t launch_neighbors(const Buffers &b, int mode, const float *radius, uin
     a.radius = radius;
     a.scale = mode == NGB_DENSITY ? 2.0f : 1.0f;
     a.wstack = b.wstack;
-    a.heavy = b.gorder;  // at most n groups; a walk writes it before it reads it
+    a.heavy = b.nheavy;
+    a.order = nullptr;
     a.count = count;
     a.offset = offset;
     a.index = index;
@@ -621,6 +633,10 @@ hipError_t launch_neighbors(const Buffers &b, int mode, const float *radius, uin
     static_assert(offsetof(Header, ngb_heavy) == offsetof(Header, walk_head) + sizeof(Header::walk_head), "one fill");
     hipError_t e = launch_fill_u32(b.hdr->walk_head, WALK_QUEUES * QUEUE_STRIDE + 1, 0u, s);
     if (e != hipSuccess) return e;
+    if (n > NGB_ONE_PASS && walk_sorts_groups(n)) {
+        if ((e = launch_group_order(b, n, s)) != hipSuccess) return e;
+        a.order = b.gorder;
+    }
     if (mode == NGB_COUNT) launch_passes<NGB_COUNT>(a, n, b.walk_waves, s);
     else if (mode == NGB_LISTS) launch_passes<NGB_LISTS>(a, n, b.walk_waves, s);
     else launch_passes<NGB_DENSITY>(a, n, b.walk_waves, s);

@@ -681,11 +681,12 @@ __global__ __launch_bounds__(64 * NW, 4) void k_walk(WalkArgs a) {
 // contiguous unless groups of deeper levels sit between them, so few entries
 // compete (a wave's first entry tries without a look at the entry before: a
 // claiming kernel of its own, which had that, took 4.5 us more).
-// With `gorder` the kernel also places the queue's groups: each eighth's window by
+// With `gorder` the kernel also (without ANCHORS: only) places the queue's groups: each eighth's window by
 // particle count, largest first,
 // in the old order within a count.  Every workgroup adds up the counts of its
 // eighths' window blocks; the ranks inside a block come from ballots, so the order
 // is the same on every run.
+template <bool ANCHORS>
 __global__ __launch_bounds__(GORD_BLOCK) void k_walk_anchor(const Header *__restrict__ hdr,
                                                             const uint2 *__restrict__ groups,
                                                             const uint4 *__restrict__ topo, int up,
@@ -709,17 +710,19 @@ __global__ __launch_bounds__(GORD_BLOCK) void k_walk_anchor(const Header *__rest
         const unsigned i = blk * GORD_BLOCK + t;
         const unsigned g = i < nq ? (order ? order[i] : i) : 0u;
         const uint2 gr = i < nq ? groups[g] : make_uint2(0u, 0u);
-        const int glev = (int)((gr.y >> 8) & 255u);
-        const int lev = glev > up ? glev - up : 0;
-        unsigned lo = hdr->lvl_begin[lev], hi = hdr->lvl_begin[lev + 1];  // topo[lo].x <= gr.x
-        while (hi - lo > 1) {
-            const unsigned mid = lo + (hi - lo) / 2;
-            if (topo[mid].x <= gr.x) lo = mid; else hi = mid;
-        }
-        const unsigned prev = __shfl_up(lo, 1, 64);
-        if (i < nq) {
-            anchor[g] = lo;
-            if ((c == 0 || prev != lo) && atomicCAS(&arec[lo].w, 0u, 2u) == 0u) alist[atomicAdd(acount, 1u)] = lo;
+        if (ANCHORS) {
+            const int glev = (int)((gr.y >> 8) & 255u);
+            const int lev = glev > up ? glev - up : 0;
+            unsigned lo = hdr->lvl_begin[lev], hi = hdr->lvl_begin[lev + 1];  // topo[lo].x <= gr.x
+            while (hi - lo > 1) {
+                const unsigned mid = lo + (hi - lo) / 2;
+                if (topo[mid].x <= gr.x) lo = mid; else hi = mid;
+            }
+            const unsigned prev = __shfl_up(lo, 1, 64);
+            if (i < nq) {
+                anchor[g] = lo;
+                if ((c == 0 || prev != lo) && atomicCAS(&arec[lo].w, 0u, 2u) == 0u) alist[atomicAdd(acount, 1u)] = lo;
+            }
         }
         if (!gorder) continue;  // the same for the whole launch
         if (nq < GORD_MIN) {
@@ -1036,6 +1039,13 @@ void launch_walk_waves(const WalkArgs &a, bool shared, int nw, unsigned waves, h
 // of 15% of 2^20 particles takes 364 us against 450.
 bool walk_sorts_groups(unsigned n) { return n > 65536u; }
 
+hipError_t launch_group_order(const Buffers &b, unsigned n, hipStream_t s) {
+    const unsigned blocks = min((n + GORD_BLOCK - 1u) / GORD_BLOCK, 1024u);
+    hipLaunchKernelGGL(k_walk_anchor<false>, dim3(blocks), dim3(GORD_BLOCK), 0, s, b.hdr, b.groups, b.topo, 0, nullptr,
+                       nullptr, nullptr, nullptr, b.ghist, b.gorder, nullptr, nullptr);
+    return hipGetLastError();
+}
+
 hipError_t launch_walk(const Buffers &b, unsigned n, unsigned nsys, float eps2, float G, int precision,
                        const uint32_t *order, const uint32_t *qlen, const uint8_t *active, float *acc, float *pot,
                        int anchor_up, hipStream_t s) {
@@ -1073,7 +1083,7 @@ hipError_t launch_walk(const Buffers &b, unsigned n, unsigned nsys, float eps2, 
         uint32_t *ghist = qlen ? b.gahist : b.ghist;
         if (gorder && qlen)
             hipLaunchKernelGGL(k_walk_count, dim3(ablk), dim3(256), 0, s, b.hdr, b.groups, order, qlen, ghist);
-        hipLaunchKernelGGL(k_walk_anchor, dim3(ablk), dim3(GORD_BLOCK), 0, s, b.hdr, b.groups, b.topo, anchor_up, b.anchor,
+        hipLaunchKernelGGL(k_walk_anchor<true>, dim3(ablk), dim3(GORD_BLOCK), 0, s, b.hdr, b.groups, b.topo, anchor_up, b.anchor,
                            b.arec, order, qlen, ghist, gorder, b.alist, &b.hdr->anchor_count);
         if (gorder) a.order = gorder;
         hipLaunchKernelGGL(k_walk_prefix, dim3(min(b.walk_waves, 1024u)), dim3(PREFIX_THREADS), 0, s, a, b.hdr->prefix_head,

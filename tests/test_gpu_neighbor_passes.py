@@ -1,4 +1,4 @@
-"""Neighbour search with every group on eight waves (trees of up to 65536
+"""Neighbour search with every group on eight waves (trees of up to 32768
 particles) against the two passes of larger trees (a wave per group, eight for
 the heavy ones): the same systems alone and inside a batch.  Counts and lists are
 compared exactly, densities within 1e-5 (float32 sums of positive terms in two
@@ -83,3 +83,23 @@ def test_fill_with_earlier_counts(n):
     ctx.sync()
     assert torch.equal(short[:-5], idx[:-5]) and bool((short[-5:] == -7).all())
     assert mibh.lib().mibh_neighbor_fill(ctx.handle, r.data_ptr(), cnt.data_ptr(), None, short.data_ptr(), 5) == -1
+
+
+@pytest.mark.parametrize("n", [32768, 32769, 65537])
+def test_both_sides_of_the_pass_lines(n):
+    import torch
+    pos, mass, r = (torch.from_numpy(x).cuda() for x in _system(0, n))
+    far = (pos + 100.0).contiguous()  # a second system, to reach more particles
+    one = gpu_context(n)
+    one.build_tree(pos, mass)
+    one.compute_multipoles()
+    both = gpu_context(2 * n, max_systems=2)
+    both.build_tree_batch(torch.cat([pos, far]), torch.cat([mass, mass]), np.array([0, n, 2 * n]))
+    both.compute_multipoles()
+    print(f"[gpu] neighbour pass lines: n={n}", flush=True)
+    c1, o1, i1 = (t.cpu().numpy() for t in one.neighbor_list(r))
+    c2, o2, i2 = (t.cpu().numpy() for t in both.neighbor_list(torch.cat([r, r])))
+    np.testing.assert_array_equal(c1, c2[:n])
+    own = np.repeat(np.arange(n), c1)
+    i2 = i2[: o2[n]]
+    np.testing.assert_array_equal(i1[np.lexsort((i1, own))], i2[np.lexsort((i2, own))])
