@@ -33,6 +33,14 @@ namespace {
 constexpr unsigned NGB_LSTACK = 512;   // LDS part of the cell stack (spills to the global stack)
 constexpr unsigned NGB_LIST = 1536;    // candidate list of a group's wave
 constexpr unsigned NGB_WAVES = 8;      // waves of a group with more candidates
+// Heavy groups up to which they are taken in parts, and beyond which each takes one
+// wave after all: a workgroup per part or group costs several times the work of a
+// wave, so it is for the groups that would outlast the others.  Densities with 512
+// neighbours, us: 131072 particles 678 (parts of every group 2605, one wave for every
+// group 3750), 500000 particles 1300 (10244, 2050); up to 8192 heavy groups on eight
+// waves 816 at 131072.
+constexpr unsigned NGB_FEW = 512;
+constexpr unsigned NGB_MANY = 2048;
 constexpr unsigned NGB_PART = 8;       // particles of a part of a heavy group
 constexpr unsigned NGB_ONE_PASS = 32768;  // particles up to which every group has NGB_WAVES waves
 constexpr unsigned NGB_LIST_HEAVY = 4096;
@@ -141,6 +149,7 @@ struct NgbArgs {
     float scale;             // search radius = scale * radius (2 for density)
     uint32_t *wstack;
     const uint32_t *order;   // first pass: the groups in the queues' order (NULL: Morton)
+    uint8_t *gflag;          // of each group: left by the first pass
     uint32_t *heavy;         // groups left to the second pass (NULL: no first pass, every group)
     uint32_t *count;         // per input particle
     const uint32_t *offset;  // list: first slot of each input particle
@@ -251,19 +260,23 @@ __device__ void ngb_density(const NgbArgs &a, const uint32_t *list, unsigned n, 
     }
 }
 
-// Two passes over the groups (one of NW = NGB_WAVES in small trees: see
+// Three passes over the groups (one of NW = NGB_WAVES in small trees: see
 // launch_passes).  The first (NW = 1) gives each group a wave and
 // leaves those with more than NGB_LIST candidates, of which it has then only
 // walked the tree, to the second, which gives each NGB_PART of their particles a
-// workgroup of NGB_WAVES waves, as a group of their own: a cell per thread and step
-// of the traversal, and the tiles of candidates dealt to the waves.  The first pass
-// takes large trees' groups in the walk's order, the end of each queue by size
-// (density of 250007 particles 313 us in Morton order, 240 so).  In a sphere's outskirts a radius that reaches 64 neighbours may
-// reach the whole core: with one wave for every group the pass lasted as long as
-// that group, whatever n.
-template <int MODE, int NW>
+// workgroup of NGB_WAVES waves, as a group of their own (NGB_FEW heavy groups or
+// fewer; else whole groups): a cell per thread and step of the traversal, and the
+// tiles of candidates dealt to the waves.  Where most groups are heavy, more than
+// NGB_MANY, the third pass (ALL, NW = 1) takes them instead, a wave each, and tests
+// the list whenever it is full.  How many are heavy depends on the input alone.  The
+// first pass takes large trees' groups in the walk's order, the end of each queue by
+// size (density of 250007 particles 313 us in Morton order, 240 so).  In a sphere's
+// outskirts a radius that reaches 64 neighbours may reach the whole core: with one
+// wave for every group the pass lasted as long as that group, whatever n.
+template <int MODE, int NW, bool ALL>
 __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
-    constexpr bool HEAVY = NW > 1;
+    constexpr bool HEAVY = NW > 1, REST = NW == 1 && ALL;  // REST: the third pass
+    static_assert(ALL || NW == 1, "only a first pass leaves groups");
     constexpr unsigned NT = 64 * NW, STEP = HEAVY ? 256u : 64u;  // cells taken per step at most
     constexpr unsigned RING = HEAVY ? 16u * STEP : NGB_LSTACK, MASK = RING - 1;
     constexpr unsigned LIST = HEAVY ? NGB_LIST_HEAVY : NGB_LIST;
@@ -285,9 +298,12 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
     if (a.hdr->flags & (FLAG_NONFINITE | FLAG_NEGMASS | FLAG_CELLCAP)) return;
     constexpr unsigned per_round = 8;  // particles per thread: a round always fits an empty list
     static_assert(per_round * STEP <= LIST, "a round fits");
+    const unsigned nheavy = ALL && a.heavy ? uniform(a.hdr->ngb_heavy) : 0u;
+    if (HEAVY && nheavy > NGB_MANY) return;
+    if (REST && nheavy <= NGB_MANY) return;
     // slots: the groups, or the heavy ones' parts
-    const unsigned part = HEAVY && a.heavy ? NGB_PART : 64u, nparts = 64u / part;
-    const unsigned ngroups = uniform(HEAVY && a.heavy ? a.hdr->ngb_heavy : a.hdr->ngroups) * nparts;
+    const unsigned part = HEAVY && a.heavy && nheavy <= NGB_FEW ? NGB_PART : 64u, nparts = 64u / part;
+    const unsigned ngroups = (HEAVY && a.heavy ? nheavy : uniform(a.hdr->ngroups)) * nparts;
     QueueCursor qc = queue_start();
     unsigned par = 0;
     // sums over the workgroup of each wave's v (the same in all its lanes), before this wave and in all
@@ -315,10 +331,11 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
     };
     for (unsigned slot = blockIdx.x;; slot += gridDim.x) {
         // every lane takes part in the queue atomic (see the walk's queue loop)
-        if (!HEAVY) slot = queue_next(a.head, ngroups, qc);
+        if (!HEAVY) slot = queue_next(REST ? a.hdr->prefix_head : a.head, ngroups, qc);
         if (slot >= ngroups) break;
         const unsigned k = HEAVY ? slot / nparts : slot;
         const unsigned g = HEAVY ? (a.heavy ? uniform(a.heavy[k]) : k) : (a.order ? uniform(a.order[k]) : k);
+        if (REST && uniform(a.gflag[g]) == 0u) continue;
         const uint2 gr = a.groups[g];
         const unsigned p0 = HEAVY ? slot % nparts * part : 0u, gall = uniform(gr.y & 255u);
         if (HEAVY && p0 >= gall) continue;  // the same for the whole workgroup
@@ -451,7 +468,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
             if (all[2] == 0 && all[0] <= LIST) {
                 if (all[0]) {
                     if (nl + all[0] > LIST) {
-                        if (!HEAVY) {
+                        if (!ALL) {
                             later = true;
                             break;
                         }
@@ -469,7 +486,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
                     exchange(rsum, rb, ra);
                     if (ra[0] == 0) break;
                     if (nl + ra[0] > LIST) {
-                        if (!HEAVY) {
+                        if (!ALL) {
                             later = true;
                             break;
                         }
@@ -500,6 +517,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
             st += nsum;
             __syncthreads();
         }
+        if (!ALL) a.gflag[g] = later ? 1 : 0;
         if (later) {
             // (every lane stores the same word: no lane-dependent branch in this loop)
             a.heavy[uniform(atomicAdd(&a.hdr->ngb_heavy, ln == 0 ? 1u : 0u))] = g;
@@ -603,9 +621,10 @@ template <int MODE>
 void launch_passes(NgbArgs a, unsigned n, unsigned waves, hipStream_t s) {
     const bool one = n <= NGB_ONE_PASS;
     if (one) a.heavy = nullptr;
-    else hipLaunchKernelGGL((k_neighbors<MODE, 1>), dim3(waves), dim3(64), 0, s, a);
-    hipLaunchKernelGGL((k_neighbors<MODE, NGB_WAVES>), dim3(one ? waves : min(waves, 512u)), dim3(64 * NGB_WAVES), 0, s,
-                       a);
+    else hipLaunchKernelGGL((k_neighbors<MODE, 1, false>), dim3(waves), dim3(64), 0, s, a);
+    hipLaunchKernelGGL((k_neighbors<MODE, NGB_WAVES, true>), dim3(one ? waves : min(waves, 512u)), dim3(64 * NGB_WAVES), 0,
+                       s, a);
+    if (!one) hipLaunchKernelGGL((k_neighbors<MODE, 1, true>), dim3(waves), dim3(64), 0, s, a);
 }
 
 }  // namespace
@@ -624,14 +643,18 @@ hipError_t launch_neighbors(const Buffers &b, int mode, const float *radius, uin
     a.scale = mode == NGB_DENSITY ? 2.0f : 1.0f;
     a.wstack = b.wstack;
     a.heavy = b.nheavy;
+    a.gflag = b.gflag;
     a.order = nullptr;
     a.count = count;
     a.offset = offset;
     a.index = index;
     a.capacity = capacity < 0 ? 0u : (unsigned)std::min<int64_t>(capacity, 0xffffffffll);
     a.rho = rho;
-    static_assert(offsetof(Header, ngb_heavy) == offsetof(Header, walk_head) + sizeof(Header::walk_head), "one fill");
-    hipError_t e = launch_fill_u32(b.hdr->walk_head, WALK_QUEUES * QUEUE_STRIDE + 1, 0u, s);
+    // the heads of the first and third passes' queues and the number of heavy groups
+    static_assert(offsetof(Header, prefix_head) == offsetof(Header, walk_head) + sizeof(Header::walk_head) + 256 &&
+                      offsetof(Header, ngb_heavy) == offsetof(Header, walk_head) + sizeof(Header::walk_head),
+                  "one fill");
+    hipError_t e = launch_fill_u32(b.hdr->walk_head, 2 * WALK_QUEUES * QUEUE_STRIDE + 64, 0u, s);
     if (e != hipSuccess) return e;
     if (n > NGB_ONE_PASS && walk_sorts_groups(n)) {
         if ((e = launch_group_order(b, n, s)) != hipSuccess) return e;

@@ -103,3 +103,30 @@ def test_both_sides_of_the_pass_lines(n):
     own = np.repeat(np.arange(n), c1)
     i2 = i2[: o2[n]]
     np.testing.assert_array_equal(i1[np.lexsort((i1, own))], i2[np.lexsort((i2, own))])
+
+
+@pytest.mark.parametrize("sizes", [[30000, 4000], [30000, 30000, 10000]])  # 1535 and 3006 groups, nearly all heavy
+def test_many_heavy_groups(sizes):
+    import torch
+    pos = torch.cat([torch.from_numpy(W.uniform_cube(n, 400 + k)[0]) for k, n in enumerate(sizes)]).cuda()
+    mass = torch.full((len(pos),), 1.0 / len(pos), device="cuda")
+    r = torch.full((len(pos),), 0.33, device="cuda")
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    print(f"[gpu] many heavy groups: {sizes}", flush=True)
+    ctx = gpu_context(int(off[-1]), max_systems=len(sizes))
+    ctx.build_tree_batch(pos, mass, off)
+    ctx.compute_multipoles()
+    cnt, o, idx = ctx.neighbor_list(r)
+    rho, dcnt = ctx.sph_density(r * 0.5)
+    assert torch.equal(rho, ctx.sph_density(r * 0.5)[0]) and torch.equal(cnt, dcnt)
+    for k, n in enumerate(sizes):
+        s = slice(off[k], off[k + 1])
+        one = gpu_context(n)
+        one.build_tree(pos[s].contiguous(), mass[s].contiguous())
+        one.compute_multipoles()
+        c1, o1, i1 = one.neighbor_list(r[s].contiguous())
+        assert torch.equal(cnt[s], c1)
+        own = torch.repeat_interleave(torch.arange(n, device="cuda"), c1.long())
+        a = idx[int(o[off[k]]):int(o[off[k + 1]])].long() - int(off[k])
+        assert torch.equal(torch.sort(own * n + a)[0], torch.sort(own * n + i1.long())[0])
+        assert float(((rho[s] - one.sph_density((r * 0.5)[s].contiguous())[0]).abs() / rho[s]).max()) <= 1e-5
