@@ -23,7 +23,7 @@
 // operations); list entries are placed by ballot ranks; densities are summed per
 // lane, reduced across the wave by three transposed stages and three
 // butterflies, moved to their particle's lane, and added up over the waves in
-// their order: every run gives the same bits.
+// their order (float64): every run gives the same bits.
 #include "mibh_device.h"
 
 namespace mibh {
@@ -532,12 +532,16 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
                 s_rho[w][ln] = rho;
                 __syncthreads();
                 if (w == 0 && ln < gn) {
+                    // the waves' sums in float64, rounded once: added in float32 one
+                    // after the other, the rms error of a density of 4096 particles
+                    // was 8.0e-8 (7.7e-8 with one wave per group)
+                    double sum = rho;
                     for (unsigned u = 1; u < NW; u++) {
                         cnt += s_pcnt[u][ln];
-                        rho += s_rho[u][ln];
+                        sum += (double)s_rho[u][ln];
                     }
                     a.count[oi] = cnt;
-                    if (MODE == NGB_DENSITY) a.rho[oi] = rho;
+                    if (MODE == NGB_DENSITY) a.rho[oi] = (float)sum;
                 }
             }
         } else if (ln < gn) {
