@@ -334,8 +334,10 @@ mibh_status mibh_neighbor_list(mibh_ctx *ctx, const float *d_radius, uint32_t *d
                                uint32_t *d_index, int64_t capacity, int64_t *total);
 /* The lists alone, with the counts and offsets that mibh_neighbor_list wrote for
  * the same tree and radii (its call with capacity 0 gives *total): a list sized
- * from the counts needs no second counting pass.  Entries at or past capacity are
- * not written.  Errors: as mibh_neighbor_list. */
+ * from the counts needs no second counting pass.  It does not synchronise and so
+ * cannot tell whether the lists fit: entries at or past capacity are left out and
+ * the call still returns OK, so a caller compares *total with capacity itself.
+ * Errors: EINVAL (a null pointer, capacity < 0), ESTATE. */
 mibh_status mibh_neighbor_fill(mibh_ctx *ctx, const float *d_radius, const uint32_t *d_count,
                                const uint32_t *d_offset, uint32_t *d_index, int64_t capacity);
 mibh_status mibh_sph_density(mibh_ctx *ctx, const float *d_h, float *d_rho, uint32_t *d_count);

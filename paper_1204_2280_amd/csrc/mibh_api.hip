@@ -686,6 +686,7 @@ mibh_status mibh_neighbor_fill(mibh_ctx *ctx, const float *d_radius, const uint3
     mibh_status st = neighbors_check(ctx, d_radius, d_count);
     if (st) return st;
     if (!d_offset || (capacity > 0 && !d_index)) return fail(MIBH_EINVAL, "null pointer");
+    if (capacity < 0) return fail(MIBH_EINVAL, "capacity = %lld is negative", (long long)capacity);
     HIP_TRY(launch_neighbors(ctx->b, 1, d_radius, const_cast<uint32_t *>(d_count), d_offset, d_index, capacity, nullptr,
                              (unsigned)ctx->n, (unsigned)ctx->nsys, ctx->stream),
             "neighbors");

@@ -652,7 +652,7 @@ hipError_t launch_neighbors(const Buffers &b, int mode, const float *radius, uin
     a.count = count;
     a.offset = offset;
     a.index = index;
-    a.capacity = capacity < 0 ? 0u : (unsigned)std::min<int64_t>(capacity, 0xffffffffll);
+    a.capacity = (unsigned)std::min<int64_t>(capacity, 0xffffffffll);
     a.rho = rho;
     // the heads of the first and third passes' queues and the number of heavy groups
     static_assert(offsetof(Header, prefix_head) == offsetof(Header, walk_head) + sizeof(Header::walk_head) + 256 &&
