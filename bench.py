@@ -33,8 +33,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "walk_hbm_traffic.json")
 
 PEAK_HBM_GBS = 8000.0  # MI355X published HBM3E bandwidth
 
-# Algorithmic HBM bytes of the tree stages: per particle and per cell (the bucket
-# sort, which inputs of up to 5.59 million particles take).
+# Algorithmic HBM bytes of the tree stages: per particle and per cell.
 #   sorting: bounding box reads x, y, z, m (16); the counting reads the positions
 #     (12) and writes the bucket (2); the scatter reads both and the mass (18) and
 #     writes record and index (20);
@@ -45,14 +44,22 @@ PEAK_HBM_GBS = 8000.0  # MI355X published HBM3E bandwidth
 #   multipoles: sorted records read (16) plus per cell the topology (16), float64
 #     moments, delta and l' written (96) and read back by the parent (96), the
 #     particle box (24) and the walk data (48) written.
+# Beyond the bucket sort's 4096 buckets of 1365 particles the library sorts by radix:
+#   sorting: bounding box (16); keys read the input again and write the key (8) and
+#     the packed record (16); each of the 8 passes reads the key for the histogram
+#     (8), reads key + index (12) and writes them (12);
+#   moving: index (4), gathered record (16), written record (16).
 HBM_B_PER_PARTICLE = {"sorting": 16 + 14 + 18 + 20, "moving": 49, "tree_construction": 25, "multipoles": 16}
+HBM_B_RADIX = {"sorting": 16 + 40 + 8 * 32, "moving": 36}
 HBM_B_PER_CELL = {"tree_construction": 16, "multipoles": 16 + 96 + 96 + 24 + 48}
+BUCKET_SORT_MAX = 4096 * 1365  # particles of one system
 
 
 def hbm_stages(stage_ms, n, ncells):
-    """Achieved algorithmic bandwidth of each tree stage against 8 TB/s."""
+    """Achieved algorithmic bandwidth of each tree stage of one system against 8 TB/s."""
+    per_particle = {**HBM_B_PER_PARTICLE, **(HBM_B_RADIX if n > BUCKET_SORT_MAX else {})}
     out = {}
-    for k, bp in HBM_B_PER_PARTICLE.items():
+    for k, bp in per_particle.items():
         ms = stage_ms[k] + (stage_ms["mac_prep"] if k == "multipoles" else 0.0)
         b = bp * n + HBM_B_PER_CELL.get(k, 0) * ncells
         gbs = b / (ms * 1e-3) / 1e9
