@@ -358,9 +358,12 @@ mibh_status mibh_sph_density(mibh_ctx *ctx, const float *d_h, float *d_rho, uint
  *   MIBH_EXPORT_FEATURES float32 [ngroups][8] work-estimator features (mibh_group_features)
  *   MIBH_EXPORT_PREDICTIONS float32 [ngroups] estimator output of the last compute_forces
  *                                         with MIBH_ORDER_ESTIMATOR
- *   MIBH_EXPORT_QUEUE   uint32 [ngroups]  group indices in the order the last walk took them
- *                                         (ESTATE when that walk used Morton order; after an
- *                                         active walk the visited groups first, in Morton order)
+ *   MIBH_EXPORT_QUEUE   uint32 [ngroups]  group indices in the order of the last walk's queue:
+ *                                         by work, or after an active walk the visited groups,
+ *                                         then the others, both in Morton order (a tree of more
+ *                                         than 65536 particles is walked with the end of each
+ *                                         XCD's share by particle count; the export does not
+ *                                         show that).  ESTATE when the walk used Morton order
  *   MIBH_EXPORT_LSIDE   float64 [ncells]  l' = max(cell side, 2 * largest per-axis distance of
  *                                         a particle from the cell's geometric centre); the
  *                                         MAC uses r_open = l'/theta + delta (l' = side unless
