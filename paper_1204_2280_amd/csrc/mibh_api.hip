@@ -169,6 +169,7 @@ size_t layout(int64_t n_max, const mibh_params &p, char *base, Buffers *b) {
     t.pc_cap = (unsigned)p.pc_cap;
     t.pp_cap = (unsigned)p.pp_cap;
     t.max_systems = (unsigned)p.max_systems;
+    t.group_cap = (unsigned)p.group_cap;
     if (b) *b = t;
     return off;
 }

@@ -267,7 +267,7 @@ struct Buffers {
     uint32_t *ohist;        // [ORDER_BUCKETS][ORDER_BLOCKS] bucket counts of the queue order
     double *epart;          // energy partials [ENERGY_BLOCKS][2]
     unsigned cap_cells, n_max, ntiles_max, nblk_max;
-    unsigned walk_waves, pc_cap, pp_cap, max_systems;
+    unsigned walk_waves, pc_cap, pp_cap, max_systems, group_cap;
 };
 
 // System of sorted or input position i: the s with sys_off[s] <= i < sys_off[s+1].

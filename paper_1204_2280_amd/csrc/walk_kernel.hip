@@ -681,9 +681,9 @@ __global__ __launch_bounds__(64 * NW, 4) void k_walk(WalkArgs a) {
 // contiguous unless groups of deeper levels sit between them, so few entries
 // compete (a wave's first entry tries without a look at the entry before: a
 // claiming kernel of its own, which had that, took 4.5 us more).
-// With `gorder` the kernel also (without ANCHORS: only) places the queue's groups: each eighth's window by
-// particle count, largest first,
-// in the old order within a count.  Every workgroup adds up the counts of its
+// With `gorder` the kernel also (without ANCHORS: only) places the queue's groups:
+// each eighth's window by particle count, largest first, in the old order within a
+// count.  Every workgroup adds up the counts of its
 // eighths' window blocks; the ranks inside a block come from ballots, so the order
 // is the same on every run.
 template <bool ANCHORS>
@@ -998,20 +998,31 @@ __global__ __launch_bounds__(PREFIX_THREADS) void k_walk_prefix(WalkArgs a, unsi
     }
 }
 
-// Waves per group for a tree of n particles.  A chip full of groups wants one:
-// the waves that wait while the first builds the lists hold registers that
-// another group's wave could use.  With few groups the heaviest one sets the
-// time.  Walk stage with 1 / 2 / 4 waves per group (Plummer sphere, theta 0.75,
-// us): n = 1000 96 / 66 / 52, 20000 195 / 131 / 121, 32768 209 / 148 / 146,
-// 65536 260 / 217 / 229, 131072 390 / 370 / 415, 200000 480 / 481 / 555, 300007
-// 617 / 636 / 746, 2^20 1513 / 1731 / 2334.  The results are the same bits.  With
-// the queue's end by size one wave gains more than two, so the second line lies
-// between where these meet at theta 0.75 (115000) and 0.5 (128000): with one wave
-// and with two, us, 100003 278 / 483 and 265 / 446, 125000 278 / 548 and 298 / 522,
-// 140000 288 / 562 and 318 / 568, 160000 303 / 577 and 354 / 638.  Eight waves
-// against four, theta 0.75, us with the anchor pass: 1000 47.8 / 50.1, 3000 63.2 /
-// 67.8, 6000 77.3 / 83.9, 10000 106 / 88.
-int walk_group_waves(unsigned n) { return n <= 8192u ? 8 : n <= 32768u ? 4 : n <= 122880u ? 2 : 1; }
+// Waves per group for a tree of n particles in groups of up to `cap`.  A chip full of
+// groups wants one: the waves that wait while the first builds the lists hold
+// registers that another group's wave could use.  With few groups the heaviest one
+// sets the time.  Groups of up to 64, walk stage with 1 / 2 / 4 waves per group
+// (Plummer sphere, theta 0.75, us): n = 1000 96 / 66 / 52, 20000 195 / 131 / 121,
+// 32768 209 / 148 / 146, 65536 260 / 217 / 229, 131072 390 / 370 / 415, 200000 480 /
+// 481 / 555, 300007 617 / 636 / 746, 2^20 1513 / 1731 / 2334.  The results are the
+// same bits.  With the queue's end by size one wave gains more than two, so the
+// second line lies between where these meet at theta 0.75 (115000) and 0.5 (128000):
+// with one wave and with two, us, 100003 278 / 483 and 265 / 446, 125000 278 / 548
+// and 298 / 522, 140000 288 / 562 and 318 / 568, 160000 303 / 577 and 354 / 638.
+// Eight waves against four, theta 0.75, us with the anchor pass: 1000 47.8 / 50.1,
+// 3000 63.2 / 67.8, 6000 77.3 / 83.9, 10000 106 / 88.
+// Smaller groups are more (they hold about 0.27 cap + 0.7 particles), so the lines
+// are taken at m, the particles that make as many groups of up to 64; and a group of
+// few particles leaves the further waves little, so the lines come sooner.  Forces,
+// theta 0.5, us, with 1 / 2 / 4 / 8 waves: cap 32, n = 5000 178 / 92 / 84 / 110, 20000
+// 262 / 180 / 223 / 346, 50000 342 / 331 / 476, 100003 395 / 506; cap 16, 5000 138 /
+// 87 / 81 / 130, 10000 163 / 135 / 165, 20000 191 / 213 / 338 (a cube 113 / 79 / 117);
+// cap 8, 2000 106 / 54 / 55 / 76, 10000 149 / 136 / 210, 20000 206 / 251 / 430; cap 1,
+// 1000 105 / 58 / 59 / 83, 2000 111 / 68 / 100, 5000 162 / 185 / 303.
+int walk_group_waves(unsigned n, unsigned cap) {
+    const unsigned long long m = 67ull * n / (cap + 3u);
+    return m <= 8192u ? 8 : m <= 15360u + 272u * cap ? 4 : m <= 73728u + 768u * cap ? 2 : 1;
+}
 
 // As many workgroups as the launch parameter's waves have spill stacks.  Of 4096
 // workgroups of 2, 4 or 8 waves the chip holds a part at once; the
@@ -1090,7 +1101,7 @@ hipError_t launch_walk(const Buffers &b, unsigned n, unsigned nsys, float eps2, 
                            &b.hdr->anchor_count, b.alist, &b.hdr->pool_head, b.arec, b.pool, b.pool_cap, b.pscr,
                            &b.hdr->anchor_fail);
     }
-    const int nw = walk_group_waves(n);
+    const int nw = walk_group_waves(n, b.group_cap);
     if (precision == 2) launch_walk_waves<2>(a, shared, nw, b.walk_waves, s);
     else if (precision == 1) launch_walk_waves<1>(a, shared, nw, b.walk_waves, s);
     else launch_walk_waves<0>(a, shared, nw, b.walk_waves, s);
