@@ -124,9 +124,16 @@ size_t layout(int64_t n_max, const mibh_params &p, char *base, Buffers *b) {
     t.blkcnt = (uint32_t *)take(4 * NCOUNTERS * nblk);
     t.blkoff = (uint32_t *)take(4 * NCOUNTERS * nblk);
     t.ctot = (uint32_t *)take(4 * NCOUNTERS);
-    size_t nranges = 0;  // of the multipole pass: chunks, then one in MP_FAN until one is left
-    for (size_t r = (n + MP_CHUNK - 1) / MP_CHUNK; r > 1; r = (r + MP_FAN - 1) / MP_FAN) nranges += r;
-    t.mlist = (uint32_t *)take(4 * KEY_LEVELS * std::max<size_t>(nranges, 1));
+    // ranges of the multipole pass: chunks (of one size or another up to n_max), then
+    // one in MP_FAN until one is left
+    size_t nranges = 1;
+    for (size_t top : {(size_t)MP_SMALL_MAX, (size_t)MP_FINE_MAX, n}) {
+        const size_t m = std::min(n, top), chunk = multipole_chunk((unsigned)m, (unsigned)p.ncrit);
+        size_t sum = 0;
+        for (size_t r = (m + chunk - 1) / chunk; r > 1; r = (r + MP_FAN - 1) / MP_FAN) sum += r;
+        nranges = std::max(nranges, sum);
+    }
+    t.mlist = (uint32_t *)take(4 * KEY_LEVELS * nranges);
     t.topo = (uint4 *)take(16 * cap_cells);
     t.mp = (double *)take(80 * cap_cells);
     t.delta = (double *)take(8 * cap_cells);
@@ -169,6 +176,7 @@ size_t layout(int64_t n_max, const mibh_params &p, char *base, Buffers *b) {
     t.pc_cap = (unsigned)p.pc_cap;
     t.pp_cap = (unsigned)p.pp_cap;
     t.max_systems = (unsigned)p.max_systems;
+    t.ncrit = (unsigned)p.ncrit;
     t.group_cap = (unsigned)p.group_cap;
     if (b) *b = t;
     return off;

@@ -32,8 +32,22 @@ constexpr int SORT_TILE = SORT_THREADS * SORT_ITEMS;
 #endif
 constexpr int BUILD_THREADS = MIBH_BUILD_THREADS;
 constexpr int MAX_WINDOW = 64;          // largest ncrit and group_cap (a build wave's window reach)
-constexpr unsigned MP_CHUNK = 2048;     // particles per workgroup of the multipole pass
-constexpr unsigned MP_FAN = 64;         // ranges per workgroup of its merge launches
+constexpr unsigned MP_FAN = 64;         // ranges per workgroup of the multipole pass' merge launches
+// Particles per workgroup of the multipole pass.  Smaller chunks reach more compute
+// units and have shorter chains of rounds, but more cells that leave them, whose
+// merges take about 10 us for every MP_FAN chunks: so 1024 while one merge is enough
+// (20000 particles, us: 2048 38, 1024 31, 512 31; 45000 with 1024 and two merges:
+// a cube 28 against 26).  Leaves of few particles make many cells: with ncrit 1, us,
+// 2048 / 1024 / 512: 3000 87 / 65 / 41, 20000 96 / 69 / 47, 100003 105 / 86 / 87,
+// 300007 133 / 112 / -, 2^20 243 / 257 / 250; with ncrit 4 3000 45 / 40 / 32, 20000 52 /
+// 42 / 34, 100003 57 / 55 / 66.
+constexpr unsigned MP_SMALL_MAX = 512u * MP_FAN, MP_FINE_MAX = 1u << 19;
+__host__ inline unsigned multipole_chunk(unsigned n, unsigned ncrit) {
+    if (n <= 1024u) return 1024;
+    if (n <= 2048u) return ncrit < 3u ? 512 : 2048;
+    if (n <= MP_SMALL_MAX) return ncrit < 8u ? 512 : 1024;
+    return n <= MP_FINE_MAX && ncrit < 3u ? 1024 : 2048;
+}
 constexpr int BBOX_BLOCKS = 1024;
 constexpr int ENERGY_BLOCKS = 1024;
 constexpr int ENERGY_THREADS = 256;
@@ -267,7 +281,7 @@ struct Buffers {
     uint32_t *ohist;        // [ORDER_BUCKETS][ORDER_BLOCKS] bucket counts of the queue order
     double *epart;          // energy partials [ENERGY_BLOCKS][2]
     unsigned cap_cells, n_max, ntiles_max, nblk_max;
-    unsigned walk_waves, pc_cap, pp_cap, max_systems, group_cap;
+    unsigned walk_waves, pc_cap, pp_cap, max_systems, ncrit, group_cap;
 };
 
 // System of sorted or input position i: the s with sys_off[s] <= i < sys_off[s+1].

@@ -909,10 +909,12 @@ __device__ __forceinline__ void leaf_cell(const CellBuffers &a, unsigned c, unsi
     };
 #pragma unroll 4
     for (unsigned j = 0; j < nl; j++) first_pass(sp[j]);
+#pragma unroll 4
     for (unsigned j = nl; j < cnt; j++) first_pass(gp[j]);
     for (int k = 0; k < 3; k++) com[k] = M > 0.0 ? cm[k] / M : centre[k];
 #pragma unroll 4
     for (unsigned j = 0; j < nl; j++) second_pass(sp[j]);
+#pragma unroll 4
     for (unsigned j = nl; j < cnt; j++) second_pass(gp[j]);
     double *o = a.mp + 10 * (size_t)c;
     o[0] = M;
@@ -930,15 +932,16 @@ __device__ __forceinline__ void leaf_cell(const CellBuffers &a, unsigned c, unsi
 // An internal cell: (c, first child, system << 16 | level << 8 | children, first particle).
 __device__ __forceinline__ uint4 cell_entry(unsigned c, const uint4 &t) { return make_uint4(c, t.z, t.w, t.x); }
 
-// Internal cell of entry e, its children done: the children's values are
-// loaded together, then combined in child order.
+// Internal cell of entry e, its children (NJ at most) done: the children's values
+// are loaded together, then combined in child order.
+template <unsigned NJ>
 __device__ __forceinline__ void internal_cell(const CellBuffers &a, const Octet &o, const uint4 &e) {
 #pragma clang fp contract(off)
     const unsigned nch = e.z & 255u;
-    double Mc[8], xa[8], xb[8], Sc[8];
-    float bc[8];
+    double Mc[NJ], xa[NJ], xb[NJ], Sc[NJ];
+    float bc[NJ];
 #pragma unroll
-    for (unsigned j = 0; j < 8; j++) {
+    for (unsigned j = 0; j < NJ; j++) {
         const unsigned k = e.y + min(j, nch - 1u);  // the last child again: its values are not used
         const double *m = a.mp + 10 * (size_t)k;
         Mc[j] = m[0];
@@ -952,7 +955,7 @@ __device__ __forceinline__ void internal_cell(const CellBuffers &a, const Octet 
     double M = 0.0, cm = 0.0, S = 0.0;
     float box = bc[0];
 #pragma unroll
-    for (unsigned j = 0; j < 8; j++) {
+    for (unsigned j = 0; j < NJ; j++) {
         const bool in = j < nch;
         const double M1 = M + Mc[j], c1 = fma(Mc[j], xa[j], cm);
         M = in ? M1 : M;
@@ -968,7 +971,7 @@ __device__ __forceinline__ void internal_cell(const CellBuffers &a, const Octet 
     const double com = oct_shfl(own, o.ax);
     const double ca = oct_shfl(own, o.ma), cb = oct_shfl(own, o.mb);
 #pragma unroll
-    for (unsigned j = 0; j < 8; j++) {
+    for (unsigned j = 0; j < NJ; j++) {
         const double ea = xa[j] - ca, eb = xb[j] - cb;
         const double S1 = S + (Sc[j] + (Mc[j] * ea) * eb);
         S = j < nch ? S1 : S;
@@ -977,6 +980,33 @@ __device__ __forceinline__ void internal_cell(const CellBuffers &a, const Octet 
     m[o.q < 6u ? 4u + o.q : 0u] = o.q < 6u ? S : M;
     m[1 + o.ax] = com;
     a.cbox[6 * (size_t)e.x + o.qb] = box;
+}
+
+// A cell with one child, one thread: the same sums.  Above points that coincide
+// there are chains of up to 19 of these.
+__device__ __forceinline__ void chain_cell(const CellBuffers &a, const uint4 &e) {
+#pragma clang fp contract(off)
+    const double *c = a.mp + 10 * (size_t)e.y;
+    const float *cb = a.cbox + 6 * (size_t)e.y;
+    double v[10], com[3];
+    float box[6];
+    for (int k = 0; k < 10; k++) v[k] = c[k];
+    for (int k = 0; k < 6; k++) box[k] = cb[k];
+    const double M = 0.0 + v[0];
+    for (int k = 0; k < 3; k++) com[k] = fma(v[0], v[1 + k], 0.0) / M;
+    if (!(M > 0.0))
+        for (unsigned ax = 0; ax < 3; ax++) cell_geometry(a, e.w, (e.z >> 8) & 255u, e.z >> 16, ax, com + ax);
+    const double d[3] = {v[1] - com[0], v[2] - com[1], v[3] - com[2]};
+    double *o = a.mp + 10 * (size_t)e.x;
+    o[0] = M;
+    for (int k = 0; k < 3; k++) o[1 + k] = com[k];
+    o[4] = 0.0 + (v[4] + (v[0] * d[0]) * d[0]);
+    o[5] = 0.0 + (v[5] + (v[0] * d[1]) * d[1]);
+    o[6] = 0.0 + (v[6] + (v[0] * d[2]) * d[2]);
+    o[7] = 0.0 + (v[7] + (v[0] * d[0]) * d[1]);
+    o[8] = 0.0 + (v[8] + (v[0] * d[0]) * d[2]);
+    o[9] = 0.0 + (v[9] + (v[0] * d[1]) * d[2]);
+    for (int k = 0; k < 6; k++) a.cbox[6 * (size_t)e.x + k] = box[k];
 }
 
 // The derived quantities of the internal cell of entry e, its moments done: one thread.
@@ -996,7 +1026,7 @@ __device__ __forceinline__ void derive_cell(const CellBuffers &a, const uint4 &e
     store_derived(a, e.x, l, centre, M, com, S, bn, bx);
 }
 
-// All cells in a few launches.  The particles are cut into chunks of MP_CHUNK,
+// All cells in a few launches.  The particles are cut into chunks (multipole_chunk),
 // whole build blocks; the cells of one level that start in a chunk are
 // consecutive (the build's block counts give their range), and all but the last
 // of them end in it.
@@ -1011,34 +1041,46 @@ __device__ __forceinline__ void derive_cell(const CellBuffers &a, const uint4 &e
 // What bounds it: the chain of levels, more than 1 us each (float64 sums and a
 // division, the barrier), so the quantities that no parent needs are derived
 // after the last level, and a cell's centre, which the moments need only of
-// massless cells, too.  A leaf pass and one launch per level (21 launches) took
-// 57 / 68 / 77 / 103 / 203 us at n = 1000 / 20000 / 100003 / 2^20 / 2^22; this
-// takes 20 / 41 / 46 / 74 / 162 us (with every cell's centre 21 / 43 / 50 / 81 /
-// 174; chunks of 1024 then 21 / 41 / 60 / 88 / 196; one workgroup for all listed
-// cells instead of MP_FAN-way merges: 567 us at 2^22).  A chunk's moments kept in
-// LDS for the parents change nothing up to 2^19 particles and take 85 / 217 us at
-// 2^20 / 2^22: one workgroup per compute unit.
+// massless cells, too.  A leaf pass and one launch per level (21 launches) took,
+// with the launching call, 60-80 / 67-84 / 70-85 / 111 / 189 us at n = 1000 / 20000 /
+// 100003 / 2^20 / 2^22 (Plummer sphere, ncrit 16); this takes 16 / 31 / 39 / 66 / 139
+// (one workgroup for all listed cells instead of MP_FAN-way merges: 567 us at 2^22).
+// A chunk's moments kept in LDS for the parents change nothing up to 2^19 particles
+// and take 85 / 217 us at 2^20 / 2^22: one workgroup per compute unit.
+// Deep trees are bound by the number of cells: 24 particles at each of n / 24 points
+// are a chain of 16 cells with one child each per point.  With eight lanes for each
+// of those, and 8 rounds of loads, 152 / 231 / 664 us at 100003 / 2^20 / 2^22; with one
+// thread for each (chain_cell) 69 / 120 / 321 (one launch per level: 80 / 134 / 343).
 constexpr unsigned MP_THREADS = 256;
 constexpr unsigned MP_OCTS = MP_THREADS / OCT;
-constexpr unsigned MP_CELLS = 512;  // internal cells of a chunk listed in LDS (more: the level ranges are walked)
+constexpr unsigned MP_MERGE_THREADS = 512;
+// internal cells of a chunk listed in LDS as they are met (more: some levels at a
+// time): with chunks of 2048, room for four workgroups per compute unit
+constexpr unsigned MP_CELLS = 512;
 constexpr unsigned MP_NONE = 0xffffffffu;
-static_assert(MP_CHUNK % BUILD_THREADS == 0, "chunks are whole build blocks");
 
-__global__ __launch_bounds__(MP_THREADS, 3) void k_multipole_chunk(const Header *__restrict__ hdr, CellBuffers a,
+template <unsigned CHUNK>
+__global__ __launch_bounds__(MP_THREADS, 4) void k_multipole_chunk(const Header *__restrict__ hdr, CellBuffers a,
                                                                    const uint32_t *__restrict__ blkoff, unsigned nblk,
                                                                    unsigned n, unsigned nchunks,
                                                                    uint32_t *__restrict__ out) {
-    __shared__ float4 s_p[MP_CHUNK];
-    __shared__ uint4 s_raw[MP_CELLS], s_int[MP_CELLS];  // internal cells as met, then by level
+    static_assert(CHUNK % BUILD_THREADS == 0, "chunks are whole build blocks");
+    static_assert(MP_CELLS <= CHUNK, "the list by level takes the particles' place");
+    static_assert(CHUNK <= 2048 && KEY_LEVELS < 32 && MAX_SYSTEMS <= 256, "11 + 8 + 5 + 4 bits of a packed cell");
+    __shared__ float4 s_p[CHUNK];                       // the particles, then the internal cells by level
+    // internal cells as met: number, first child, and first particle << 17 | system << 9 | level << 4 | children
+    __shared__ uint32_t s_raw[3][MP_CELLS];
     __shared__ unsigned short s_rank[MP_CELLS];         // their ranks in their levels
-    __shared__ unsigned s_lo[KEY_LEVELS + 1], s_hi[KEY_LEVELS + 1];  // cells of a level that start here
-    __shared__ unsigned s_pre[KEY_LEVELS + 2];          // their prefix sums
-    __shared__ unsigned s_cnt[KEY_LEVELS + 1], s_at[KEY_LEVELS + 1];  // internal cells of a level: number, place
+    __shared__ unsigned s_lo[KEY_LEVELS + 1];           // first cell of a level that starts here
+    __shared__ unsigned s_pre[KEY_LEVELS + 2];          // prefix sums of the numbers of these
+    __shared__ unsigned s_cnt[KEY_LEVELS + 1];          // internal cells of a level
+    __shared__ unsigned s_at[KEY_LEVELS + 1], s_end[KEY_LEVELS + 1];  // their places in the list by level
     __shared__ unsigned s_nint;
-    constexpr unsigned PB = MP_CHUNK / BUILD_THREADS;
+    uint4 *s_int = reinterpret_cast<uint4 *>(s_p);  // once the leaves are done
+    constexpr unsigned PB = CHUNK / BUILD_THREADS;
     if (hdr->flags & FLAG_CELLCAP) return;
     const unsigned t = threadIdx.x;
-    const unsigned b = blockIdx.x * MP_CHUNK, e = min(b + MP_CHUNK, n);
+    const unsigned b = blockIdx.x * CHUNK, e = min(b + CHUNK, n);
     if (t < 64u) {  // the first wave: ranges of the levels and their prefix sums
         const bool lev = t <= (unsigned)KEY_LEVELS;
         const unsigned l = lev ? t : 0u;
@@ -1050,7 +1092,6 @@ __global__ __launch_bounds__(MP_THREADS, 3) void k_multipole_chunk(const Header 
         const unsigned inc = wave_incl_scan(cnt);
         if (lev) {
             s_lo[l] = lo;
-            s_hi[l] = hi;
             s_pre[l] = inc - cnt;
             s_cnt[l] = 0;
             if (out && l < (unsigned)KEY_LEVELS) out[l * nchunks + blockIdx.x] = MP_NONE;
@@ -1072,12 +1113,14 @@ __global__ __launch_bounds__(MP_THREADS, 3) void k_multipole_chunk(const Header 
         const uint4 tc = a.topo[c];
         if ((tc.w & 255u) == 0) {
             leaf_cell(a, c, tc.x, tc.y, l, tc.w >> 16, s_p + (tc.x - b), min(tc.y, e - tc.x));
-        } else if (tc.x + tc.y > b + MP_CHUNK) {
+        } else if (tc.x + tc.y > b + CHUNK) {
             out[l * nchunks + blockIdx.x] = c;  // leaves the chunk: there is more than one, so a list
         } else {
             const unsigned r = atomicAdd(&s_cnt[l], 1u), k = atomicAdd(&s_nint, 1u);
             if (k < MP_CELLS) {
-                s_raw[k] = cell_entry(c, tc);
+                s_raw[0][k] = c;
+                s_raw[1][k] = tc.z;
+                s_raw[2][k] = (tc.x - b) << 17 | (tc.w >> 16) << 9 | l << 4 | (tc.w & 15u);
                 s_rank[k] = (unsigned short)r;
             }
         }
@@ -1085,51 +1128,90 @@ __global__ __launch_bounds__(MP_THREADS, 3) void k_multipole_chunk(const Header 
     __syncthreads();
     const unsigned nint = s_nint;
     const bool listed = nint <= MP_CELLS;
-    if (t < 64u) {
-        const unsigned cnt = t <= (unsigned)KEY_LEVELS ? s_cnt[t] : 0u;
-        const unsigned inc = wave_incl_scan(cnt);
-        if (t <= (unsigned)KEY_LEVELS) s_at[t] = inc - cnt;
-    }
-    __syncthreads();
-    if (listed)
-        for (unsigned k = t; k < nint; k += MP_THREADS) s_int[s_at[(s_raw[k].z >> 8) & 255u] + s_rank[k]] = s_raw[k];
-    __syncthreads();
     const Octet o = octet();
     const unsigned oct = t / OCT;
-    for (int l = KEY_LEVELS - 1; l >= 0; l--) {
-        const unsigned cnt = s_cnt[l];
-        if (cnt == 0) continue;  // the same for the whole workgroup
-        if (listed) {
+    if (listed) {
+        if (t < 64u) {
+            const unsigned cnt = t <= (unsigned)KEY_LEVELS ? s_cnt[t] : 0u;
+            const unsigned inc = wave_incl_scan(cnt);
+            if (t <= (unsigned)KEY_LEVELS) s_at[t] = inc - cnt;
+        }
+        __syncthreads();
+        for (unsigned k = t; k < nint; k += MP_THREADS) {
+            const unsigned v = s_raw[2][k], l = (v >> 4) & 31u;
+            s_int[s_at[l] + s_rank[k]] =
+                make_uint4(s_raw[0][k], s_raw[1][k], ((v >> 9) & 255u) << 16 | l << 8 | (v & 15u), b + (v >> 17));
+        }
+        __syncthreads();
+        for (int l = KEY_LEVELS - 1; l >= 0; l--) {
+            const unsigned cnt = s_cnt[l];
+            if (cnt == 0) continue;  // the same for the whole workgroup
             const unsigned at = s_at[l];
-            for (unsigned i = oct; i < cnt; i += MP_OCTS) internal_cell(a, o, s_int[at + i]);
-        } else {
-            for (unsigned c = s_lo[l] + oct; c < s_hi[l]; c += MP_OCTS) {
-                const uint4 tc = a.topo[c];
-                if ((tc.w & 255u) != 0 && tc.x + tc.y <= b + MP_CHUNK) internal_cell(a, o, cell_entry(c, tc));
+            for (unsigned i = oct; i < cnt; i += MP_OCTS) internal_cell<8>(a, o, s_int[at + i]);
+            __syncthreads();
+        }
+        // the derived quantities at the end, off the chain of the levels
+        for (unsigned k = t; k < nint; k += MP_THREADS) derive_cell(a, s_int[k]);
+        return;
+    }
+    // More cells than that list holds: gathered again from their ranges, as many
+    // levels at a time as fit the particles' place (one at least: an internal cell has
+    // two particles or more), those with one child first in each level.  Where points
+    // coincide most cells are such, and along a line most have two children at most:
+    // the octets of a wave take the short form where all of theirs have.
+    for (int l1 = KEY_LEVELS; l1 > 0;) {
+        int l0 = l1;
+        unsigned sum = 0;
+        while (l0 > 0 && sum + s_cnt[l0 - 1] <= CHUNK) sum += s_cnt[--l0];  // the same for the whole workgroup
+        if (t == 0) {
+            unsigned at = 0;
+            for (int l = l1 - 1; l >= l0; l--) {
+                s_at[l] = at;
+                at += s_cnt[l];
+                s_end[l] = at;
             }
         }
         __syncthreads();
-    }
-    // the derived quantities at the end, off the chain of the levels
-    if (listed) {
-        for (unsigned k = t; k < nint; k += MP_THREADS) derive_cell(a, s_int[k]);
-    } else {
-        for (int l = KEY_LEVELS - 1; l >= 0; l--)
-            for (unsigned c = s_lo[l] + t; c < s_hi[l]; c += MP_THREADS) {
-                const uint4 tc = a.topo[c];
-                if ((tc.w & 255u) != 0 && tc.x + tc.y <= b + MP_CHUNK) derive_cell(a, cell_entry(c, tc));
+        for (unsigned i = s_pre[l0] + t; i < s_pre[l1]; i += MP_THREADS) {
+            unsigned l = l0, h = l1;  // s_pre[l] <= i < s_pre[h]
+            while (h - l > 1) {
+                const unsigned mid = (l + h) >> 1;
+                if (s_pre[mid] <= i) l = mid; else h = mid;
             }
+            const unsigned c = s_lo[l] + (i - s_pre[l]);
+            const uint4 tc = a.topo[c];
+            const unsigned nch = tc.w & 255u;
+            if (nch != 0 && tc.x + tc.y <= b + CHUNK)
+                s_int[nch == 1 ? atomicAdd(&s_at[l], 1u) : atomicSub(&s_end[l], 1u) - 1u] = cell_entry(c, tc);
+        }
+        __syncthreads();
+        unsigned at = 0;
+        for (int l = l1 - 1; l >= l0; l--) {
+            const unsigned one = s_at[l], end = at + s_cnt[l];  // cells with one child end at `one` now
+            if (at == end) continue;
+            for (unsigned i = at + t; i < one; i += MP_THREADS) chain_cell(a, s_int[i]);
+            for (unsigned i = one + oct; i < end; i += MP_OCTS) {
+                const uint4 e = s_int[i];
+                if (__ballot((e.z & 255u) > 2u)) internal_cell<8>(a, o, e);
+                else internal_cell<2>(a, o, e);
+            }
+            __syncthreads();
+            at = end;
+        }
+        for (unsigned k = t; k < sum; k += MP_THREADS) derive_cell(a, s_int[k]);
+        __syncthreads();  // the list is free again
+        l1 = l0;
     }
 }
 
 // in[level][nin]: listed cells of the ranges below, MP_FAN of them per
 // workgroup; `span`: particles of this workgroup's range; out as above
-__global__ __launch_bounds__(MP_THREADS) void k_multipole_merge(const Header *__restrict__ hdr, CellBuffers a,
+__global__ __launch_bounds__(MP_MERGE_THREADS) void k_multipole_merge(const Header *__restrict__ hdr, CellBuffers a,
                                                                 const uint32_t *__restrict__ in, unsigned nin,
                                                                 unsigned long long span, unsigned nout,
                                                                 uint32_t *__restrict__ out) {
     __shared__ uint4 s_int[KEY_LEVELS][MP_FAN];
-    __shared__ unsigned s_cnt[KEY_LEVELS];
+    __shared__ unsigned s_cnt[KEY_LEVELS];  // cells of the level; in the high half those with more than one child
     if (hdr->flags & FLAG_CELLCAP) return;
     const unsigned t = threadIdx.x;
     const unsigned r0 = blockIdx.x * MP_FAN;
@@ -1139,42 +1221,47 @@ __global__ __launch_bounds__(MP_THREADS) void k_multipole_merge(const Header *__
         if (out) out[t * nout + blockIdx.x] = MP_NONE;
     }
     __syncthreads();
-    for (unsigned i = t; i < (unsigned)KEY_LEVELS * MP_FAN; i += MP_THREADS) {
+    for (unsigned i = t; i < (unsigned)KEY_LEVELS * MP_FAN; i += MP_MERGE_THREADS) {
         const unsigned l = i / MP_FAN, k = r0 + i % MP_FAN;
         const unsigned c = k < nin ? in[l * nin + k] : MP_NONE;
         if (c != MP_NONE) {
             const uint4 tc = a.topo[c];
             if (tc.x + (unsigned long long)tc.y > end) out[l * nout + blockIdx.x] = c;
-            else s_int[l][atomicAdd(&s_cnt[l], 1u)] = cell_entry(c, tc);
+            else s_int[l][atomicAdd(&s_cnt[l], (tc.w & 255u) > 1u ? 0x10001u : 1u) & 0xffffu] = cell_entry(c, tc);
         }
     }
     __syncthreads();
     const Octet o = octet();
     const unsigned oct = t / OCT;
     for (int l = KEY_LEVELS - 1; l >= 0; l--) {
-        const unsigned cnt = s_cnt[l];
+        const unsigned cnt = s_cnt[l] & 0xffffu, wide = s_cnt[l] >> 16;
         if (cnt == 0) continue;  // the same for the whole workgroup
-        for (unsigned i = oct; i < cnt; i += MP_OCTS) internal_cell(a, o, s_int[l][i]);
+        if (wide) {
+            for (unsigned i = oct; i < cnt; i += MP_MERGE_THREADS / OCT) internal_cell<8>(a, o, s_int[l][i]);
+        } else {
+            for (unsigned i = t; i < cnt; i += MP_MERGE_THREADS) chain_cell(a, s_int[l][i]);
+        }
         __syncthreads();
     }
-    for (unsigned i = t; i < (unsigned)KEY_LEVELS * MP_FAN; i += MP_THREADS)
-        if (i % MP_FAN < s_cnt[i / MP_FAN]) derive_cell(a, s_int[i / MP_FAN][i % MP_FAN]);
+    for (unsigned i = t; i < (unsigned)KEY_LEVELS * MP_FAN; i += MP_MERGE_THREADS)
+        if (i % MP_FAN < (s_cnt[i / MP_FAN] & 0xffffu)) derive_cell(a, s_int[i / MP_FAN][i % MP_FAN]);
 }
 
 hipError_t launch_multipoles(const Buffers &b, unsigned n, unsigned nsys, hipStream_t s) {
     const CellBuffers a = {b.cube, b.topo, b.keys[0], b.spos, b.mp, b.delta, b.cbox, b.lside,
                            b.cmac, b.ceval};
     const unsigned nblk = (n + BUILD_THREADS - 1) / BUILD_THREADS;
-    unsigned nr = (n + MP_CHUNK - 1) / MP_CHUNK;
+    const unsigned chunk = multipole_chunk(n, b.ncrit);
+    unsigned nr = (n + chunk - 1) / chunk;
     uint32_t *list = b.mlist;
-    unsigned long long span = MP_CHUNK;
-    hipLaunchKernelGGL(k_multipole_chunk, dim3(nr), dim3(MP_THREADS), 0, s, b.hdr, a, b.blkoff, nblk, n, nr,
-                       nr > 1 ? list : nullptr);
+    unsigned long long span = chunk;
+    auto k = chunk == 512 ? k_multipole_chunk<512> : chunk == 1024 ? k_multipole_chunk<1024> : k_multipole_chunk<2048>;
+    hipLaunchKernelGGL(k, dim3(nr), dim3(MP_THREADS), 0, s, b.hdr, a, b.blkoff, nblk, n, nr, nr > 1 ? list : nullptr);
     while (nr > 1) {
         const unsigned nout = (nr + MP_FAN - 1) / MP_FAN;
         uint32_t *next = list + (size_t)KEY_LEVELS * nr;
         span *= MP_FAN;
-        hipLaunchKernelGGL(k_multipole_merge, dim3(nout), dim3(MP_THREADS), 0, s, b.hdr, a, list, nr, span, nout,
+        hipLaunchKernelGGL(k_multipole_merge, dim3(nout), dim3(MP_MERGE_THREADS), 0, s, b.hdr, a, list, nr, span, nout,
                            nout > 1 ? next : nullptr);
         list = next;
         nr = nout;
