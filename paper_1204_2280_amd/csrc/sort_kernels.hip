@@ -42,7 +42,12 @@ constexpr unsigned TILE_ITEMS = 8;       // particles per thread in the counting
 constexpr unsigned BS_THREADS = 256, BS_WAVES = 4;
 constexpr unsigned BS_VT = SORT_BUCKET / (BS_THREADS * ITEMS);  // places per thread in a full bucket
 static_assert(BS_VT == 2, "a bucket's sort takes one or two places per thread");
-constexpr unsigned BS_RUN = 24;          // longest run of equal leading bits that one thread puts in order
+// Longest run of equal leading bits that one thread puts in order, its dependent
+// loads one after the other.  Builds with 2 / 4 / 8 / 24, us: 2^22 particles at n / 24
+// points 600 / 591 / 607 / 868 (radix sort 687), along a line (4 to a key, up to 14)
+// 555 / 569 / 611 / 678 (609), 50 within a few grid cells of each of n / 50 points 595 /
+// 588 / 532 / 533 (675); 3000 particles three to a point 88 / 70 / 70 / 70 (150).
+constexpr unsigned BS_RUN = 8;
 
 // Places in the LDS arrays, one in nine left free: neighbouring threads work 8
 // or 16 elements apart, and such strides would meet in few banks.
@@ -216,6 +221,47 @@ __device__ __forceinline__ void order_runs(uint64_t *sv, unsigned m, const Words
     }
 }
 
+// Sorts the words in sv[0, m) again, those whose key bits agree by rest(p) (at most
+// 64 - 2 tb bits: what the key bits leave out, then the index), then by place.  The
+// words then hold the first place of their run, the rest, and the place.
+template <unsigned NT, unsigned VT, typename R>
+__device__ __forceinline__ void sort_runs(uint64_t *sv, unsigned m, const Words &wd, R rest) {
+    const unsigned active = (m + ITEMS - 1) / ITEMS;
+    uint64_t v[VT * ITEMS];
+#pragma unroll
+    for (unsigned x = 0; x < VT; x++) {
+        const unsigned r0 = (threadIdx.x + x * NT) * ITEMS;
+        uint64_t prev = 0;
+        unsigned lo = 0;
+#pragma unroll
+        for (unsigned u = 0; u < ITEMS; u++) {
+            const unsigned r = r0 + u;
+            uint64_t w = ~0ull;
+            if (r < m) {
+                const uint64_t d = sv[phys(r)] >> wd.tb;
+                if (u == 0) {  // the first word with these bits
+                    lo = 0;
+                    unsigned hi = r;
+                    while (lo < hi) {
+                        const unsigned mid = (lo + hi) >> 1;
+                        if (sv[phys(mid)] >> wd.tb < d) lo = mid + 1u; else hi = mid;
+                    }
+                } else if (d != prev) {
+                    lo = r;
+                }
+                prev = d;
+                const unsigned p = wd.place(sv[phys(r)]);
+                w = (uint64_t)lo << (64u - wd.tb) | rest(p) << wd.tb | p;
+            }
+            v[x * ITEMS + u] = w;
+        }
+    }
+    __syncthreads();
+    block_sort<NT, VT>(v, active, sv);
+}
+
+// A published 32-bit integer hash (two rounds of xor-shift and multiply, "lowbias32"
+// of C. Wellons' hash prospector, 2018).
 __device__ __forceinline__ unsigned mix32(unsigned v) {
     v ^= v >> 16;
     v *= 0x7feb352du;
@@ -291,38 +337,12 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void k_bucket_sample(
     for (unsigned u = 0; u < ITEMS; u++) k[u] = t < active ? wd.word(k[u], u * active + t) : ~0ull;
     block_sort<SAMPLE_THREADS, 1>(k, active, sv);
     // Places rise with the indices, so only words that leave key bits out can be
-    // out of order.  A run too long for one thread is put in order by all of
-    // them: each of its words counts the words that come before it.
+    // out of order.
     if (wd.sh > 0) {
         order_runs<SAMPLE_THREADS>(sv, m, wd, &s_long, key, index);
         __syncthreads();
-        if (s_long) {
-            unsigned at[ITEMS];
-#pragma unroll
-            for (unsigned u = 0; u < ITEMS; u++) {
-                const unsigned r = u * SAMPLE_THREADS + t;
-                at[u] = r;
-                k[u] = r < m ? sv[phys(r)] : ~0ull;
-                if (r >= m) continue;
-                unsigned lo = r, hi = r + 1u;
-                while (lo > 0 && sv[phys(lo - 1u)] >> wd.tb == k[u] >> wd.tb) lo--;
-                while (hi < m && sv[phys(hi)] >> wd.tb == k[u] >> wd.tb) hi++;
-                if (hi - lo <= BS_RUN) continue;
-                const unsigned p = wd.place(k[u]);
-                const uint64_t kp = key(p);
-                unsigned cnt = 0;
-                for (unsigned e = lo; e < hi; e++) {
-                    const unsigned pe = wd.place(sv[phys(e)]);
-                    cnt += before(key(pe), pe, kp, p) ? 1u : 0u;
-                }
-                at[u] = lo + cnt;
-            }
-            __syncthreads();
-#pragma unroll
-            for (unsigned u = 0; u < ITEMS; u++)
-                if (u * SAMPLE_THREADS + t < m) sv[phys(at[u])] = k[u];
-            __syncthreads();
-        }
+        if (s_long)
+            sort_runs<SAMPLE_THREADS, 1>(sv, m, wd, [&](unsigned p) { return (key(p) - wd.kmin) & ((1ull << wd.sh) - 1ull); });
     }
     if (sa.lists == 1u) {
         for (unsigned r = 1 + t; r < nb; r += SAMPLE_THREADS) {
@@ -684,55 +704,13 @@ __device__ __forceinline__ Words sort_piece(const BucketArgs &a, unsigned sys, u
     return wd;
 }
 
-// Sorts the words in sv again by every bit, least significant digit first: the
-// indices' distances from the smallest, then the keys'.
-template <bool DIRECT>
-__device__ __forceinline__ void sort_all_bits(const BucketArgs &a, unsigned q0, unsigned m, const Words &wd, uint64_t *sv,
-                                           uint64_t *s_mm) {
-    const unsigned active = (m + ITEMS - 1) / ITEMS, pmask = (1u << wd.tb) - 1u;
-    uint64_t xmin = ~0ull, xmax = 0;
-    for (unsigned j = threadIdx.x; j < m; j += BS_THREADS) {
-        const uint64_t x = bucket_index<DIRECT>(a, q0 + j);
-        xmin = min(xmin, x);
-        xmax = max(xmax, x);
-    }
-    block_minmax<BS_THREADS>(xmin, xmax, s_mm);
-    const int xbits = xmax > xmin ? 64 - __clzll((long long)(xmax - xmin)) : 0;
-    const int db = 64 - 2 * (int)wd.tb;  // bits of a digit: a word also holds the rank so far and the place
-    for (int at = 0; at < xbits + wd.kbits;) {
-        const bool by_key = at >= xbits;
-        const int bits = by_key ? min(db, xbits + wd.kbits - at) : min(db, xbits - at);
-        const uint64_t dmask = (1ull << bits) - 1ull;
-        uint64_t v[BS_VT * ITEMS];
-#pragma unroll
-        for (unsigned x = 0; x < BS_VT; x++) {
-            const unsigned t = threadIdx.x + x * BS_THREADS;
-#pragma unroll
-            for (unsigned u = 0; u < ITEMS; u++) {
-                const unsigned r = u * active + t;
-                uint64_t w = ~0ull;
-                if (t < active && r < m) {
-                    const unsigned p = at ? (unsigned)sv[phys(r)] & pmask : r;
-                    const uint64_t d =
-                        by_key ? (a.kin[q0 + p] - wd.kmin) >> (at - xbits) : (bucket_index<DIRECT>(a, q0 + p) - xmin) >> at;
-                    w = (d & dmask) << (2 * wd.tb) | (uint64_t)r << wd.tb | p;
-                }
-                v[x * ITEMS + u] = w;
-            }
-        }
-        __syncthreads();
-        block_sort<BS_THREADS, BS_VT>(v, active, sv);
-        at += bits;
-    }
-}
-
 // One workgroup per bucket.  What is sorted in LDS is one 64-bit word per
 // element (struct Words): at least 52 bits of key distance and the place.
-// Words that agree in those are then put in order by (key, index), each run by
-// one thread; a bucket with a run longer than BS_RUN (many particles at one
-// point) is sorted again by all bits of index and key, least significant digit
-// first, with the same sort, which a word's rank of the digit before makes
-// stable.
+// Words that agree in those are then put in order by (key, index): a short run by
+// one thread, and a bucket with a run longer than BS_RUN (particles that coincide
+// or lie close) by a second sort of words that hold the run and the index
+// in place of the key.  (Sorted by every digit of index and key instead, 2^22
+// particles at n / 40 points took 812 us for the build; now 595, the radix sort 677.)
 // BEGIN: the one workgroup of a one-bucket build also starts it.
 template <bool DIRECT, bool BEGIN>
 __global__ __launch_bounds__(BS_THREADS, BS_WAVES) void k_bucket_sort(BucketArgs a, BuildStart st) {
@@ -759,11 +737,19 @@ __global__ __launch_bounds__(BS_THREADS, BS_WAVES) void k_bucket_sort(BucketArgs
         if (t == 0) s_long = 0;
         const Words wd = m <= BS_THREADS * ITEMS ? sort_piece<DIRECT, 1>(a, sys, q0, m, sv, s_mm, s_box)
                                                  : sort_piece<DIRECT, BS_VT>(a, sys, q0, m, sv, s_mm, s_box);
-        order_runs<BS_THREADS>(sv, m, wd, &s_long, [&](unsigned p) { return a.kin[q0 + p]; },
-                               [&](unsigned p) { return bucket_index<DIRECT>(a, q0 + p); });
+        auto key = [&](unsigned p) { return a.kin[q0 + p]; };
+        auto index = [&](unsigned p) { return bucket_index<DIRECT>(a, q0 + p); };
+        // (places in input order need nothing where the words hold every key bit)
+        if (!DIRECT || wd.sh > 0) order_runs<BS_THREADS>(sv, m, wd, &s_long, key, index);
         __syncthreads();
         const bool all = s_long != 0;  // the same for the whole workgroup
-        if (all) sort_all_bits<DIRECT>(a, q0, m, wd, sv, s_mm);
+        if (all) {
+            static_assert(SORT_BUCKET <= 4096, "words leave out 8 key bits at most: 8 + 32 + 2 * 12 bits");
+            sort_runs<BS_THREADS, BS_VT>(sv, m, wd, [&](unsigned p) {
+                const uint64_t low = wd.sh > 0 ? (key(p) - wd.kmin) & ((1ull << wd.sh) - 1ull) : 0ull;
+                return low << 32 | index(p);
+            });
+        }
         tb = wd.tb;
         pmask = (1u << tb) - 1u;
         kmin = wd.kmin;
