@@ -79,33 +79,38 @@ __device__ __forceinline__ uint32_t compact3(uint64_t x) {
 }
 
 // First index j > i whose key differs from key i in the first `lev` octal
-// digits (n if none) in the sorted keys.  A round reads seven keys side by side and
-// cuts the range to an eighth: first at distances 64, 512, .. from i, then evenly
-// in what is left.  A chain of dependent reads, 0.4 us each, is what the search
-// costs: by doubling and halving the write kernel below took 10.4 / 14.0 / 25 us at
-// n = 1000 / 32768 / 2^20, by eighths 8.2 / 9.1 / 20 (60 and 62.6 at 2^22, which
-// bytes bound).
+// digits (n if none) in the sorted keys.  A round reads WAYS - 1 keys side by side
+// and cuts the range to a part in WAYS: first at distances 64 and up from i, then
+// evenly in what is left.  A chain of dependent reads, 0.4 us each, is what the
+// search costs where the chip is not full; in large trees it is the reads' bytes.
+// The write kernel below by doubling and halving / with 4 / with 8 ways, us: n =
+// 40000 13.6 / 9.3 / 8.6, 2^18 15.4 / 10.3 / 9.8, 2^19 17.3 / 12.8 / 12.6, 2^20 23.3 /
+// 19.3 / 19.4, 2^21 34.8 / 30.8 / 34.0, 2^22 59.2 / 56.2 / 63.4, 12 million 164 / 153 /
+// 177: 8 up to RUN_END_EIGHTHS particles, 4 beyond.
+constexpr unsigned RUN_END_EIGHTHS = 1u << 19;
+template <unsigned WAYS>
 __device__ __forceinline__ unsigned run_end(const uint64_t *__restrict__ keys, unsigned n, unsigned i,
                                             int lev) {
+    constexpr unsigned Q = WAYS - 1u, GROW = 21u / Q;  // the last of the first round's distances: 2^24 / 2^GROW
     // n is the end of i's system: keys of different systems are never compared
     if (lev == 0) return n;
     const int sh = 3 * (KEY_LEVELS - lev);
     const uint64_t p = keys[i] >> sh;
     unsigned lo = i, hi = n;  // lo is in the run, hi is not
-    unsigned first = 64, step = 0;
+    unsigned step = 0;
     do {
-        unsigned pos[7];
-        uint64_t k[7];
+        unsigned pos[Q];
+        uint64_t k[Q];
 #pragma unroll
-        for (unsigned q = 0; q < 7; q++) {
-            pos[q] = min(step ? lo + step * (q + 1u) : lo + (first << 3 * q), hi);
+        for (unsigned q = 0; q < Q; q++) {
+            pos[q] = min(step ? lo + step * (q + 1u) : lo + (64u << GROW * q), hi);
             k[q] = keys[min(pos[q], n - 1u)] >> sh;
         }
 #pragma unroll
-        for (unsigned q = 0; q < 7; q++) lo = pos[q] < hi && k[q] == p ? pos[q] : lo;
+        for (unsigned q = 0; q < Q; q++) lo = pos[q] < hi && k[q] == p ? pos[q] : lo;
 #pragma unroll
-        for (int q = 6; q >= 0; q--) hi = pos[q] > lo ? pos[q] : hi;
-        step = (hi - lo + 7u) / 8u;
+        for (int q = (int)Q - 1; q >= 0; q--) hi = pos[q] > lo ? pos[q] : hi;
+        step = (hi - lo + Q) / WAYS;
     } while (hi - lo > 1);
     return hi;
 }
@@ -608,7 +613,7 @@ static_assert(BUILD_PENDING >= (BUILD_THREADS / 64) * (KEY_LEVELS + 1), "one def
 // SCAN: up to 64 blocks, whose counts every block adds up itself (a wave per
 // counter and a lane per block: no launch between, 4.6 us).
 constexpr unsigned BUILD_SCAN_BLOCKS = 64;
-template <bool SCAN>
+template <bool SCAN, unsigned WAYS>
 __global__ __launch_bounds__(BUILD_THREADS) void k_build_write(
     const uchar4 *__restrict__ lvinfo, const uint64_t *__restrict__ keys, unsigned n, unsigned nsys,
     const uint32_t *__restrict__ sys_off, int gcap, const uint32_t *__restrict__ blkcnt,
@@ -708,7 +713,7 @@ __global__ __launch_bounds__(BUILD_THREADS) void k_build_write(
                 s_pext[k] = make_uint2(send, 0u);
                 if (l == glev) gpend = k + 1;
             } else {  // end inside the wave, or no room left to defer
-                const unsigned end = after ? i + (unsigned)__ffsll((long long)after) : run_end(keys, send, i, l);
+                const unsigned end = after ? i + (unsigned)__ffsll((long long)after) : run_end<WAYS>(keys, send, i, l);
                 if (idx < cap_cells) topo[idx] = make_uint4(i, end - i, cf, word);
                 if (l == glev) gend = end;
             }
@@ -721,11 +726,11 @@ __global__ __launch_bounds__(BUILD_THREADS) void k_build_write(
             const unsigned g = s_blk[NCOUNTERS - 1] + s_wpre[w][NCOUNTERS - 1] + rank_below(b);
             const unsigned gword = (sys << 16) | ((unsigned)glev << 8);
             if (info.w & 2) {
-                groups[g] = make_uint2(i, gword | min((unsigned)gcap, run_end(keys, send, i, KEY_LEVELS) - i));
+                groups[g] = make_uint2(i, gword | min((unsigned)gcap, run_end<WAYS>(keys, send, i, KEY_LEVELS) - i));
             } else if (gend == 0 && gpend) {
                 s_pext[gpend - 1].y = g + 1;  // written with its cell's end below
             } else {
-                groups[g] = make_uint2(i, gword | ((gend ? gend : run_end(keys, send, i, glev)) - i));
+                groups[g] = make_uint2(i, gword | ((gend ? gend : run_end<WAYS>(keys, send, i, glev)) - i));
             }
         }
     }
@@ -734,7 +739,7 @@ __global__ __launch_bounds__(BUILD_THREADS) void k_build_write(
     for (unsigned k = threadIdx.x; k < np; k += BUILD_THREADS) {
         const uint4 r = s_prec[k];
         const uint2 e = s_pext[k];
-        const unsigned end = run_end(keys, e.x, r.y, (int)((r.w >> 8) & 255u));
+        const unsigned end = run_end<WAYS>(keys, e.x, r.y, (int)((r.w >> 8) & 255u));
         if (r.x < cap_cells) topo[r.x] = make_uint4(r.y, end - r.y, r.z, r.w);
         if (e.y) groups[e.y - 1] = make_uint2(r.y, r.w | (end - r.y));
     }
@@ -768,14 +773,13 @@ hipError_t launch_build(const Buffers &b, unsigned n, unsigned nsys, int ncrit, 
     const uint64_t *keys = b.keys[0];
     hipLaunchKernelGGL(k_build_count, dim3(nblk), dim3(BUILD_THREADS), 0, s, b.cl, keys, n, nsys, b.sys_off,
                        ncrit, gcap, b.lvinfo, b.blkcnt, nblk);
-    if (nblk <= BUILD_SCAN_BLOCKS) {
-        hipLaunchKernelGGL(k_build_write<true>, dim3(nblk), dim3(BUILD_THREADS), 0, s, b.lvinfo, keys, n, nsys, b.sys_off,
-                           gcap, b.blkcnt, b.blkoff, b.ctot, nblk, b.hdr, b.topo, b.groups, b.cap_cells);
-    } else {
+    auto write = nblk <= BUILD_SCAN_BLOCKS ? k_build_write<true, 8>
+                 : n <= RUN_END_EIGHTHS    ? k_build_write<false, 8>
+                                           : k_build_write<false, 4>;
+    if (nblk > BUILD_SCAN_BLOCKS)
         hipLaunchKernelGGL(k_build_scan, dim3(NCOUNTERS), dim3(1024), 0, s, b.blkcnt, nblk, b.blkoff, b.ctot);
-        hipLaunchKernelGGL(k_build_write<false>, dim3(nblk), dim3(BUILD_THREADS), 0, s, b.lvinfo, keys, n, nsys, b.sys_off,
-                           gcap, b.blkcnt, b.blkoff, b.ctot, nblk, b.hdr, b.topo, b.groups, b.cap_cells);
-    }
+    hipLaunchKernelGGL(write, dim3(nblk), dim3(BUILD_THREADS), 0, s, b.lvinfo, keys, n, nsys, b.sys_off, gcap, b.blkcnt,
+                       b.blkoff, b.ctot, nblk, b.hdr, b.topo, b.groups, b.cap_cells);
     const unsigned grid = min((b.cap_cells + 255u) / 256u, 4096u);
     hipLaunchKernelGGL(k_build_nchild, dim3(grid), dim3(256), 0, s, b.hdr, b.groups, b.topo, b.cap_cells,
                        walk_sorts_groups(n) ? b.ghist : nullptr);
