@@ -42,6 +42,22 @@ constexpr unsigned NGB_WAVES = 8;      // waves of a group with more candidates
 constexpr unsigned NGB_FEW = 512;
 constexpr unsigned NGB_MANY = 2048;
 constexpr unsigned NGB_PART = 8;       // particles of a part of a heavy group
+// A group whose list overflows stays with its wave all the same, which tests the
+// list whenever it is full, where it is one of many alike: leaving it, the pass would
+// walk the tree twice.  It is taken for such a group if
+//   * it has no more than twice a wave's share of the particles;
+//   * NGB_LIKE of 64 radii taken evenly from its system reach NGB_ALIKE of its largest;
+//   * its reach holds no more than NGB_DENSE times what the system's mean density puts
+//     there (the reach's particles: those listed, and of the cells on the stack the
+//     share of their boxes that lies in it), and
+//   * that makes no more than NGB_PAIRS pairs.
+// Each depends on the input alone.  Counts with these groups left to the later passes /
+// staying, us (one wave for every group from the start: third figure), of uniform
+// cubes: 60000 particles with 392 / 675 neighbours 119 / 80 (127), 197 / 124 (166),
+// 100000 with 400 / 693 136 / 105 (156), 224 / 156 (195), 500000 with 421 / 737 612 / 474
+// (513), 1010 / 683 (726), 2^20 with 427 1086 / 824 (870).
+constexpr unsigned NGB_LIKE = 48;
+constexpr float NGB_ALIKE = 0.7f, NGB_DENSE = 2.0f, NGB_PAIRS = 400.0f * NGB_LIST;
 constexpr unsigned NGB_ONE_PASS = 32768;  // particles up to which every group has NGB_WAVES waves
 constexpr unsigned NGB_LIST_HEAVY = 4096;
 constexpr float NGB_FAR = 1.0e18f;
@@ -216,7 +232,7 @@ __device__ void ngb_test(const NgbArgs &a, const uint32_t *list, unsigned n, uns
 // scalar registers and took 887 us against 809 at 2^20 particles).
 template <int NW>
 __device__ void ngb_density(const NgbArgs &a, const uint32_t *list, unsigned n, unsigned w, unsigned gn, float px,
-                            float py, float pz, float pr2, float ph, unsigned &cnt, float &rho) {
+                            float py, float pz, float pr2, float ph, unsigned &cnt, double &rho) {
     constexpr int K = 3, CHUNK = 1 << K;
     const unsigned ln = lane64();
     if (64 * w >= n) return;
@@ -256,14 +272,14 @@ __device__ void ngb_density(const NgbArgs &a, const uint32_t *list, unsigned n, 
         const float tot = reduce_pow2<K>(acc);
         const unsigned p = ln - c0;
         const float mine = __shfl(tot, (int)(bitrev_k<K>(p & (CHUNK - 1u)) << (6 - K)), 64);
-        rho += ln >= c0 && ln < c0 + cn ? mine : 0.0f;
+        rho += ln >= c0 && ln < c0 + cn ? (double)mine : 0.0;
     }
 }
 
 // Three passes over the groups (one of NW = NGB_WAVES in small trees: see
 // launch_passes).  The first (NW = 1) gives each group a wave and
-// leaves those with more than NGB_LIST candidates, of which it has then only
-// walked the tree, to the second, which gives each NGB_PART of their particles a
+// leaves those with more than NGB_LIST candidates, unless they are many alike (see
+// NGB_LIKE), to the second, which gives each NGB_PART of their particles a
 // workgroup of NGB_WAVES waves, as a group of their own (NGB_FEW heavy groups or
 // fewer; else whole groups): a cell per thread and step of the traversal, and the
 // tiles of candidates dealt to the waves.  Where most groups are heavy, more than
@@ -362,7 +378,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
         }
         const float open2 = rmax * rmax * (1.0f + 1.0e-5f);
         unsigned cnt = 0, cand = 0;  // cand: candidates listed so far
-        float rho = 0.0f;
+        double rho = 0.0;  // (in float32 the lists' sums of a group with several would each round)
         const unsigned obase = MODE == NGB_LISTS ? a.offset[oi] : 0u;
         const unsigned ocap = MODE == NGB_LISTS ? min(a.offset[oi] + a.count[oi], a.capacity) : 0u;
 
@@ -371,7 +387,37 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
         const uint4 tr = a.topo[root];
         const unsigned rn = uniform(tr.w & 255u);
         unsigned sb = 0, st = rn ? rn : 1u, gtop = 0, nl = 0;
-        bool overflow = false, later = false;
+        bool overflow = false, later = false, stay = false, full = false;
+        unsigned m = 0, nl0 = 0;  // cells of a step, candidates listed before it
+        // Whether the group's box is within its largest radius of cell k's particle
+        // box (min xyz, max xyz: bx).
+        auto near_box = [&](unsigned k, float (&bx)[6]) {
+#pragma clang fp contract(off)
+            const float2 *cb = reinterpret_cast<const float2 *>(a.cbox + 6 * (size_t)k);
+            const float2 b0 = cb[0], b1 = cb[1], b2 = cb[2];
+            bx[0] = b0.x; bx[1] = b0.y; bx[2] = b1.x;
+            bx[3] = b1.y; bx[4] = b2.x; bx[5] = b2.y;
+            float gap2 = 0.0f;
+#pragma unroll
+            for (int d = 0; d < 3; d++) {
+                const float u = bx[d] - bmax[d];
+                const float v = bmin[d] - bx[3 + d];
+                const float gp = fmaxf(fmaxf(u, v), 0.0f);
+                gap2 = gap2 + gp * gp;
+            }
+            return gap2 <= open2;
+        };
+        // Of y particles in the box b, the share within the largest radius of the group's box.
+        auto in_reach = [&](const float (&b)[6], unsigned y) {
+            float v = (float)y;
+#pragma unroll
+            for (int d = 0; d < 3; d++) {
+                const float ext = b[3 + d] - b[d];
+                const float in = fminf(bmax[d] + rmax, b[3 + d]) - fmaxf(bmin[d] - rmax, b[d]);
+                v *= ext > 0.0f ? fmaxf(in, 0.0f) / ext : 1.0f;
+            }
+            return v;
+        };
         auto test_list = [&]() {
             __syncthreads();
             if (MODE == NGB_DENSITY) {
@@ -398,6 +444,8 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
         const unsigned first = rn ? tr.z + min(ln, rn - 1) : root;
         if (ln < st) s_stk[ln] = first;
         __syncthreads();
+        do {  // (once, but for a first pass whose list is full before the stack is empty)
+        full = false;
         while (st != sb || gtop > 0) {
             if (st == sb) {  // refill the LDS part of the stack from the global spill
                 const unsigned k = min(gtop, RING / 2);
@@ -407,7 +455,8 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
                 gtop -= k;
                 __syncthreads();
             }
-            const unsigned m = min(st - sb, HEAVY && gtop + (st - sb) <= WIDE ? STEP : 64u);
+            nl0 = nl;
+            m = min(st - sb, HEAVY && gtop + (st - sb) <= WIDE ? STEP : 64u);
             const bool valid = t < m;
             const unsigned c = valid ? s_stk[(st - m + t) & MASK] : 0u;
             st -= m;
@@ -415,22 +464,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
             const unsigned nch = tc.w & 255u;
             bool open = false;
             float bx[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};  // the cell's particle box: min xyz, max xyz
-            if (valid) {
-#pragma clang fp contract(off)
-                const float2 *cb = reinterpret_cast<const float2 *>(a.cbox + 6 * (size_t)c);
-                const float2 b0 = cb[0], b1 = cb[1], b2 = cb[2];
-                bx[0] = b0.x; bx[1] = b0.y; bx[2] = b1.x;
-                bx[3] = b1.y; bx[4] = b2.x; bx[5] = b2.y;
-                float gap2 = 0.0f;
-#pragma unroll
-                for (int d = 0; d < 3; d++) {
-                    const float u = bx[d] - bmax[d];
-                    const float v = bmin[d] - bx[3 + d];
-                    const float gp = fmaxf(fmaxf(u, v), 0.0f);
-                    gap2 = gap2 + gp * gp;
-                }
-                open = gap2 <= open2;
-            }
+            if (valid) open = near_box(c, bx);
             // The cells the group's box reaches, against its particles one by
             // one: a cell stays open when it is within some particle's radius.
             // Without it a group in a sphere's outskirts (a large box, large
@@ -469,7 +503,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
                 if (all[0]) {
                     if (nl + all[0] > LIST) {
                         if (!ALL) {
-                            later = true;
+                            full = true;
                             break;
                         }
                         test_list();
@@ -487,7 +521,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
                     if (ra[0] == 0) break;
                     if (nl + ra[0] > LIST) {
                         if (!ALL) {
-                            later = true;
+                            full = true;
                             break;
                         }
                         test_list();
@@ -498,7 +532,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
                     rem -= take;
                     src += take;
                 }
-                if (later) break;
+                if (full) break;
             }
             const unsigned used = st - sb;
             if (used + nsum > RING) {  // spill the bottom of the LDS ring
@@ -517,19 +551,46 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
             st += nsum;
             __syncthreads();
         }
+        if (!ALL && full) {  // the list does not take this step's candidates: the step is taken back
+            cand -= nl - nl0;
+            nl = nl0;
+            st += m;
+            if (!stay && nl > 0 && (unsigned long long)gn * gridDim.x <= 2ull * uniform(a.hdr->n)) {
+                const unsigned sample = tr.x + (unsigned)((2u * ln + 1u) * (unsigned long long)tr.y >> 7);
+                const float other = a.scale * a.radius[a.perm[sample]];
+                stay = (unsigned)__popcll(__ballot(other >= NGB_ALIKE * rmax)) >= NGB_LIKE;
+                if (stay) {
+                    float more = 0.0f, box[6];
+                    __threadfence_block();
+                    for (unsigned i = ln; i < gtop + (st - sb); i += 64) {
+                        const unsigned k = i < gtop ? gstk[i] : s_stk[(sb + i - gtop) & MASK];
+                        if (near_box(k, box)) more += in_reach(box, a.topo[k].y);
+                    }
+#pragma unroll
+                    for (int o = 32; o > 0; o >>= 1) more += __shfl_xor(more, o, 64);
+                    const float all = (float)cand + readlane_f(more, 0);
+                    for (int d = 0; d < 6; d++) box[d] = a.cbox[6 * (size_t)root + d];
+                    stay = all * (float)max(gn, 16u) <= NGB_PAIRS &&
+                           all <= NGB_DENSE * readlane_f(in_reach(box, tr.y), 0);
+                }
+            }
+            later = nl == 0 || !stay;
+            if (later) break;
+        }
+        if (!overflow && nl > 0) test_list();
+        } while (!ALL && full);
         if (!ALL) a.gflag[g] = later ? 1 : 0;
         if (later) {
             // (every lane stores the same word: no lane-dependent branch in this loop)
             a.heavy[uniform(atomicAdd(&a.hdr->ngb_heavy, ln == 0 ? 1u : 0u))] = g;
             continue;
         }
-        if (!overflow && nl > 0) test_list();
         if (overflow) {
             atomicOr(&a.hdr->flags, FLAG_STACK);
         } else if (HEAVY) {
             if (MODE != NGB_LISTS) {
                 s_pcnt[w][ln] = cnt;
-                s_rho[w][ln] = rho;
+                s_rho[w][ln] = (float)rho;
                 __syncthreads();
                 if (w == 0 && ln < gn) {
                     // the waves' sums in float64, rounded once: added in float32 one
@@ -546,7 +607,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
             }
         } else if (ln < gn) {
             if (MODE != NGB_LISTS) a.count[oi] = cnt;
-            if (MODE == NGB_DENSITY) a.rho[oi] = rho;
+            if (MODE == NGB_DENSITY) a.rho[oi] = (float)rho;
         }
         if (HEAVY) __syncthreads();  // the LDS arrays are free again
     }
