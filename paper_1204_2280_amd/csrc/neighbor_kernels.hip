@@ -44,20 +44,17 @@ constexpr unsigned NGB_MANY = 2048;
 constexpr unsigned NGB_PART = 8;       // particles of a part of a heavy group
 // A group whose list overflows stays with its wave all the same, which tests the
 // list whenever it is full, where it is one of many alike: leaving it, the pass would
-// walk the tree twice.  It is taken for such a group if
-//   * it has no more than twice a wave's share of the particles;
-//   * NGB_LIKE of 64 radii taken evenly from its system reach NGB_ALIKE of its largest;
-//   * its reach holds no more than NGB_DENSE times what the system's mean density puts
-//     there (the reach's particles: those listed, and of the cells on the stack the
-//     share of their boxes that lies in it), and
-//   * that makes no more than NGB_PAIRS pairs.
-// Each depends on the input alone.  Counts with these groups left to the later passes /
+// walk the tree twice.  It is taken for such a group if it has no more than twice a
+// wave's share of the particles, if NGB_LIKE of 64 radii taken evenly from its system
+// reach NGB_ALIKE of its largest, and if its box is no denser than its system's.  Each
+// depends on the input and the parameters alone.  Counts with these groups left to the later passes /
 // staying, us (one wave for every group from the start: third figure), of uniform
 // cubes: 60000 particles with 392 / 675 neighbours 119 / 80 (127), 197 / 124 (166),
 // 100000 with 400 / 693 136 / 105 (156), 224 / 156 (195), 500000 with 421 / 737 612 / 474
-// (513), 1010 / 683 (726), 2^20 with 427 1086 / 824 (870).
+// (513), 1010 / 683 (726), 2^20 with 427 1086 / 824 (870).  (Of 60000 particles whose
+// radii are wide in a spot of the cube alone 98, staying there 405 (426).)
 constexpr unsigned NGB_LIKE = 48;
-constexpr float NGB_ALIKE = 0.7f, NGB_DENSE = 2.0f, NGB_PAIRS = 400.0f * NGB_LIST;
+constexpr float NGB_ALIKE = 0.7f;
 constexpr unsigned NGB_ONE_PASS = 32768;  // particles up to which every group has NGB_WAVES waves
 constexpr unsigned NGB_LIST_HEAVY = 4096;
 constexpr float NGB_FAR = 1.0e18f;
@@ -162,7 +159,7 @@ struct NgbArgs {
     const uint32_t *perm;
     const uint2 *groups;
     const float *radius;     // per input particle: radius (count, list) or h (density)
-    float scale;             // search radius = scale * radius (2 for density)
+    unsigned share;          // twice a wave's share of the particles
     uint32_t *wstack;
     const uint32_t *order;   // first pass: the groups in the queues' order (NULL: Morton)
     uint8_t *gflag;          // of each group: left by the first pass
@@ -293,6 +290,7 @@ template <int MODE, int NW, bool ALL>
 __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
     constexpr bool HEAVY = NW > 1, REST = NW == 1 && ALL;  // REST: the third pass
     static_assert(ALL || NW == 1, "only a first pass leaves groups");
+    constexpr float SCALE = MODE == NGB_DENSITY ? 2.0f : 1.0f;  // search radius to the caller's
     constexpr unsigned NT = 64 * NW, STEP = HEAVY ? 256u : 64u;  // cells taken per step at most
     constexpr unsigned RING = HEAVY ? 16u * STEP : NGB_LSTACK, MASK = RING - 1;
     constexpr unsigned LIST = HEAVY ? NGB_LIST_HEAVY : NGB_LIST;
@@ -361,7 +359,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
         const float4 p = a.spos[mine];
         const unsigned oi = a.perm[mine];
         const float hr = a.radius[oi];
-        const float rr = a.scale * hr;
+        const float rr = SCALE * hr;
         const float pr2 = rr * rr;
         // (every wave writes the same values)
         s_p[ln] = make_float4(p.x, p.y, p.z, ln < gn ? pr2 : -1.0f);
@@ -389,35 +387,6 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
         unsigned sb = 0, st = rn ? rn : 1u, gtop = 0, nl = 0;
         bool overflow = false, later = false, stay = false, full = false;
         unsigned m = 0, nl0 = 0;  // cells of a step, candidates listed before it
-        // Whether the group's box is within its largest radius of cell k's particle
-        // box (min xyz, max xyz: bx).
-        auto near_box = [&](unsigned k, float (&bx)[6]) {
-#pragma clang fp contract(off)
-            const float2 *cb = reinterpret_cast<const float2 *>(a.cbox + 6 * (size_t)k);
-            const float2 b0 = cb[0], b1 = cb[1], b2 = cb[2];
-            bx[0] = b0.x; bx[1] = b0.y; bx[2] = b1.x;
-            bx[3] = b1.y; bx[4] = b2.x; bx[5] = b2.y;
-            float gap2 = 0.0f;
-#pragma unroll
-            for (int d = 0; d < 3; d++) {
-                const float u = bx[d] - bmax[d];
-                const float v = bmin[d] - bx[3 + d];
-                const float gp = fmaxf(fmaxf(u, v), 0.0f);
-                gap2 = gap2 + gp * gp;
-            }
-            return gap2 <= open2;
-        };
-        // Of y particles in the box b, the share within the largest radius of the group's box.
-        auto in_reach = [&](const float (&b)[6], unsigned y) {
-            float v = (float)y;
-#pragma unroll
-            for (int d = 0; d < 3; d++) {
-                const float ext = b[3 + d] - b[d];
-                const float in = fminf(bmax[d] + rmax, b[3 + d]) - fmaxf(bmin[d] - rmax, b[d]);
-                v *= ext > 0.0f ? fmaxf(in, 0.0f) / ext : 1.0f;
-            }
-            return v;
-        };
         auto test_list = [&]() {
             __syncthreads();
             if (MODE == NGB_DENSITY) {
@@ -464,7 +433,22 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
             const unsigned nch = tc.w & 255u;
             bool open = false;
             float bx[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};  // the cell's particle box: min xyz, max xyz
-            if (valid) open = near_box(c, bx);
+            if (valid) {
+#pragma clang fp contract(off)
+                const float2 *cb = reinterpret_cast<const float2 *>(a.cbox + 6 * (size_t)c);
+                const float2 b0 = cb[0], b1 = cb[1], b2 = cb[2];
+                bx[0] = b0.x; bx[1] = b0.y; bx[2] = b1.x;
+                bx[3] = b1.y; bx[4] = b2.x; bx[5] = b2.y;
+                float gap2 = 0.0f;
+#pragma unroll
+                for (int d = 0; d < 3; d++) {
+                    const float u = bx[d] - bmax[d];
+                    const float v = bmin[d] - bx[3 + d];
+                    const float gp = fmaxf(fmaxf(u, v), 0.0f);
+                    gap2 = gap2 + gp * gp;
+                }
+                open = gap2 <= open2;
+            }
             // The cells the group's box reaches, against its particles one by
             // one: a cell stays open when it is within some particle's radius.
             // Without it a group in a sphere's outskirts (a large box, large
@@ -555,24 +539,21 @@ __global__ __launch_bounds__(64 * NW, 4) void k_neighbors(NgbArgs a) {
             cand -= nl - nl0;
             nl = nl0;
             st += m;
-            if (!stay && nl > 0 && (unsigned long long)gn * gridDim.x <= 2ull * uniform(a.hdr->n)) {
+            if (!stay && nl > 0 && gn <= a.share) {
                 const unsigned sample = tr.x + (unsigned)((2u * ln + 1u) * (unsigned long long)tr.y >> 7);
-                const float other = a.scale * a.radius[a.perm[sample]];
+                const float other = SCALE * a.radius[a.perm[sample]];
                 stay = (unsigned)__popcll(__ballot(other >= NGB_ALIKE * rmax)) >= NGB_LIKE;
-                if (stay) {
-                    float more = 0.0f, box[6];
-                    __threadfence_block();
-                    for (unsigned i = ln; i < gtop + (st - sb); i += 64) {
-                        const unsigned k = i < gtop ? gstk[i] : s_stk[(sb + i - gtop) & MASK];
-                        if (near_box(k, box)) more += in_reach(box, a.topo[k].y);
-                    }
+                // the particles that the system's mean density would put into the group's
+                // box, widened by their mean distance
+                const float gap = cbrtf(1.0f / (float)tr.y);
+                const float *rb = a.cbox + 6 * (size_t)root;
+                float mean = (float)tr.y;
 #pragma unroll
-                    for (int o = 32; o > 0; o >>= 1) more += __shfl_xor(more, o, 64);
-                    const float all = (float)cand + readlane_f(more, 0);
-                    for (int d = 0; d < 6; d++) box[d] = a.cbox[6 * (size_t)root + d];
-                    stay = all * (float)max(gn, 16u) <= NGB_PAIRS &&
-                           all <= NGB_DENSE * readlane_f(in_reach(box, tr.y), 0);
+                for (int d = 0; d < 3; d++) {
+                    const float ext = rb[3 + d] - rb[d];
+                    mean *= ext > 0.0f ? fminf((bmax[d] - bmin[d]) / ext + gap, 1.0f) : 1.0f;
                 }
+                stay = stay && (float)gn <= readlane_f(mean, 0);
             }
             later = nl == 0 || !stay;
             if (later) break;
@@ -705,7 +686,7 @@ hipError_t launch_neighbors(const Buffers &b, int mode, const float *radius, uin
     a.perm = b.vals[0];
     a.groups = b.groups;
     a.radius = radius;
-    a.scale = mode == NGB_DENSITY ? 2.0f : 1.0f;
+    a.share = (unsigned)std::min<uint64_t>(2ull * n / b.walk_waves, 64u);
     a.wstack = b.wstack;
     a.heavy = b.nheavy;
     a.gflag = b.gflag;
