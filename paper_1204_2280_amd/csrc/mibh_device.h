@@ -416,7 +416,13 @@ constexpr unsigned SORT_BUCKET = 4096;       // elements one workgroup sorts in 
 // 2^22 the chip is full and the sample per bucket, 4096 of 8 lists at most, thin:
 // 1024 330, 1365 312.
 __host__ __device__ inline unsigned sort_bucket_mean(unsigned n) { return n <= 1u << 21 ? 1024u : 1365u; }
-constexpr unsigned SORT_MAX_BUCKETS = 4096;  // splitters and counts of all buckets fit LDS
+// The counting kernel keeps splitters and counts of all buckets in LDS, 16 bytes a
+// bucket: 64 KB with this many, what a launch gets without asking for more, and two
+// workgroups of 1024 threads, a full compute unit, fit.  Twice as many buckets would
+// leave one of the two, and the dependent reads of each particle's search are what
+// the kernel waits for; from memory they would take several times as long each.
+// (Neither was built: larger inputs keep the radix sort, 1.55 ms at 2^24 particles.)
+constexpr unsigned SORT_MAX_BUCKETS = 4096;
 // shared digits of a particle that the tree build takes from its keys
 constexpr int8_t CL_FROM_KEYS = 127;
 __host__ __device__ inline unsigned sort_buckets(unsigned n, unsigned mean) {

@@ -9,7 +9,8 @@
 //     W the cubic spline of Monaghan & Lattanzio (1985).
 //
 // One wave64 per group, persistent waves on the walk's per-XCD group queues, and
-// eight for a group with many candidates or where groups are few.  The
+// eight for a group with many candidates (unless most have as many) or where
+// groups are few.  The
 // traversal opens a cell when the gap between the group's bounding box and
 // the cell's particle box (both float32, from the multipole pass) is within
 // the group's largest radius, with a relative margin of 1e-5 on the squared
@@ -47,9 +48,9 @@ constexpr unsigned NGB_PART = 8;       // particles of a part of a heavy group
 // walk the tree twice.  It is taken for such a group if it has no more than twice a
 // wave's share of the particles, if NGB_LIKE of 64 radii taken evenly from its system
 // reach NGB_ALIKE of its largest, and if its box is no denser than its system's.  Each
-// depends on the input and the parameters alone.  Counts with these groups left to the later passes /
-// staying, us (one wave for every group from the start: third figure), of uniform
-// cubes: 60000 particles with 392 / 675 neighbours 119 / 80 (127), 197 / 124 (166),
+// depends on the input and the parameters alone.  Counts with these groups left to the
+// later passes / staying, us (in brackets one wave for every group from the start), of
+// uniform cubes: 60000 particles with 392 / 675 neighbours 119 / 80 (127), 197 / 124 (166),
 // 100000 with 400 / 693 136 / 105 (156), 224 / 156 (195), 500000 with 421 / 737 612 / 474
 // (513), 1010 / 683 (726), 2^20 with 427 1086 / 824 (870).  (Of 60000 particles whose
 // radii are wide in a spot of the cube alone 98, staying there 405 (426).)
@@ -668,8 +669,8 @@ void launch_passes(NgbArgs a, unsigned n, unsigned waves, hipStream_t s) {
     const bool one = n <= NGB_ONE_PASS;
     if (one) a.heavy = nullptr;
     else hipLaunchKernelGGL((k_neighbors<MODE, 1, false>), dim3(waves), dim3(64), 0, s, a);
-    hipLaunchKernelGGL((k_neighbors<MODE, NGB_WAVES, true>), dim3(one ? waves : min(waves, 512u)), dim3(64 * NGB_WAVES), 0,
-                       s, a);
+    hipLaunchKernelGGL((k_neighbors<MODE, NGB_WAVES, true>), dim3(one ? waves : min(waves, 512u)),
+                       dim3(64 * NGB_WAVES), 0, s, a);
     if (!one) hipLaunchKernelGGL((k_neighbors<MODE, 1, true>), dim3(waves), dim3(64), 0, s, a);
 }
 

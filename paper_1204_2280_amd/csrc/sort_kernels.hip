@@ -83,9 +83,10 @@ __device__ __forceinline__ void sort_network(F order) {
                     if (i + j + k < N && (i + j) / (2 * p) == (i + j + k) / (2 * p)) order(i + j, i + j + k);
 }
 
-// First output of one merge step: outputs d .. of the merge of A = [a0, a0 +
-// la) and B = [a0 + la, a0 + la + lb) take lo elements of A and d - lo of B
-// first; less(i, j): element i of A goes before element j of B.
+// First output of one merge step, by the "merge path" method (Odeh, Green, Mwassi,
+// Shmueli & Birk 2012; Green, McColl & Bader 2012): outputs d .. of the merge of
+// A = [a0, a0 + la) and B = [a0 + la, a0 + la + lb) take lo elements of A and d - lo
+// of B first; less(i, j): element i of A goes before element j of B.
 template <typename F>
 __device__ __forceinline__ unsigned merge_path(unsigned a0, unsigned la, unsigned lb, unsigned d, F less) {
     unsigned lo = d > lb ? d - lb : 0u, hi = min(d, la);

@@ -408,7 +408,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_walk(WalkArgs a) {
             __syncthreads();
             slot = uniform(s_slot);
         } else {
-            slot = queue_next<false>(a.head, ngroups, qc);  // a large tree: more groups than workgroups
+            slot = queue_next<false>(a.head, ngroups, qc);  // many groups: more than workgroups by default
         }
         if (slot >= ngroups) break;
         const unsigned g = a.order ? uniform(a.order[slot]) : slot;
@@ -1019,6 +1019,10 @@ __global__ __launch_bounds__(PREFIX_THREADS) void k_walk_prefix(WalkArgs a, unsi
 // 87 / 81 / 130, 10000 163 / 135 / 165, 20000 191 / 213 / 338 (a cube 113 / 79 / 117);
 // cap 8, 2000 106 / 54 / 55 / 76, 10000 149 / 136 / 210, 20000 206 / 251 / 430; cap 1,
 // 1000 105 / 58 / 59 / 83, 2000 111 / 68 / 100, 5000 162 / 185 / 303.
+// An active walk takes the waves of its whole tree: how many groups it visits is
+// known on the device alone (*qlen), and the launch's form is fixed before.  With few
+// groups due in a large tree the heaviest of them, on one wave, then sets the time;
+// the results do not depend on it.
 int walk_group_waves(unsigned n, unsigned cap) {
     const unsigned long long m = 67ull * n / (cap + 3u);
     return m <= 8192u ? 8 : m <= 15360u + 272u * cap ? 4 : m <= 73728u + 768u * cap ? 2 : 1;
